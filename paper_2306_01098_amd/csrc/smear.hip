@@ -7,16 +7,26 @@
 // from nested staples in three passes, all links periodic:
 //   T_{+nu}[A]_mu(x) = L_nu(x) A_mu(x+nu) L_nu(x+mu)^+
 //   T_{-nu}[A]_mu(x) = L_nu(x-nu)^+ A_mu(x-nu) L_nu(x-nu+mu)
-//   pass 1: S1[mu][nu,s] = T_{s nu}[L]_mu                 (24 fields)
-//   pass 2: Q[mu][nu] = sum_{rho not mu,nu} sum_r T_{r rho}[c5 L_mu + c7 P_sigma]
-//           with P_sigma = S1[mu][sigma,+] + S1[mu][sigma,-], sigma the
-//           fourth direction                                  (12 fields)
-//   pass 3: F_mu = c1 L_mu + sum_{nu,s} T_{s nu}[c3 L_mu + Q[mu][nu] + cL S1[mu][nu,s]]
+//   pass 1: Z[mu][nu] = c5 L_mu + c7 sum_s T_{s nu}[L]_mu             (12 fields)
+//   pass 2: R[mu][nu] = c3 L_mu + sum_{rho not mu,nu} sum_r T_{r rho}[Z[mu][sigma]]
+//           with sigma the fourth direction                          (12 fields)
+//   pass 3: F_mu = c1 L_mu + sum_{nu,s} T_{s nu}[R[mu][nu] + cL T_{s nu}[L]_mu]
 // which expands to the 6 three-link, 24 five-link, 48 seven-link and 6 Lepage
-// paths.  These are one-off per gauge field, so the passes favour clarity
-// (one thread per output matrix, matrices stored whole) over bandwidth.
+// paths.  The inner staple of the Lepage term is formed again in pass 3, so
+// that pass 1 need not store the 24 signed staples.
+//
+// Bound: the matrices of neighbouring sites past the L2 and from L2 to L1, not
+// the FP64 units (about 40 % busy).  At 32^4 (1M sites) one thread per matrix
+// with matrices stored whole took 21.1 ms; element planes (whole-line loads),
+// 12 instead of 24 fields from pass 1 and the projection and Naik links fused
+// into pass 3 9.3 ms, with the block order of work_item 8.3 ms, with products
+// accumulated by FMA 7.8 ms, with pass 2's three fields in a thread 7.6 ms.
+// The staples run in loops that are not unrolled, so that one staple's three
+// matrices are in registers at a time; forced below 256 VGPRs (three
+// wavefronts per SIMD) the kernels spill and take 22 ms.
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "api_util.hpp"
 #include "internal.hpp"
@@ -31,15 +41,7 @@ struct M3 {
     double2 e[9];  // row-major, (re, im)
 };
 
-__device__ __forceinline__ M3 ldm(const double *base, size_t idx) {
-    const double2 *p = reinterpret_cast<const double2 *>(base) + idx * 9;
-    M3 m;
-#pragma unroll
-    for (int k = 0; k < 9; ++k)
-        m.e[k] = p[k];
-    return m;
-}
-
+// Matrix idx of a canonical link array (matrices stored whole).
 __device__ __forceinline__ void stm(double *base, size_t idx, const M3 &m) {
     double2 *p = reinterpret_cast<double2 *>(base) + idx * 9;
 #pragma unroll
@@ -47,71 +49,91 @@ __device__ __forceinline__ void stm(double *base, size_t idx, const M3 &m) {
         p[k] = m.e[k];
 }
 
+// Matrix of site x of field f in the workspace layout [field][element][site]:
+// a wavefront reads an element of 64 neighbouring sites as one 1 KiB request.
+__device__ __forceinline__ M3 ld_site(const double *base, size_t V, int f, int x) {
+    const double2 *p = reinterpret_cast<const double2 *>(base) + (size_t)f * 9 * V;
+    M3 m;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        m.e[k] = p[k * V + x];
+    return m;
+}
+
+__device__ __forceinline__ void st_site(double *base, size_t V, int f, int x, const M3 &m) {
+    double2 *p = reinterpret_cast<double2 *>(base) + (size_t)f * 9 * V;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        p[k * V + x] = m.e[k];
+}
+
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ double2 cmul_conj_b(double2 a, double2 b) {  // a conj(b)
-    return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
 __device__ __forceinline__ double2 cmul_conj_a(double2 a, double2 b) {  // conj(a) b
     return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
 
-// A B
-__device__ __forceinline__ M3 mul(const M3 &a, const M3 &b) {
+// s += a b, a conj(b), conj(a) b
+__device__ __forceinline__ void mac(double2 &s, double2 a, double2 b) {
+    s.x = fma(a.x, b.x, s.x);
+    s.x = fma(-a.y, b.y, s.x);
+    s.y = fma(a.x, b.y, s.y);
+    s.y = fma(a.y, b.x, s.y);
+}
+__device__ __forceinline__ void mac_conj_b(double2 &s, double2 a, double2 b) {
+    s.x = fma(a.x, b.x, s.x);
+    s.x = fma(a.y, b.y, s.x);
+    s.y = fma(-a.x, b.y, s.y);
+    s.y = fma(a.y, b.x, s.y);
+}
+
+// A B, or A^+ B
+template <bool ADJ = false> __device__ __forceinline__ M3 mul(const M3 &a, const M3 &b) {
     M3 c;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            double2 s = make_double2(0.0, 0.0);
+            double2 s = ADJ ? cmul_conj_a(a.e[i], b.e[j]) : cmul(a.e[3 * i], b.e[j]);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double2 t = cmul(a.e[3 * i + k], b.e[3 * k + j]);
-                s.x += t.x;
-                s.y += t.y;
+            for (int k = 1; k < 3; ++k) {
+                if (ADJ)
+                    mac_conj_b(s, b.e[3 * k + j], a.e[3 * k + i]);
+                else
+                    mac(s, a.e[3 * i + k], b.e[3 * k + j]);
             }
             c.e[3 * i + j] = s;
         }
     return c;
 }
 
-// A B^+
-__device__ __forceinline__ M3 mul_adj(const M3 &a, const M3 &b) {
-    M3 c;
+// acc += A B D^+ (MINUS false) or A^+ B D (MINUS), one row of A B at a time.
+template <bool MINUS> __device__ __forceinline__ void mac_staple(const M3 &a, const M3 &b, const M3 &d, M3 &acc) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            double2 s = make_double2(0.0, 0.0);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double2 t = cmul_conj_b(a.e[3 * i + k], b.e[3 * j + k]);
-                s.x += t.x;
-                s.y += t.y;
-            }
-            c.e[3 * i + j] = s;
-        }
-    return c;
-}
-
-// A^+ B
-__device__ __forceinline__ M3 adj_mul(const M3 &a, const M3 &b) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i) {
+        double2 t[3];
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            double2 s = make_double2(0.0, 0.0);
+            t[j] = MINUS ? cmul_conj_a(a.e[i], b.e[j]) : cmul(a.e[3 * i], b.e[j]);
+#pragma unroll
+            for (int k = 1; k < 3; ++k) {
+                if (MINUS)
+                    mac_conj_b(t[j], b.e[3 * k + j], a.e[3 * k + i]);
+                else
+                    mac(t[j], a.e[3 * i + k], b.e[3 * k + j]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const double2 t = cmul_conj_a(a.e[3 * k + i], b.e[3 * k + j]);
-                s.x += t.x;
-                s.y += t.y;
+                if (MINUS)
+                    mac(acc.e[3 * i + j], t[k], d.e[3 * k + j]);
+                else
+                    mac_conj_b(acc.e[3 * i + j], t[k], d.e[3 * j + k]);
             }
-            c.e[3 * i + j] = s;
-        }
-    return c;
+    }
 }
 
 __device__ __forceinline__ void axpy(double a, const M3 &x, M3 &y) {
@@ -132,133 +154,240 @@ __device__ __forceinline__ M3 zero3() {
 
 struct Lat {
     int n[4];  // Nx, Ny, Nz, Nt
-    int64_t V;
+    int V;
+    int by, sz;  // rows of y and planes of z in a column of the block order (divide Ny, Nz)
 };
 
-__device__ __forceinline__ void coords(const Lat &g, int64_t lex, int c[4]) {
-    c[0] = (int)(lex % g.n[0]);
-    lex /= g.n[0];
-    c[1] = (int)(lex % g.n[1]);
-    lex /= g.n[1];
-    c[2] = (int)(lex % g.n[2]);
-    c[3] = (int)(lex / g.n[2]);
+// Coordinates of a site and its neighbours' indices (periodic).
+struct Place {
+    int x, c[4];
+};
+
+__device__ __forceinline__ int stride_of(const Lat &g, int d) {
+    return d == 0 ? 1 : d == 1 ? g.n[0] : d == 2 ? g.n[0] * g.n[1] : g.n[0] * g.n[1] * g.n[2];
 }
 
-__device__ __forceinline__ int64_t lex_of(const Lat &g, const int c[4]) {
-    return c[0] + (int64_t)g.n[0] * (c[1] + (int64_t)g.n[1] * (c[2] + (int64_t)g.n[2] * c[3]));
+__device__ __forceinline__ Place place_of(const Lat &g, int x) {
+    Place p;
+    p.x = x;
+    p.c[0] = x % g.n[0];
+    x /= g.n[0];
+    p.c[1] = x % g.n[1];
+    x /= g.n[1];
+    p.c[2] = x % g.n[2];
+    p.c[3] = x / g.n[2];
+    return p;
 }
 
-// lex of site c + k * unit(d) (periodic)
-__device__ __forceinline__ int64_t shift(const Lat &g, const int c[4], int d, int k) {
-    int s[4] = {c[0], c[1], c[2], c[3]};
-    s[d] = ((s[d] + k) % g.n[d] + g.n[d]) % g.n[d];
-    return lex_of(g, s);
+// p + k along d (d uniform over the block, |k| <= 2 < every extent)
+__device__ __forceinline__ Place step(const Lat &g, const Place &p, int d, int k) {
+    Place q = p;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j == d) {
+            int v = p.c[j] + k;
+            v = v >= g.n[j] ? v - g.n[j] : v < 0 ? v + g.n[j] : v;
+            q.x += (v - p.c[j]) * stride_of(g, j);
+            q.c[j] = v;
+        }
+    return q;
 }
 
 // The k-th direction (k = 0, 1, 2) other than mu.
 __device__ __forceinline__ int other(int mu, int k) { return k < mu ? k : k + 1; }
 
-// Index (0..2) of direction nu among the directions other than mu.
-__device__ __forceinline__ int other_index(int mu, int nu) { return nu < mu ? nu : nu - 1; }
-
-// Staple T_{s nu}[A]_mu(x) of the field whose value at site y is A(y).
-template <typename F>
-__device__ __forceinline__ M3 staple(const Lat &g, const double *L, const int c[4], int mu, int nu, int s, F A) {
-    if (s > 0) {
-        const int64_t xn = shift(g, c, nu, 1);
-        const int64_t xm = shift(g, c, mu, 1);
-        const M3 a = ldm(L, (size_t)nu * g.V + lex_of(g, c));
-        const M3 b = A(xn);
-        const M3 d = ldm(L, (size_t)nu * g.V + xm);
-        return mul_adj(mul(a, b), d);
+// acc += T_{s nu}[A]_mu at p, A(q) the transported field's matrix at place q.
+template <int S, typename F>
+__device__ __forceinline__ void add_staple(const Lat &g, const double *L, const Place &p, int mu, int nu, F A,
+                                           M3 &acc) {
+    if constexpr (S > 0) {
+        const M3 a = ld_site(L, g.V, nu, p.x);
+        const M3 b = A(step(g, p, nu, 1));
+        const M3 d = ld_site(L, g.V, nu, step(g, p, mu, 1).x);
+        mac_staple<false>(a, b, d, acc);
+    } else {
+        const Place m = step(g, p, nu, -1);
+        const M3 a = ld_site(L, g.V, nu, m.x);
+        const M3 b = A(m);
+        const M3 d = ld_site(L, g.V, nu, step(g, m, mu, 1).x);
+        mac_staple<true>(a, b, d, acc);
     }
-    int cm[4] = {c[0], c[1], c[2], c[3]};
-    cm[nu] = (cm[nu] - 1 + g.n[nu]) % g.n[nu];
-    const int64_t xmn = lex_of(g, cm);
-    const int64_t xmnm = shift(g, cm, mu, 1);
-    const M3 a = ldm(L, (size_t)nu * g.V + xmn);
-    const M3 b = A(xmn);
-    const M3 d = ldm(L, (size_t)nu * g.V + xmnm);
-    return mul(adj_mul(a, b), d);
 }
 
-// pass 1: S1[(mu * 6 + 2 k + (s < 0)) V + x] = T_{s nu_k}[L]_mu(x)
-__global__ void __launch_bounds__(SB) staple1_kernel(Lat g, const double *L, double *S1) {
-    const int64_t gid = (int64_t)blockIdx.x * SB + threadIdx.x;
-    if (gid >= 24 * g.V)
-        return;
-    const int f = (int)(gid / g.V);
-    const int64_t x = gid - (int64_t)f * g.V;
-    const int mu = f / 6, j = f % 6;
-    const int nu = other(mu, j >> 1), s = (j & 1) ? -1 : 1;
-    int c[4];
-    coords(g, x, c);
-    const M3 r = staple(g, L, c, mu, nu, s, [&](int64_t y) { return ldm(L, (size_t)mu * g.V + y); });
-    stm(S1, (size_t)f * g.V + x, r);
+// Block order: workgroup b runs on XCD b mod 8, and each XCD takes one
+// contiguous range of the site order (slab of sz z-planes, band of by y-rows,
+// t, z, y, x), the nf fields of a block of sites side by side.  The links and
+// staples of a column's neighbouring t-slices then meet in the XCD's L2: with
+// by = 8, sz = 4 a slice of 32^4 is 1024 sites, and pass 2 fetches 5.6 GB past
+// the L2 instead of 7.3 GB when the fields run one after another in plain
+// site order (whole smearing at 32^4: 9.9 -> 8.3 ms; by, sz = 16, 4 and 8, 8
+// within 2 %, 4, 4 and 8, 2 5 % slower).
+__device__ __forceinline__ bool work_item(const Lat &g, int nf, int &f, int &x) {
+    const int per = gridDim.x / (8 * nf);  // site blocks of an XCD
+    const int j = blockIdx.x >> 3;
+    f = j % nf;
+    int ip = ((blockIdx.x & 7) * per + j / nf) * SB + threadIdx.x;
+    if (ip >= g.V)
+        return false;
+    x = ip % g.n[0];
+    ip /= g.n[0];
+    int y = ip % g.by;
+    ip /= g.by;
+    int z = ip % g.sz;
+    ip /= g.sz;
+    const int t = ip % g.n[3];
+    ip /= g.n[3];
+    const int nb = g.n[1] / g.by;
+    y += g.by * (ip % nb);
+    z += g.sz * (ip / nb);
+    x += g.n[0] * (y + g.n[1] * (z + g.n[2] * t));
+    return true;
 }
 
-// pass 2: Q[(mu * 3 + k) V + x] for nu = nu_k
-__global__ void __launch_bounds__(SB) staple2_kernel(Lat g, const double *L, const double *S1, double *Q,
-                                                      double c5, double c7) {
-    const int64_t gid = (int64_t)blockIdx.x * SB + threadIdx.x;
-    if (gid >= 12 * g.V)
+// canonical links -> [mu][element][site], 256 matrices of the canonical array
+// through LDS so that both sides are read and written in whole lines.
+__global__ void __launch_bounds__(SB) split_kernel(int64_t n, int V, const double *thin, double *L) {
+    __shared__ double2 lds[9 * SB];
+    const int64_t m0 = (int64_t)blockIdx.x * SB;
+    const double2 *src = reinterpret_cast<const double2 *>(thin) + m0 * 9;
+    const int here = (int)min((int64_t)SB, n - m0) * 9;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        if (k * SB + (int)threadIdx.x < here)
+            lds[k * SB + threadIdx.x] = src[k * SB + threadIdx.x];
+    __syncthreads();
+    const int64_t m = m0 + threadIdx.x;
+    if (m >= n)
         return;
-    const int f = (int)(gid / g.V);
-    const int64_t x = gid - (int64_t)f * g.V;
+    const int mu = (int)(m / V), x = (int)(m - (int64_t)mu * V);
+    double2 *dst = reinterpret_cast<double2 *>(L) + (size_t)mu * 9 * V + x;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        dst[(size_t)k * V] = lds[threadIdx.x * 9 + k];
+}
+
+// pass 1: field mu * 3 + k of Z, nu = nu_k
+__global__ void __launch_bounds__(SB) staple1_kernel(Lat g, const double *L, double *Z, double c5, double c7) {
+    int f, x;
+    if (!work_item(g, 12, f, x))
+        return;
     const int mu = f / 3, nu = other(mu, f % 3);
-    int c[4];
-    coords(g, x, c);
-    M3 acc = zero3();
+    const Place p = place_of(g, x);
+    auto A = [&](const Place &q) { return ld_site(L, g.V, mu, q.x); };
+    M3 acc = zero3(), z = zero3();
+    add_staple<1>(g, L, p, mu, nu, A, acc);
+    add_staple<-1>(g, L, p, mu, nu, A, acc);
+    axpy(c5, A(p), z);
+    axpy(c7, acc, z);
+    st_site(Z, g.V, f, x, z);
+}
+
+// pass 2: the three fields R[mu][.] in one thread, so that the two transported
+// fields of a direction rho share its links (100 matrices read per site
+// instead of 156 with one field a thread).  The loop over rho rotates the
+// accumulators: a0 is the one of nu = rho, which takes no staple along rho.
+__global__ void __launch_bounds__(SB) staple2_kernel(Lat g, const double *L, const double *Z, double *R, double c3) {
+    int mu, x;
+    if (!work_item(g, 4, mu, x))
+        return;
+    const Place p = place_of(g, x);
+    M3 a0 = zero3();
+    axpy(c3, ld_site(L, g.V, mu, x), a0);
+    M3 a1 = a0, a2 = a0;
 #pragma unroll 1
     for (int k = 0; k < 3; ++k) {
         const int rho = other(mu, k);
-        if (rho == nu)
-            continue;
-        const int sig = 6 - mu - nu - rho;
-        const int js = other_index(mu, sig);
-        auto Z = [&](int64_t y) {
-            M3 z = zero3();
-            axpy(c5, ldm(L, (size_t)mu * g.V + y), z);
-            axpy(c7, ldm(S1, (size_t)(mu * 6 + 2 * js) * g.V + y), z);
-            axpy(c7, ldm(S1, (size_t)(mu * 6 + 2 * js + 1) * g.V + y), z);
-            return z;
-        };
-        axpy(1.0, staple(g, L, c, mu, rho, 1, Z), acc);
-        axpy(1.0, staple(g, L, c, mu, rho, -1, Z), acc);
+        const int j1 = k == 2 ? 0 : k + 1, j2 = k == 0 ? 2 : k - 1;
+        const int xm = step(g, p, mu, 1).x - x;
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            const Place m = half ? step(g, p, rho, -1) : p;
+            const Place q = half ? m : step(g, p, rho, 1);
+            const M3 a = ld_site(L, g.V, rho, m.x);
+            const M3 d = ld_site(L, g.V, rho, m.x + xm);
+            const M3 z1 = ld_site(Z, g.V, mu * 3 + j2, q.x);
+            const M3 z2 = ld_site(Z, g.V, mu * 3 + j1, q.x);
+            if (half) {
+                mac_staple<true>(a, z1, d, a1);
+                mac_staple<true>(a, z2, d, a2);
+            } else {
+                mac_staple<false>(a, z1, d, a1);
+                mac_staple<false>(a, z2, d, a2);
+            }
+        }
+        const M3 t = a0;  // the next k leaves out the next accumulator
+        a0 = a1;
+        a1 = a2;
+        a2 = t;
     }
-    stm(Q, (size_t)f * g.V + x, acc);
+    st_site(R, g.V, mu * 3, x, a0);
+    st_site(R, g.V, mu * 3 + 1, x, a1);
+    st_site(R, g.V, mu * 3 + 2, x, a2);
 }
 
-// pass 3: F_mu(x)
-__global__ void __launch_bounds__(SB) staple3_kernel(Lat g, const double *L, const double *S1, const double *Q,
-                                                      double *F, double c1, double c3, double cl) {
-    const int64_t gid = (int64_t)blockIdx.x * SB + threadIdx.x;
-    if (gid >= 4 * g.V)
+__device__ __forceinline__ M3 project(const M3 &v);
+
+// pass 3.  Level 1 (LAST false): Y = projection of F, in the workspace layout.
+// Level 2 (LAST): F with the Lepage term to the canonical fat links, and the
+// Naik links W_mu(x) = cn L_mu(x) L_mu(x+mu) L_mu(x+2mu).
+template <bool LAST>
+__global__ void __launch_bounds__(SB) staple3_kernel(Lat g, const double *L, const double *R, double *F, double *W,
+                                                      double c1, double cl, double cn) {
+    int mu, x;
+    if (!work_item(g, 4, mu, x))
         return;
-    const int mu = (int)(gid / g.V);
-    const int64_t x = gid - (int64_t)mu * g.V;
-    int c[4];
-    coords(g, x, c);
+    const Place p = place_of(g, x);
     M3 acc = zero3();
-    axpy(c1, ldm(L, (size_t)mu * g.V + x), acc);
-#pragma unroll 1
-    for (int k = 0; k < 3; ++k) {
-        const int nu = other(mu, k);
-#pragma unroll 1
-        for (int sj = 0; sj < 2; ++sj) {
-            const int s = sj ? -1 : 1;
-            auto A = [&](int64_t y) {
-                M3 z = zero3();
-                axpy(c3, ldm(L, (size_t)mu * g.V + y), z);
-                axpy(1.0, ldm(Q, (size_t)(mu * 3 + k) * g.V + y), z);
-                if (cl != 0.0)
-                    axpy(cl, ldm(S1, (size_t)(mu * 6 + 2 * k + sj) * g.V + y), z);
-                return z;
-            };
-            axpy(1.0, staple(g, L, c, mu, nu, s, A), acc);
+    {
+        const M3 l = ld_site(L, g.V, mu, x);
+        axpy(c1, l, acc);
+        if constexpr (LAST) {
+            const Place p1 = step(g, p, mu, 1);
+            const M3 n = mul(mul(l, ld_site(L, g.V, mu, p1.x)), ld_site(L, g.V, mu, step(g, p1, mu, 1).x));
+            M3 w = zero3();
+            axpy(cn, n, w);
+            stm(W, (size_t)mu * g.V + x, w);
         }
     }
-    stm(F, (size_t)mu * g.V + x, acc);
+#pragma unroll 1
+    for (int j = 0; j < 6; ++j) {
+        const int k = j >> 1, nu = other(mu, k);
+        const bool minus = j & 1;
+        const int xm = step(g, p, mu, 1).x - x;
+        const Place m = minus ? step(g, p, nu, -1) : p;   // the link a, and d at m + mu
+        const Place q = minus ? m : step(g, p, nu, 1);    // the transported field
+        M3 b;
+        if constexpr (LAST) {  // cl T[L]_mu(q) + R(q)
+            const Place m2 = minus ? step(g, m, nu, -1) : q;
+            const Place q2 = minus ? m2 : step(g, q, nu, 1);
+            b = zero3();
+            {
+                const M3 a2 = ld_site(L, g.V, nu, m2.x), b2 = ld_site(L, g.V, mu, q2.x);
+                const M3 d2 = ld_site(L, g.V, nu, m2.x + xm);
+                if (minus)
+                    mac_staple<true>(a2, b2, d2, b);
+                else
+                    mac_staple<false>(a2, b2, d2, b);
+            }
+            const M3 r = ld_site(R, g.V, mu * 3 + k, q.x);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                b.e[e].x = fma(cl, b.e[e].x, r.e[e].x);
+                b.e[e].y = fma(cl, b.e[e].y, r.e[e].y);
+            }
+        } else {
+            b = ld_site(R, g.V, mu * 3 + k, q.x);
+        }
+        const M3 a = ld_site(L, g.V, nu, m.x), d = ld_site(L, g.V, nu, m.x + xm);
+        if (minus)
+            mac_staple<true>(a, b, d, acc);
+        else
+            mac_staple<false>(a, b, d, acc);
+    }
+    if constexpr (LAST)
+        stm(F, (size_t)mu * g.V + x, acc);
+    else
+        st_site(F, g.V, mu, x, project(acc));
 }
 
 // Y = V (V^+ V)^(-1/2).  The eigenvalues g_i of the Hermitian Q = V^+ V come
@@ -268,12 +397,8 @@ __global__ void __launch_bounds__(SB) staple3_kernel(Lat g, const double *L, con
 // f0 = (u v^2 - w (u^2 + v)) / D, f1 = (2 u v - u^3 - w) / D, f2 = u / D,
 // D = w (u v - w): symmetric in the eigenvalues, so degenerate spectra are
 // harmless (Hasenfratz, Hoffmann and Schaefer, JHEP 0705:029).
-__global__ void __launch_bounds__(SB) project_kernel(int64_t n, const double *Vin, double *Y) {
-    const int64_t i = (int64_t)blockIdx.x * SB + threadIdx.x;
-    if (i >= n)
-        return;
-    const M3 v = ldm(Vin, (size_t)i);
-    const M3 q = adj_mul(v, v);
+__device__ __forceinline__ M3 project(const M3 &v) {
+    const M3 q = mul<true>(v, v);
     const double q00 = q.e[0].x, q11 = q.e[4].x, q22 = q.e[8].x;
     const double2 q01 = q.e[1], q02 = q.e[2], q12 = q.e[5];
     const double p1 = q01.x * q01.x + q01.y * q01.y + q02.x * q02.x + q02.y * q02.y + q12.x * q12.x +
@@ -313,54 +438,45 @@ __global__ void __launch_bounds__(SB) project_kernel(int64_t n, const double *Vi
     h.e[0].x = h.e[4].x = h.e[8].x = f0;
     axpy(f1, q, h);
     axpy(f2, q2, h);
-    stm(Y, (size_t)i, mul(v, h));
+    return mul(v, h);
 }
 
-// W_mu(x) = c Y_mu(x) Y_mu(x + mu) Y_mu(x + 2 mu)
-__global__ void __launch_bounds__(SB) naik_kernel(Lat g, const double *Y, double *W, double cn) {
-    const int64_t gid = (int64_t)blockIdx.x * SB + threadIdx.x;
-    if (gid >= 4 * g.V)
-        return;
-    const int mu = (int)(gid / g.V);
-    const int64_t x = gid - (int64_t)mu * g.V;
-    int c[4];
-    coords(g, x, c);
-    const M3 a = ldm(Y, (size_t)mu * g.V + x);
-    const M3 b = ldm(Y, (size_t)mu * g.V + shift(g, c, mu, 1));
-    const M3 d = ldm(Y, (size_t)mu * g.V + shift(g, c, mu, 2));
-    M3 r = mul(mul(a, b), d);
-    M3 out = zero3();
-    axpy(cn, r, out);
-    stm(W, (size_t)mu * g.V + x, out);
+unsigned blocks(const Lat &g, int nf) { return (unsigned)((((g.V + SB - 1) / SB + 7) / 8) * 8 * nf); }
+
+int divisor_upto(int n, int most) {
+    int d = most < n ? most : n;
+    while (n % d)
+        --d;
+    return d;
 }
 
-unsigned blocks(int64_t n) { return (unsigned)((n + SB - 1) / SB); }
-
+// 44 matrices per site, of which the passes use 32.
 struct SmearLayout {
-    size_t v, y, s1, q, total;
+    size_t u, y, z, r, total;
 };
 
 SmearLayout smear_layout(int64_t V) {
     const size_t mat = 144;
     SmearLayout L;
-    L.v = 0;
-    L.y = L.v + 4 * V * mat;
-    L.s1 = L.y + 4 * V * mat;
-    L.q = L.s1 + 24 * V * mat;
-    L.total = L.q + 12 * V * mat;
+    L.u = 0;
+    L.y = L.u + 4 * V * mat;
+    L.z = L.y + 4 * V * mat;
+    L.r = L.z + 12 * V * mat;
+    L.total = 44 * V * mat;
     return L;
 }
 
-hipError_t smear_level(const Lat &g, const double *L, double *S1, double *Q, double *F, double c1, double c3,
-                       double c5, double c7, double cl, hipStream_t st) {
-    staple1_kernel<<<blocks(24 * g.V), SB, 0, st>>>(g, L, S1);
+template <bool LAST>
+hipError_t smear_level(const Lat &g, const double *L, double *Z, double *R, double *F, double *W, double c1, double c3,
+                       double c5, double c7, double cl, double cn, hipStream_t st) {
+    staple1_kernel<<<blocks(g, 12), SB, 0, st>>>(g, L, Z, c5, c7);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    staple2_kernel<<<blocks(12 * g.V), SB, 0, st>>>(g, L, S1, Q, c5, c7);
+    staple2_kernel<<<blocks(g, 4), SB, 0, st>>>(g, L, Z, R, c3);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
-    staple3_kernel<<<blocks(4 * g.V), SB, 0, st>>>(g, L, S1, Q, F, c1, c3, cl);
+    staple3_kernel<LAST><<<blocks(g, 4), SB, 0, st>>>(g, L, R, F, W, c1, cl, cn);
     return hipGetLastError();
 }
 
@@ -393,32 +509,27 @@ hisq_status hisq_smear_links(hisq_context *ctx, const hisq_lattice *lat, const v
     Lat g;
     for (int d = 0; d < 4; ++d)
         g.n[d] = lat->dims[d];
-    g.V = (int64_t)g.n[0] * g.n[1] * g.n[2] * g.n[3];
+    g.V = g.n[0] * g.n[1] * g.n[2] * g.n[3];
+    g.by = divisor_upto(g.n[1], 8);
+    g.sz = divisor_upto(g.n[2], 4);
     const SmearLayout L = smear_layout(g.V);
     if (ws_bytes < L.total)
         return fail(HISQ_ERR_WORKSPACE, "workspace holds %zu bytes, needs %zu", ws_bytes, L.total);
     TRY(set_device(ctx));
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    char *W = static_cast<char *>(ws);
-    double *V1 = reinterpret_cast<double *>(W + L.v);
-    double *Y = reinterpret_cast<double *>(W + L.y);
-    double *S1 = reinterpret_cast<double *>(W + L.s1);
-    double *Q = reinterpret_cast<double *>(W + L.q);
-    const double *U = static_cast<const double *>(thin_c128);
-    // level 1 (fat7), projection, level 2 (fat7 + Lepage), Naik
-    hipError_t e = smear_level(g, U, S1, Q, V1, 1.0 / 8, 1.0 / 16, 1.0 / 64, 1.0 / 384, 0.0, st);
-    if (e == hipSuccess) {
-        project_kernel<<<blocks(4 * g.V), SB, 0, st>>>(4 * g.V, V1, Y);
-        e = hipGetLastError();
-    }
+    char *base = static_cast<char *>(ws);
+    double *U = reinterpret_cast<double *>(base + L.u);
+    double *Y = reinterpret_cast<double *>(base + L.y);
+    double *Z = reinterpret_cast<double *>(base + L.z);
+    double *R = reinterpret_cast<double *>(base + L.r);
+    split_kernel<<<(unsigned)((4 * (int64_t)g.V + SB - 1) / SB), SB, 0, st>>>(4 * (int64_t)g.V, g.V, static_cast<const double *>(thin_c128), U);
+    hipError_t e = hipGetLastError();
+    // level 1 (fat7) and projection, level 2 (fat7 + Lepage) and Naik
     if (e == hipSuccess)
-        e = smear_level(g, Y, S1, Q, static_cast<double *>(fat_c128), 1.0, 1.0 / 16, 1.0 / 64, 1.0 / 384,
-                        -1.0 / 8, st);
-    if (e == hipSuccess) {
-        naik_kernel<<<blocks(4 * g.V), SB, 0, st>>>(g, Y, static_cast<double *>(naik_c128),
-                                                      -1.0 / 24 + naik_eps / 8);
-        e = hipGetLastError();
-    }
+        e = smear_level<false>(g, U, Z, R, Y, nullptr, 1.0 / 8, 1.0 / 16, 1.0 / 64, 1.0 / 384, 0.0, 0.0, st);
+    if (e == hipSuccess)
+        e = smear_level<true>(g, Y, Z, R, static_cast<double *>(fat_c128), static_cast<double *>(naik_c128), 1.0,
+                              1.0 / 16, 1.0 / 64, 1.0 / 384, -1.0 / 8, -1.0 / 24 + naik_eps / 8, st);
     return e == hipSuccess ? HISQ_OK : device_fail(e, "smear_links");
 }
 

@@ -72,3 +72,15 @@ def test_smeared_links_drive_the_dslash(gpu_lib):
     got = h.unpack_field_to_host(lat, "fp64", out)[0]
     ref = O.dslash(dims, -1, Xr, Wr, src, 1)
     assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("dims", [(6, 10, 14, 4), (4, 22, 6, 4), (16, 8, 8, 4)])
+def test_smear_block_order_edges(gpu_lib, dims):
+    """Sites are walked in columns of up to 8 y-rows and 4 z-planes, a divisor
+    of each extent, in blocks of 256: extents whose divisors are 5 and 2, 2 and
+    3 and the full 8 and 4, with a last block that is partly empty and XCDs
+    without a block.  Same bound as for the smooth links above."""
+    U = gen.smooth_links(dims, gen.rng_for(522, 1), 0.5)
+    _, X, W = run(gpu_lib, dims, U, eps=-0.2)
+    Xr, Wr = S.hisq_smear(U, eps=-0.2)
+    assert rel(X, Xr) <= 1e-12 and rel(W, Wr) <= 1e-12
