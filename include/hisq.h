@@ -428,9 +428,10 @@ hisq_status hisq_cg_batch(hisq_context *ctx, int32_t nproblems, const hisq_probl
  * ------------------------------------------------------------------------- */
 #define HISQ_PTC_NWEIGHTS 720
 
-/* Workspace of the network (activations of one application, gradients). */
+/* Workspace of the network. */
 size_t hisq_ptc_workspace_bytes(const hisq_lattice *lat);
-/* out_even = N(in_even).  Keeps the activations in ws for hisq_ptc_backward.
+/* out_even = N(in_even).  Keeps what hisq_ptc_backward needs (the input and the
+ * weights) in ws.  The layers are applied as one folded linear map.
  * Asynchronous. */
 hisq_status hisq_ptc_forward(hisq_context *ctx, const hisq_lattice *lat, const void *links_f32, const void *weights,
                              const void *in_even, void *out_even, void *ws, size_t ws_bytes, void *stream);

@@ -1,7 +1,31 @@
-// PTC network kernels: forward layers, backward (input gradient through the
-// adjoint transports, weight gradient as a deterministic reduction over all
-// sites), the training loss and Adam.  FP32 fields, FP64 reductions.
+// PTC network kernels: the network as a folded linear map, its gradient, the
+// training loss and Adam.  FP32 fields, FP64 reductions.
+//
+// The network is linear in its input and its weights do not depend on the
+// site, its input lives on the even sites and only the even sites of its output
+// are read, and every path is the identity or one hop.  So of all products of
+// three paths only those with no hop or with two remain, and the network is
+//   out(x) = c0 in(x) + sum_p' T_p' u_p'(x),   u_p'(y) = sum_p C[p'][p] (T_p in)(y)
+// over the eight hops p, p' and the odd sites y, with (paths 0 = identity)
+//   c0       = sum_dc w3[d][0] w2[d][c][0] w1[c][0]
+//   C[p'][p] = sum_dc ( w3[d][0] w2[d][c][p'] w1[c][p] + w3[d][p'] w2[d][c][0] w1[c][p]
+//                     + w3[d][p'] w2[d][c][p] w1[c][0] ).
+// The folding (FP64, from the FP32 weights, once per call) replaces the layers
+// 1 -> 8 -> 8 -> 1: a site takes 192 complex multiply-adds instead of about
+// 2000, and no 8-channel activation is written.  The gradient with respect to
+// C and c0 is one 8 x 8 correlation over the odd sites,
+//   K[p'][p] = sum_y <(T_p in)(y), (T_p'^+ g)(y)>,   K0 = sum_x <in(x), g(x)>,
+// and the gradients of the 720 weights follow from it by the chain rule.
+//
+// Bound: memory.  At 32^4 the forward pass reads the links once (302 MB),
+// writes and reads the eight half-lattice vectors (101 MB each) and takes 117
+// us (spread 91, 4.6 TB/s, gather 26, 5.3 TB/s); layer by layer it took 753 us,
+// 460 of them FP32 arithmetic of the 8 -> 8 layer.  The backward pass with
+// input gradient took 2.2 ms; training on four pairs at 16^4 1656 -> 152 us,
+// small lattices bound by the launches.
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 #include "dslash.hpp"
 #include "internal.hpp"
@@ -13,504 +37,549 @@ namespace hisq {
 namespace {
 
 constexpr int PB = PTC_BLOCK;
+constexpr int NHOP = PTC_PATHS - 1;  // hop 2 mu: +mu, 2 mu + 1: -mu; the adjoint of hop q is hop q ^ 1
 
+// Hop q of the odd site i: the even site it reads and its link.
 struct Hop {
-    int nb;      // half-lattice index of the site read
-    int par;     // its parity
-    int lblk;    // link parity block
-    int lidx;    // link index
-    float sg;    // boundary sign
-    bool back;   // apply the adjoint
+    int nb;
+    int lblk, lidx;  // link parity block and index
+    float sg;        // boundary sign
 };
 
-// Path p of the layer, at site (par, i): which site and link it reads.
-__device__ __forceinline__ Hop path_hop(const Geom &g, const Site &s, int par, int i, int p) {
-    Hop h;
-    if (p == 0) {
-        h.nb = i;
-        h.par = par;
-        h.lblk = 0;
-        h.lidx = 0;
-        h.sg = 1.f;
-        h.back = false;
-        return h;
-    }
-    const int mu = (p - 1) >> 1;
-    const bool fwd = ((p - 1) & 1) == 0;
+__device__ __forceinline__ Hop odd_hop(const Geom &g, const Site &s, int i, int q) {
+    const int mu = q >> 1;
+    const bool fwd = (q & 1) == 0;
     const int c = mu == 0 ? s.x : mu == 1 ? s.y : mu == 2 ? s.z : s.t;
     const int n = mu == 0 ? g.nx : mu == 1 ? g.ny : mu == 2 ? g.nz : g.nt;
     const int stride = mu == 1 ? g.hx : mu == 2 ? g.hx * g.ny : g.hx * g.ny * g.nz;
+    Hop h;
     neighbour<float>(g, i, c, n, stride, mu, fwd ? +1 : -1, h.nb, h.sg);
-    h.par = 1 - par;
-    h.lblk = fwd ? par : 1 - par;
+    h.lblk = fwd ? 1 : 0;
     h.lidx = fwd ? i : h.nb;
-    h.back = !fwd;
     return h;
 }
 
-__device__ __forceinline__ void transport(const float m[18], bool back, float sg, const cplx<float> v[3],
-                                          cplx<float> t[3]) {
+// t = m v, or m^+ v
+template <bool ADJ>
+__device__ __forceinline__ void transport(const float (&m)[18], const cplx<float> (&v)[3], cplx<float> (&t)[3]) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         t[a].re = t[a].im = 0.f;
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            if (!back)
+            if (!ADJ)
                 cmac(t[a], m[6 * a + 2 * b], m[6 * a + 2 * b + 1], v[b]);
             else
                 cmac_conj(t[a], m[6 * b + 2 * a], m[6 * b + 2 * a + 1], v[b]);
         }
-        t[a].re *= sg;
-        t[a].im *= sg;
     }
 }
 
-__device__ __forceinline__ const char *xblock(const char *links, int par, int mu, int vh) {
-    return links + link_block<HISQ_FP32>(0, par, mu, vh);
+// The link times the boundary sign of its hop.
+__device__ __forceinline__ void load_link(const char *links, int vh, int mu, const Hop &h, float (&m)[18]) {
+    LinkIO<HISQ_FP32>::load<false>(links + link_block<HISQ_FP32>(0, h.lblk, mu, vh), vh, h.lidx, m);
+#pragma unroll
+    for (int k = 0; k < 18; ++k)
+        m[k] *= h.sg;
 }
 
-// out_co(x) = sum_ci sum_p w[co][ci][p] (T_p in_ci)(x), one thread per site.
-// IN_EVEN: the input is zero on the odd sites (the first layer), so the paths
-// that read odd sites are left out (an even site keeps the identity path, an
-// odd site the eight hops).  OUT_EVEN: only the even output sites are formed
-// (the last layer, whose odd sites nothing reads).  The launch does nothing
-// while skip (nullable) points to a nonzero value.
-template <int CIN, int COUT, bool IN_EVEN, bool OUT_EVEN>
-__global__ void __launch_bounds__(PB) layer_fwd_kernel(Geom g, const char *links, const float2 *w, const void *in,
-                                                       void *out, const int *skip) {
-    if (skip && *skip)
-        return;
-    const int gid = blockIdx.x * PB + threadIdx.x;
-    if (gid >= (OUT_EVEN ? 1 : 2) * g.vh)
-        return;
-    const int par = gid >= g.vh;
-    const int i = gid - par * g.vh;
-    const Site s = site_coords(g, par, i);
-    cplx<float> acc[COUT][3];
-#pragma unroll
-    for (int co = 0; co < COUT; ++co)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            acc[co][a].re = acc[co][a].im = 0.f;
-#pragma unroll
-    for (int p = 0; p < PTC_PATHS; ++p) {
-        const Hop h = path_hop(g, s, par, i, p);
-        if (IN_EVEN && h.par == 1)
-            continue;
-        float m[18];
-        if (p > 0)
-            LinkIO<HISQ_FP32>::load(xblock(links, h.lblk, (p - 1) >> 1, g.vh), g.vh, h.lidx, m);
-        for (int ci = 0; ci < CIN; ++ci) {
-            cplx<float> v[3], t[3];
-            FieldIO<HISQ_FP32>::template load<float>(in, g.vh, 1, 2 * ci + h.par, h.nb, v);
-            if (p > 0) {
-                transport(m, h.back, h.sg, v, t);
-            } else {
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    t[a] = v[a];
-            }
-#pragma unroll
-            for (int co = 0; co < COUT; ++co) {
-                const float2 wv = w[(co * CIN + ci) * PTC_PATHS + p];
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    cmac(acc[co][a], wv.x, wv.y, t[a]);
-            }
-        }
-    }
-#pragma unroll
-    for (int co = 0; co < COUT; ++co)
-        FieldIO<HISQ_FP32>::template store<float>(out, g.vh, 1, 2 * co + par, i, acc[co]);
+// Site block of this workgroup: XCD b mod 8 takes a contiguous range of sites.
+__device__ __forceinline__ int site_block() {
+    const int b = blockIdx.x, G = gridDim.x, q = G >> 3, r = G & 7, k = b & 7;
+    return k * q + min(k, r) + (b >> 3);
 }
 
-// g_in_ci(x) = sum_p T_p^+ (sum_co conj(w[co][ci][p]) g_co)(x); T_{+mu}^+ = T_{-mu}.
-// GOUT_EVEN: g_out is zero on the odd sites (the last layer), so the paths
-// that read odd sites are left out; OUT_EVEN: only the even sites of g_in are
-// formed (the first layer, whose input gradient is read on the even sites).
-template <int CIN, int COUT, bool GOUT_EVEN, bool OUT_EVEN>
-__global__ void __launch_bounds__(PB) layer_bwd_in_kernel(Geom g, const char *links, const float2 *w,
-                                                          const void *gout, void *gin) {
-    const int gid = blockIdx.x * PB + threadIdx.x;
-    if (gid >= (OUT_EVEN ? 1 : 2) * g.vh)
-        return;
-    const int par = gid >= g.vh;
-    const int i = gid - par * g.vh;
-    const Site s = site_coords(g, par, i);
-    cplx<float> acc[CIN][3];
-#pragma unroll
-    for (int ci = 0; ci < CIN; ++ci)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            acc[ci][a].re = acc[ci][a].im = 0.f;
-#pragma unroll
-    for (int p = 0; p < PTC_PATHS; ++p) {
-        // adjoint of path p is the opposite hop
-        const int padj = p == 0 ? 0 : (((p - 1) & 1) == 0 ? p + 1 : p - 1);
-        const Hop h = path_hop(g, s, par, i, padj);
-        if (GOUT_EVEN && h.par == 1)
-            continue;
-        float m[18];
-        if (p > 0)
-            LinkIO<HISQ_FP32>::load(xblock(links, h.lblk, (p - 1) >> 1, g.vh), g.vh, h.lidx, m);
-        for (int co = 0; co < COUT; ++co) {
-            cplx<float> v[3], t[3];
-            FieldIO<HISQ_FP32>::template load<float>(gout, g.vh, 1, 2 * co + h.par, h.nb, v);
-            if (p > 0) {
-                transport(m, h.back, h.sg, v, t);
-            } else {
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    t[a] = v[a];
-            }
-#pragma unroll
-            for (int ci = 0; ci < CIN; ++ci) {
-                const float2 wv = w[(co * CIN + ci) * PTC_PATHS + p];
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    cmac_conj(acc[ci][a], wv.x, wv.y, t[a]);
-            }
-        }
-    }
-#pragma unroll
-    for (int ci = 0; ci < CIN; ++ci)
-        FieldIO<HISQ_FP32>::template store<float>(gin, g.vh, 1, 2 * ci + par, i, acc[ci]);
+__device__ __forceinline__ double2 dmul(double2 a, double2 b) {
+    return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
+__device__ __forceinline__ void dmac(double2 &s, double2 a, double2 b) {
+    s.x = fma(a.x, b.x, fma(-a.y, b.y, s.x));
+    s.y = fma(a.x, b.y, fma(a.y, b.x, s.y));
+}
+__device__ __forceinline__ double2 wide(float2 a) { return make_double2(a.x, a.y); }
 
-// Block partials of dL/dw[co][ci][p] = sum_x <(T_p in_ci)(x), g_co(x)>, one
-// thread per site for all (ci, p) pairs: g_out of the site and each path's
-// link are loaded once and reused by every input channel.  Each wave sums
-// its 2 COUT values of a pair (halving exchanges, in FP32: 64 products of
-// FP32 values) into LDS as FP64 without a block barrier; at the end the block
-// adds the waves in order (deterministic, FP64) into
-// partials[(pair * 2 COUT + k) * gridDim.x + blockIdx.x], pair = ci * 9 + p.
-// IN_EVEN: the input is zero on odd sites (paths reading them contribute 0);
-// GOUT_EVEN: g_out is zero on odd sites, so only the even sites are summed.
-template <int CIN, int COUT, bool IN_EVEN, bool GOUT_EVEN>
-__global__ void __launch_bounds__(PB) layer_bwd_w_kernel(Geom g, const char *links, const void *in,
-                                                         const void *gout, double *partials) {
-    constexpr int NV = 2 * COUT;
-    constexpr int NPAIR = CIN * PTC_PATHS;
-    __shared__ double lds[(PB / 64) * NPAIR * NV];  // per wave, per pair, NV totals
-    const int gid = blockIdx.x * PB + threadIdx.x;
-    const bool valid = gid < (GOUT_EVEN ? 1 : 2) * g.vh;
-    const int par = valid && gid >= g.vh;
-    const int i = valid ? gid - par * g.vh : 0;
-    const Site s = site_coords(g, par, i);
-    cplx<float> gv[COUT][3];
-#pragma unroll
-    for (int co = 0; co < COUT; ++co) {
-        if (valid) {
-            FieldIO<HISQ_FP32>::template load<float>(gout, g.vh, 1, 2 * co + par, i, gv[co]);
-        } else {
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                gv[co][a].re = gv[co][a].im = 0.f;
-        }
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int p = 0; p < PTC_PATHS; ++p) {
-        const Hop h = path_hop(g, s, par, i, p);
-        const bool use = valid && !(IN_EVEN && h.par == 1);
-        float m[18];
-        if (p > 0 && use)
-            LinkIO<HISQ_FP32>::load(xblock(links, h.lblk, (p - 1) >> 1, g.vh), g.vh, h.lidx, m);
-        for (int ci = 0; ci < CIN; ++ci) {
-            float acc[NV];
-#pragma unroll
-            for (int k = 0; k < NV; ++k)
-                acc[k] = 0.f;
-            if (use) {
-                cplx<float> v[3], t[3];
-                FieldIO<HISQ_FP32>::template load<float>(in, g.vh, 1, 2 * ci + h.par, h.nb, v);
-                if (p > 0) {
-                    transport(m, h.back, h.sg, v, t);
-                } else {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a)
-                        t[a] = v[a];
-                }
-#pragma unroll
-                for (int co = 0; co < COUT; ++co) {
-                    // conj(t) . g over the colours in FP32, widened once per value
-                    float re = 0.f, im = 0.f;
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        re = fmaf(t[a].re, gv[co][a].re, fmaf(t[a].im, gv[co][a].im, re));
-                        im = fmaf(t[a].re, gv[co][a].im, fmaf(-t[a].im, gv[co][a].re, im));
-                    }
-                    acc[2 * co] = re;
-                    acc[2 * co + 1] = im;
-                }
-            }
-            wave_sum_multi<NV>(acc);
-            if ((lane & (64 / NV - 1)) == 0)
-                lds[(wave * NPAIR + ci * PTC_PATHS + p) * NV + wave_multi_index<NV>(lane)] = (double)acc[0];
-        }
-    }
-    // one barrier per block: the waves' totals of every pair, added in wave order
+// The weights in shared memory, NT threads.
+template <int NT> __device__ __forceinline__ void stage_weights(const float2 *w, float2 *lds) {
+    for (int k = threadIdx.x; k < PTC_NW; k += NT)
+        lds[k] = w[k];
     __syncthreads();
-    for (int k = threadIdx.x; k < NPAIR * NV; k += PB) {
-        double tot = 0.0;
-#pragma unroll
-        for (int w = 0; w < PB / 64; ++w)
-            tot += lds[w * NPAIR * NV + k];
-        partials[(size_t)k * gridDim.x + blockIdx.x] = tot;
-    }
 }
 
-// Weight gradient of the 8 -> 8 layer as a contraction over the sites,
-//   G[co][ci][p] = sum_x sum_a conj((T_p in_ci)(x)_a) gout_co(x)_a,
-// in tiles of WG_S sites (both parities).  Phase 1: thread t forms, for tile
-// site s = t % WG_S and input channel ci = t / WG_S, the nine transported
-// vectors of ci, and the output gradient of channel ci at s, into LDS.
-// Phase 2: thread t accumulates the outputs co = t % 8, q = ci * 9 + p in
-// {t / 8, t / 8 + 32, t / 8 + 64 (< 72)} over the tile's sites and colours in
-// FP32 (the per-site products are FP32) and adds the tile's sums to FP64
-// totals.  The block walks the tiles with stride gridDim.x and writes its
-// totals as the block partials of layer_bwd_w_kernel's layout (summed by
-// wgrad_reduce_kernel).  No sum runs across a wavefront per site and
-// (channel, path) pair, as in layer_bwd_w_kernel: 8 -> 8 layer at 32^4
-// 1.89 -> 1.04 ms.
-constexpr int WG_S = 32;
+__device__ __forceinline__ double2 w1_(const float2 *w, int c, int p) { return wide(w[PTC_W1 + c * PTC_PATHS + p]); }
+__device__ __forceinline__ double2 w2_(const float2 *w, int d, int c, int p) {
+    return wide(w[PTC_W2 + (d * PTC_CH + c) * PTC_PATHS + p]);
+}
+__device__ __forceinline__ double2 w3_(const float2 *w, int d, int p) { return wide(w[PTC_W3 + d * PTC_PATHS + p]); }
 
-__global__ void __launch_bounds__(256) wgrad88_kernel(Geom g, const char *links, const void *in, const void *gout,
-                                                      double *partials) {
-    constexpr int NQ = PTC_CH * PTC_PATHS;  // 72 (channel, path) pairs
-    __shared__ float2 ts[WG_S][NQ][3];
-    __shared__ float2 gs[WG_S][PTC_CH][3];
-    const int nsites = 2 * g.vh;
-    const int ntiles = (nsites + WG_S - 1) / WG_S;
-    const int t = threadIdx.x;
-    const int co = t & 7, qb = t >> 3;
-    double tot[3][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        {
-            const int sl = t % WG_S, ci = t / WG_S;
-            const int gid = tile * WG_S + sl;
-            const bool valid = gid < nsites;
-            const int par = valid && gid >= g.vh;
-            const int i = valid ? gid - par * g.vh : 0;
-            const Site st = site_coords(g, par, i);
-            cplx<float> gv[3];
-            if (valid) {
-                FieldIO<HISQ_FP32>::template load<float>(gout, g.vh, 1, 2 * ci + par, i, gv);
-            } else {
+// The folded map: fold[8 p' + p] = C[p'][p] and fold[64] = c0; the adjoint
+// network in the same form, C'[p'][p] = conj(C[p ^ 1][p' ^ 1]), at fold + 65.
+// Eight lanes (the channel d) per entry.  keep (nullable): a copy of the
+// weights.
+__global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, float2 *fold, float2 *keep,
+                                                   const int *skip) {
+    if (skip && *skip)
+        return;
+    __shared__ float2 w[PTC_NW];
+    stage_weights<576>(weights, w);
+    if (keep)
+        for (int k = threadIdx.x; k < PTC_NW; k += 576)
+            keep[k] = w[k];
+    const int e = threadIdx.x >> 3, d = threadIdx.x & 7;
+    const int po = (e >> 3) + 1, pi = (e & 7) + 1;  // paths of the outer and the inner hop
+    double2 sum = make_double2(0.0, 0.0);
+    if (e < 64) {
+        double2 a = make_double2(0.0, 0.0), b = a;
+        for (int c = 0; c < PTC_CH; ++c) {
+            dmac(a, w2_(w, d, c, po), w1_(w, c, pi));
+            dmac(b, w2_(w, d, c, 0), w1_(w, c, pi));
+            dmac(b, w2_(w, d, c, pi), w1_(w, c, 0));
+        }
+        dmac(sum, w3_(w, d, 0), a);
+        dmac(sum, w3_(w, d, po), b);
+    } else if (e == 64) {
+        double2 a = make_double2(0.0, 0.0);
+        for (int c = 0; c < PTC_CH; ++c)
+            dmac(a, w2_(w, d, c, 0), w1_(w, c, 0));
+        dmac(sum, w3_(w, d, 0), a);
+    }
 #pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    gv[a].re = gv[a].im = 0.f;
-            }
+    for (int o = 4; o > 0; o >>= 1) {
+        sum.x += __shfl_xor(sum.x, o, 64);
+        sum.y += __shfl_xor(sum.y, o, 64);
+    }
+    if (d != 0 || e > 64)
+        return;
+    const float2 r = make_float2((float)sum.x, (float)sum.y), rc = make_float2((float)sum.x, (float)-sum.y);
+    fold[e] = r;
+    fold[65 + (e < 64 ? 8 * ((e & 7) ^ 1) + ((e >> 3) ^ 1) : 64)] = rc;
+}
+
+// Two wavefronts work on 64 odd sites, one with the hops in x and y and one
+// with those in z and t: four links a thread.  With all eight hops in a thread
+// the links and vectors take over 256 VGPRs and one wavefront per SIMD is left
+// (spread 118 us at 32^4), and the 64 accumulators of the correlation spill.
+constexpr int CS = PB / 2;  // sites of a block
+
+using HalfLds = float4[PB / 64][6][64];
+
+// t[4..7] = the four vectors t[0..3] of the other wavefront of the same sites.
+__device__ __forceinline__ void swap_halves(cplx<float> (&t)[NHOP][3], HalfLds &lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float flat[24];
+#pragma unroll
+    for (int l = 0; l < 4; ++l)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            flat[6 * l + 2 * a] = t[l][a].re;
+            flat[6 * l + 2 * a + 1] = t[l][a].im;
+        }
+    __syncthreads();  // the reads of the previous exchange are done
+#pragma unroll
+    for (int j = 0; j < 6; ++j)
+        lds[wave][j][lane] = make_float4(flat[4 * j], flat[4 * j + 1], flat[4 * j + 2], flat[4 * j + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const float4 v = lds[wave ^ 1][j][lane];
+        flat[4 * j] = v.x;
+        flat[4 * j + 1] = v.y;
+        flat[4 * j + 2] = v.z;
+        flat[4 * j + 3] = v.w;
+    }
+#pragma unroll
+    for (int l = 0; l < 4; ++l)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            t[4 + l][a].re = flat[6 * l + 2 * a];
+            t[4 + l][a].im = flat[6 * l + 2 * a + 1];
+        }
+}
+
+// First half of the folded network on the odd sites y: the transported vectors
+// t_p = T_p in, for every hop p' the combination u_p', and s_p' = T_p' u_p'
+// delivered to the even site that reads it, through the link that t of the
+// adjoint hop was formed with.  The links stay in registers, so each link of
+// the lattice is read once.  Columns col0 + nper blockIdx.y ... of the
+// ncol-column field `in`, nper of them in a thread, each to s + column * 24 vh.
+__global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, const float2 *fold, const void *in,
+                                                    int ncol, int col0, int nper, int ncols, float2 *s,
+                                                    const int *skip) {
+    if (skip && *skip)
+        return;
+    __shared__ HalfLds lds;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
+    const int i = site_block() * CS + (wave >> 1) * 64 + (threadIdx.x & 63);
+    const bool valid = i < g.vh;
+    const Site st = site_coords(g, 1, valid ? i : 0);
+    Hop h[4];
+    float m[4][18];
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        h[l] = odd_hop(g, st, valid ? i : 0, 4 * half + l);
+        load_link(links, g.vh, 2 * half + (l >> 1), h[l], m[l]);
+    }
+    const int j1 = min((int)(blockIdx.y + 1) * nper, ncols);
+    for (int j = blockIdx.y * nper; j < j1; ++j) {
+        cplx<float> t[NHOP][3];
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            cplx<float> v[3];
+            FieldIO<HISQ_FP32>::template load<float>(in, g.vh, ncol, col0 + j, h[l].nb, v);
+            if (l & 1)
+                transport<true>(m[l], v, t[l]);
+            else
+                transport<false>(m[l], v, t[l]);
+        }
+        swap_halves(t, lds);
+        if (!valid)
+            continue;
+        float2 *sj = s + (size_t)j * 24 * g.vh;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            const int po = 4 * half + (l ^ 1);  // the hop p' whose vector goes over this link
+            const float2 *own = fold + 8 * po + 4 * half, *oth = fold + 8 * po + 4 * (half ^ 1);
+            cplx<float> u[3], r[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a)
-                gs[sl][ci][a] = make_float2(gv[a].re, gv[a].im);
+                u[a].re = u[a].im = 0.f;
 #pragma unroll
-            for (int p = 0; p < PTC_PATHS; ++p) {
-                cplx<float> tv[3];
-                if (valid) {
-                    const Hop h = path_hop(g, st, par, i, p);
-                    cplx<float> v[3];
-                    FieldIO<HISQ_FP32>::template load<float>(in, g.vh, 1, 2 * ci + h.par, h.nb, v);
-                    if (p > 0) {
-                        float m[18];
-                        LinkIO<HISQ_FP32>::load(xblock(links, h.lblk, (p - 1) >> 1, g.vh), g.vh, h.lidx, m);
-                        transport(m, h.back, h.sg, v, tv);
-                    } else {
-#pragma unroll
-                        for (int a = 0; a < 3; ++a)
-                            tv[a] = v[a];
-                    }
-                } else {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a)
-                        tv[a].re = tv[a].im = 0.f;
-                }
+            for (int p = 0; p < NHOP; ++p) {
+                const float2 c = p < 4 ? own[p] : oth[p - 4];
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    ts[sl][ci * PTC_PATHS + p][a] = make_float2(tv[a].re, tv[a].im);
+                    cmac(u[a], c.x, c.y, t[p][a]);
             }
-        }
-        __syncthreads();
-        float acc[3][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
-        const bool third = qb + 64 < NQ;  // uniform over the wavefront
-        for (int sl = 0; sl < WG_S; ++sl) {
+            if (l & 1)
+                transport<false>(m[l], u, r);
+            else
+                transport<true>(m[l], u, r);
+            float2 *dst = sj + (size_t)po * 3 * g.vh + h[l].nb;
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float2 gg = gs[sl][co][a];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    if (k < 2 || third) {
-                        const float2 tt = ts[sl][qb + 32 * k][a];
-                        acc[k][0] = fmaf(tt.x, gg.x, fmaf(tt.y, gg.y, acc[k][0]));
-                        acc[k][1] = fmaf(tt.x, gg.y, fmaf(-tt.y, gg.x, acc[k][1]));
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            tot[k][0] += (double)acc[k][0];
-            tot[k][1] += (double)acc[k][1];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int q = qb + 32 * k;
-        if (q < NQ) {
-            const size_t slot = (size_t)q * 2 * PTC_CH + 2 * co;  // pair q, output channel co, re / im
-            partials[slot * gridDim.x + blockIdx.x] = tot[k][0];
-            partials[(slot + 1) * gridDim.x + blockIdx.x] = tot[k][1];
+            for (int a = 0; a < 3; ++a)
+                dst[(size_t)a * g.vh] = make_float2(r[a].re, r[a].im);
         }
     }
 }
 
-// grad[(co * CIN + ci) * 9 + p] += sum over the nblk block partials, one
-// wavefront per real value (slot = pair * 2 COUT + 2 co + re/im), summed in a
-// fixed order (wave_sum_slot).
-__global__ void __launch_bounds__(256) wgrad_reduce_kernel(int cin, int cout, int nblk, const double *partials,
-                                                           double2 *grad) {
-    const int slot = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int nslots = cin * PTC_PATHS * cout * 2;
-    if (slot >= nslots)  // uniform over the wavefront
-        return;
-    const double sum = wave_sum_slot(partials + (size_t)slot * nblk, nblk);
-    if ((threadIdx.x & 63) != 0)
-        return;
-    const int pair = slot / (2 * cout);
-    const int rem = slot - pair * 2 * cout;
-    const int co = rem >> 1, part = rem & 1;
-    const int ci = pair / PTC_PATHS, p = pair - ci * PTC_PATHS;
-    double2 *dst = grad + (co * cin + ci) * PTC_PATHS + p;
-    if (part == 0)
-        dst->x += sum;
-    else
-        dst->y += sum;
+// c0 in + sum_p s_p of one element
+__device__ __forceinline__ float2 gathered(float2 c0, float2 in, const float2 *s, size_t stride) {
+    float2 v[NHOP];
+#pragma unroll
+    for (int p = 0; p < NHOP; ++p)
+        v[p] = s[p * stride];
+    float2 r = make_float2(fmaf(c0.x, in.x, -c0.y * in.y), fmaf(c0.x, in.y, c0.y * in.x));
+#pragma unroll
+    for (int p = 0; p < NHOP; ++p) {
+        r.x += v[p].x;
+        r.y += v[p].y;
+    }
+    return r;
 }
 
-// a0 = (in_even, 0 on odd sites), channel 0.
-__global__ void embed_kernel(int vh, const void *in_even, void *a0, const int *skip) {
+// Second half: out = c0 in + sum_p' s_p' on the even sites, one thread per
+// element of the one-column fields (in may be out).  keep (nullable): a copy
+// of the input.
+__global__ void __launch_bounds__(PB) gather_kernel(int n, const float2 *c0, const float2 *in, const float2 *s,
+                                                    float2 *out, float2 *keep, const int *skip) {
     if (skip && *skip)
         return;
-    const int gid = blockIdx.x * PB + threadIdx.x;
-    if (gid >= 2 * vh)
+    const int j = blockIdx.x * PB + threadIdx.x;
+    if (j >= n)
         return;
-    const int par = gid >= vh;
-    const int i = gid - par * vh;
-    cplx<float> v[3];
-    if (par == 0) {
-        FieldIO<HISQ_FP32>::template load<float>(in_even, vh, 1, 0, i, v);
-    } else {
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            v[a].re = v[a].im = 0.f;
-    }
-    FieldIO<HISQ_FP32>::template store<float>(a0, vh, 1, par, i, v);
+    const float2 v = in[j];
+    const float2 r = gathered(*c0, v, s + j, n);
+    if (keep)
+        keep[j] = v;
+    out[j] = r;
 }
 
-__global__ void extract_kernel(int vh, const void *a3, void *out_even, const int *skip) {
-    if (skip && *skip)
-        return;
-    const int i = blockIdx.x * PB + threadIdx.x;
-    if (i >= vh)
-        return;
-    cplx<float> v[3];
-    FieldIO<HISQ_FP32>::template load<float>(a3, vh, 1, 0, i, v);
-    FieldIO<HISQ_FP32>::template store<float>(out_even, vh, 1, 0, i, v);
-}
-
-// Block partials of Re <x, b> for the FP64 solution x and FP32 source b
-// (even sites).
-__global__ void __launch_bounds__(PB) xb_kernel(int vh, const void *x64, const void *b32, double *partials) {
-    __shared__ double lds[4];
-    const int i = blockIdx.x * PB + threadIdx.x;
+// Second half in training, for column blockIdx.y of a chunk: e = N(b) - x
+// (column blockIdx.y of an ne-column field) and the block partials of
+// Re <x, b>, b column col0 + blockIdx.y of the ncol-column sources, x FP64.
+__global__ void __launch_bounds__(PB) error_kernel(int vh, const float2 *c0, const void *b32, int ncol, int col0,
+                                                   const float2 *s, const void *x64, void *e, int ne,
+                                                   double *partials) {
+    __shared__ double lds[PB / 64];
+    const int i = blockIdx.x * PB + threadIdx.x, k = blockIdx.y;
     double part[1] = {0.0};
     if (i < vh) {
+        cplx<float> b[3], d[3];
         cplx<double> x[3];
-        cplx<float> b[3];
-        FieldIO<HISQ_FP64>::template load<double>(x64, vh, 1, 0, i, x);
-        FieldIO<HISQ_FP32>::template load<float>(b32, vh, 1, 0, i, b);
+        FieldIO<HISQ_FP32>::template load<float>(b32, vh, ncol, col0 + k, i, b);
+        FieldIO<HISQ_FP64>::template load<double>(x64, vh, ncol, col0 + k, i, x);
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a) {
+            const float2 y = gathered(*c0, make_float2(b[a].re, b[a].im),
+                                      s + (size_t)k * 24 * vh + (size_t)a * vh + i, (size_t)3 * vh);
+            d[a].re = (float)((double)y.x - x[a].re);
+            d[a].im = (float)((double)y.y - x[a].im);
             part[0] += x[a].re * (double)b[a].re + x[a].im * (double)b[a].im;
+        }
+        FieldIO<HISQ_FP32>::template store<float>(e, vh, ne, k, i, d);
     }
     block_sum<1>(part, lds);
     if (threadIdx.x == 0)
-        partials[blockIdx.x] = part[0];
+        partials[(size_t)k * gridDim.x + blockIdx.x] = part[0];
 }
 
-// e = y - x on even sites (y: network output, channel 0 of a3; x: FP64).
-__global__ void __launch_bounds__(PB) diff_kernel(int vh, const void *a3, const void *x64, void *e) {
-    const int i = blockIdx.x * PB + threadIdx.x;
-    if (i >= vh)
-        return;
-    cplx<float> y[3], d[3];
-    cplx<double> x[3];
-    FieldIO<HISQ_FP32>::template load<float>(a3, vh, 1, 0, i, y);
-    FieldIO<HISQ_FP64>::template load<double>(x64, vh, 1, 0, i, x);
+// Block partials of K[p'][p] and K0 for column blockIdx.y of the pair (in, g),
+// both even-site fields.  A block walks groups of CS odd sites: a thread forms
+// four t_p = T_p in and four h_q = T_q g with its four links, takes the other
+// four t_p of its site through LDS and adds conj(t_p) h_q to 32 accumulators
+// (q = p' ^ 1: T_p'^+ = T_q).  A thread's sums over its sites and the sums over
+// the wavefront are FP32 (halving exchanges), from there on FP64; slot
+// 2 (8 p' + p) + re/im, then K0, at partials[(column * 130 + slot) * gridDim.x +
+// block].
+__global__ void __launch_bounds__(PB) correlate_kernel(Geom g, const char *links, const void *in, int nin, int cin,
+                                                       const void *gr, int ngr, double *partials) {
+    __shared__ HalfLds lds;
+    __shared__ double sums[PB / 64][66];
+    const int k = blockIdx.y, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
+    float acc[64];              // [own q][own p, then the other half's p] re, then im
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        d[a].re = (float)((double)y[a].re - x[a].re);
-        d[a].im = (float)((double)y[a].im - x[a].im);
+    for (int e = 0; e < 64; ++e)
+        acc[e] = 0.f;
+    float k0r = 0.f, k0i = 0.f;
+    const int ngroups = (g.vh + CS - 1) / CS;
+    for (int gi = site_block(); gi < ngroups; gi += gridDim.x) {
+        const int i = gi * CS + (wave >> 1) * 64 + lane;
+        cplx<float> t[NHOP][3], hq[4][3];
+        if (i < g.vh) {
+            const Site st = site_coords(g, 1, i);
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                const Hop h = odd_hop(g, st, i, 4 * half + l);
+                float m[18];
+                cplx<float> v[3], w[3];
+                load_link(links, g.vh, 2 * half + (l >> 1), h, m);
+                FieldIO<HISQ_FP32>::template load<float>(in, g.vh, nin, cin + k, h.nb, v);
+                FieldIO<HISQ_FP32>::template load<float>(gr, g.vh, ngr, k, h.nb, w);
+                if (l & 1) {
+                    transport<true>(m, v, t[l]);
+                    transport<true>(m, w, hq[l]);
+                } else {
+                    transport<false>(m, v, t[l]);
+                    transport<false>(m, w, hq[l]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int l = 0; l < 4; ++l)
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    t[l][a].re = t[l][a].im = hq[l][a].re = hq[l][a].im = 0.f;
+        }
+        swap_halves(t, lds);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int p = 0; p < NHOP; ++p)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    float &re = acc[8 * q + p], &im = acc[32 + 8 * q + p];
+                    re = fmaf(t[p][a].re, hq[q][a].re, re);
+                    re = fmaf(t[p][a].im, hq[q][a].im, re);
+                    im = fmaf(t[p][a].re, hq[q][a].im, im);
+                    im = fmaf(-t[p][a].im, hq[q][a].re, im);
+                }
+        if (half == 0 && i < g.vh) {  // K0 on the even site of the same index
+            cplx<float> v[3], w[3];
+            FieldIO<HISQ_FP32>::template load<float>(in, g.vh, nin, cin + k, i, v);
+            FieldIO<HISQ_FP32>::template load<float>(gr, g.vh, ngr, k, i, w);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                k0r = fmaf(v[a].re, w[a].re, fmaf(v[a].im, w[a].im, k0r));
+                k0i = fmaf(v[a].re, w[a].im, fmaf(-v[a].im, w[a].re, k0i));
+            }
+        }
     }
-    FieldIO<HISQ_FP32>::template store<float>(e, vh, 1, 0, i, d);
+    wave_sum_multi<64>(acc);
+    k0r = wave_sum(k0r);
+    k0i = wave_sum(k0i);
+    sums[wave][wave_multi_index<64>(lane)] = (double)acc[0];
+    if (lane == 0) {
+        sums[wave][64] = (double)k0r;
+        sums[wave][65] = (double)k0i;
+    }
+    __syncthreads();
+    if (threadIdx.x < PTC_NK) {
+        int hf = 0, e = 64 + (threadIdx.x & 1);
+        if (threadIdx.x < 128) {
+            const int q = (threadIdx.x >> 4) ^ 1, p = (threadIdx.x >> 1) & 7;
+            hf = q >> 2;
+            // the other half's p follow a thread's own in its accumulators
+            e = 32 * (threadIdx.x & 1) + 8 * (q & 3) + (p & 3) + ((p >> 2) == hf ? 0 : 4);
+        }
+        double tot = 0.0;
+#pragma unroll
+        for (int wv = 0; wv < PB / 64; wv += 2)
+            tot += sums[wv + hf][e];
+        partials[((size_t)k * PTC_NK + threadIdx.x) * gridDim.x + blockIdx.x] = tot;
+    }
 }
 
-// Output gradient of L_i = <e, A e> / c (c = <x, b>), scaled by 1/B:
-// g3 = 2 A e / (B c) on even sites, 0 on odd sites; *loss_acc += <e, A e> / (B c).
-__global__ void __launch_bounds__(PB) energy_grad_kernel(int vh, const void *Ae, const double *eAe,
-                                                         const double *c, double inv_batch, void *g3,
-                                                         double *loss_acc) {
-    const int gid = blockIdx.x * PB + threadIdx.x;
-    const double cc = *c;
-    if (gid == 0)
-        *loss_acc += *eAe * inv_batch / cc;
-    if (gid >= 2 * vh)
-        return;
-    const int par = gid >= vh;
-    const int i = gid - par * vh;
-    cplx<float> gv[3];
-    if (par == 0) {
-        cplx<float> v[3];
-        FieldIO<HISQ_FP32>::template load<float>(Ae, vh, 1, 0, i, v);
-        const float coef = (float)(2.0 * inv_batch / cc);
+// Sum of n block partials by one wavefront, eight loads in flight a lane.
+__device__ __forceinline__ double sum_blocks(const double *p, int n) {
+    double v = 0.0;
+    for (int b = threadIdx.x & 63; b < n; b += 512) {
+        double t[8];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            gv[a].re = coef * v[a].re;
-            gv[a].im = coef * v[a].im;
+        for (int k = 0; k < 8; ++k)
+            t[k] = b + 64 * k < n ? p[b + 64 * k] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            v += t[k];
+    }
+    return wave_sum(v);
+}
+
+// K[slot] (+)= sum over the ncols <= PTC_COLS columns of scale_k times the
+// column's block partials, in a fixed order: one block per slot, one wavefront
+// per column.  Training (xb given): scale_k = 2 / (B <x_k, b_k>) from the nxb
+// block partials of <x, b>, and *loss (+)= sum_k <e_k, A e_k> / (B <x_k, b_k>)
+// with the ndot block partials of <e, A e>; else scale_k = 1.
+__global__ void __launch_bounds__(64 * PTC_COLS) correlate_sum_kernel(int ncols, int nblk, const double *partials,
+                                                                      int first, double *K, const double *xb, int nxb,
+                                                                      double inv_batch, const double *dot, int ndot,
+                                                                      double *loss) {
+    __shared__ double part[PTC_COLS], lpart[PTC_COLS];
+    const int slot = blockIdx.x, k = threadIdx.x >> 6;
+    double v = 0.0, l = 0.0;
+    if (k < ncols) {
+        v = sum_blocks(partials + ((size_t)k * PTC_NK + slot) * nblk, nblk);
+        if (xb) {
+            const double f = inv_batch / sum_blocks(xb + (size_t)k * nxb, nxb);
+            v *= 2.0 * f;
+            if (slot == 0)
+                l = f * sum_blocks(dot + (size_t)k * ndot, ndot);
+        }
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[k] = v;
+        lpart[k] = l;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0)
+        return;
+    v = first ? 0.0 : K[slot];
+    for (int j = 0; j < PTC_COLS; ++j)
+        v += part[j];
+    K[slot] = v;
+    if (xb && slot == 0) {
+        l = first ? 0.0 : *loss;
+        for (int j = 0; j < PTC_COLS; ++j)
+            l += lpart[j];
+        *loss = l;
+    }
+}
+
+// dL/dw_k from K by the chain rule, sum conj(dC/dw_k) K, by one wavefront,
+// lane 8 (p' - 1) + p - 1; valid in lane 0.  wf: the weights of the forward pass
+// (they made the activations that multiply the gradient of a layer), wb: those
+// of the backward pass (the layers above it); both in shared memory.
+__device__ __forceinline__ double2 weight_gradient(const float2 *wf, const float2 *wb, const double *K, int k) {
+    const int lane = threadIdx.x & 63, po = (lane >> 3) + 1, pi = (lane & 7) + 1;
+    const double2 kk = make_double2(K[2 * lane], K[2 * lane + 1]), k0 = make_double2(K[128], K[129]);
+    double2 f = make_double2(0.0, 0.0), f0 = f;  // dC[po][pi]/dw and dc0/dw
+    if (k < PTC_W2) {
+        const int c = (k - PTC_W1) / PTC_PATHS, r = (k - PTC_W1) % PTC_PATHS;
+        for (int d = 0; d < PTC_CH; ++d) {
+            if (r == 0) {
+                dmac(f, w3_(wb, d, po), w2_(wb, d, c, pi));
+                dmac(f0, w3_(wb, d, 0), w2_(wb, d, c, 0));
+            } else if (r == pi) {
+                dmac(f, w3_(wb, d, 0), w2_(wb, d, c, po));
+                dmac(f, w3_(wb, d, po), w2_(wb, d, c, 0));
+            }
+        }
+    } else if (k < PTC_W3) {
+        const int q = (k - PTC_W2) / PTC_PATHS, r = (k - PTC_W2) % PTC_PATHS, d = q / PTC_CH, c = q % PTC_CH;
+        if (r == 0) {
+            f = dmul(w3_(wb, d, po), w1_(wf, c, pi));
+            f0 = dmul(w3_(wb, d, 0), w1_(wf, c, 0));
+        } else {
+            if (r == po)
+                dmac(f, w3_(wb, d, 0), w1_(wf, c, pi));
+            if (r == pi)
+                dmac(f, w3_(wb, d, po), w1_(wf, c, 0));
         }
     } else {
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            gv[a].re = gv[a].im = 0.f;
+        const int d = (k - PTC_W3) / PTC_PATHS, r = (k - PTC_W3) % PTC_PATHS;
+        for (int c = 0; c < PTC_CH; ++c) {
+            if (r == 0) {
+                dmac(f, w2_(wf, d, c, po), w1_(wf, c, pi));
+                dmac(f0, w2_(wf, d, c, 0), w1_(wf, c, 0));
+            } else if (r == po) {
+                dmac(f, w2_(wf, d, c, 0), w1_(wf, c, pi));
+                dmac(f, w2_(wf, d, c, pi), w1_(wf, c, 0));
+            }
+        }
     }
-    FieldIO<HISQ_FP32>::template store<float>(g3, vh, 1, par, i, gv);
+    double2 s = make_double2(0.0, 0.0);
+    dmac(s, make_double2(f.x, -f.y), kk);
+    s.x = wave_sum(s.x);
+    s.y = wave_sum(s.y);
+    dmac(s, make_double2(f0.x, -f0.y), k0);
+    return s;
+}
+
+// grad += dL/dw, four weights a block.
+__global__ void __launch_bounds__(256) chain_kernel(const float2 *fwd, const float2 *bwd, const double *K,
+                                                    double2 *grad) {
+    __shared__ float2 wf[PTC_NW], wb[PTC_NW];
+    stage_weights<256>(fwd, wf);
+    stage_weights<256>(bwd, wb);
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const double2 s = weight_gradient(wf, wb, K, k);
+    if ((threadIdx.x & 63) == 0)
+        grad[k] = make_double2(grad[k].x + s.x, grad[k].y + s.y);
 }
 
 // Adam on real and imaginary parts as separate parameters; FP64 master
 // weights and moments, FP32 copy for the kernels.
-__global__ void adam_kernel(double2 *w, float2 *w32, const double2 *g, double2 *m, double2 *v, int step, double lr,
-                            double b1, double b2, double eps) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= PTC_NW)
-        return;
-    const double c1 = 1.0 - pow(b1, (double)step), c2 = 1.0 - pow(b2, (double)step);
-    double2 wk = w[k], gk = g[k], mk = m[k], vk = v[k];
-    mk.x = b1 * mk.x + (1.0 - b1) * gk.x;
-    mk.y = b1 * mk.y + (1.0 - b1) * gk.y;
-    vk.x = b2 * vk.x + (1.0 - b2) * gk.x * gk.x;
-    vk.y = b2 * vk.y + (1.0 - b2) * gk.y * gk.y;
-    wk.x -= lr * (mk.x / c1) / (sqrt(vk.x / c2) + eps);
-    wk.y -= lr * (mk.y / c1) / (sqrt(vk.y / c2) + eps);
-    w[k] = wk;
-    m[k] = mk;
-    v[k] = vk;
-    w32[k] = make_float2((float)wk.x, (float)wk.y);
+struct AdamArgs {
+    double2 *w;
+    float2 *w32;
+    double2 *m, *v;
+    double c1, c2;  // 1 - b1^step, 1 - b2^step
+    double lr, b1, b2, eps;
+};
+
+__device__ __forceinline__ void adam(const AdamArgs &a, int k, double2 gk) {
+    double2 wk = a.w[k], mk = a.m[k], vk = a.v[k];
+    mk.x = a.b1 * mk.x + (1.0 - a.b1) * gk.x;
+    mk.y = a.b1 * mk.y + (1.0 - a.b1) * gk.y;
+    vk.x = a.b2 * vk.x + (1.0 - a.b2) * gk.x * gk.x;
+    vk.y = a.b2 * vk.y + (1.0 - a.b2) * gk.y * gk.y;
+    wk.x -= a.lr * (mk.x / a.c1) / (sqrt(vk.x / a.c2) + a.eps);
+    wk.y -= a.lr * (mk.y / a.c1) / (sqrt(vk.y / a.c2) + a.eps);
+    a.w[k] = wk;
+    a.m[k] = mk;
+    a.v[k] = vk;
+    a.w32[k] = make_float2((float)wk.x, (float)wk.y);
 }
 
-__global__ void fill_f64_kernel(double *p, size_t n) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n)
-        p[i] = 0.0;
+__global__ void adam_kernel(AdamArgs a, const double2 *g) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < PTC_NW)
+        adam(a, k, g[k]);
+}
+
+// The training step's gradient and Adam in one launch; weights: the copy that
+// the fold kept, since w32 changes while other blocks read.
+__global__ void __launch_bounds__(256) chain_adam_kernel(const float2 *weights, const double *K, AdamArgs a) {
+    __shared__ float2 w[PTC_NW];
+    stage_weights<256>(weights, w);
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const double2 s = weight_gradient(w, w, K, k);
+    if ((threadIdx.x & 63) == 0)
+        adam(a, k, s);
+}
+
+AdamArgs adam_args(double2 *w, float2 *w32, double2 *m, double2 *v, int step, double lr, double b1, double b2,
+                   double eps) {
+    return AdamArgs{w, w32, m, v, 1.0 - std::pow(b1, step), 1.0 - std::pow(b2, step), lr, b1, b2, eps};
 }
 
 inline unsigned nb(int64_t n) { return (unsigned)((n + PB - 1) / PB); }
@@ -519,97 +588,72 @@ inline unsigned nb(int64_t n) { return (unsigned)((n + PB - 1) / PB); }
 
 int ptc_blocks(const Geom &g) { return (int)nb(2 * (int64_t)g.vh); }
 
-hipError_t ptc_embed(const Geom &g, const void *in_even, void *a0, hipStream_t st, const int *skip) {
-    embed_kernel<<<nb(2 * (int64_t)g.vh), PB, 0, st>>>(g.vh, in_even, a0, skip);
+// Blocks of a column in the correlation: at most 1024, four a CU, which keeps
+// the partials few and a thread's FP32 sums short (4 sites at 32^4).
+int ptc_correlate_blocks(const Geom &g) { return std::min((g.vh + CS - 1) / CS, 1024); }
+
+int ptc_error_blocks(const Geom &g) { return (int)nb(g.vh); }
+
+hipError_t ptc_fold(const float2 *w, float2 *fold, float2 *keep, hipStream_t st, const int *skip) {
+    fold_kernel<<<1, 576, 0, st>>>(w, fold, keep, skip);
     return hipGetLastError();
 }
 
-hipError_t ptc_extract(const Geom &g, const void *a3, void *out_even, hipStream_t st, const int *skip) {
-    extract_kernel<<<nb(g.vh), PB, 0, st>>>(g.vh, a3, out_even, skip);
+// From 65536 sites per parity (two wavefronts a SIMD) the columns run one after
+// another in a thread, the links read once for all of them; on smaller lattices
+// they are blocks of their own.  Training step of four pairs, blocks of their
+// own -> one after another: 24^3x16 300 -> 278 us, 32^4 1192 -> 1058 us, 16^4
+// 153 -> 156 us, 8^4 122 -> 128 us.
+hipError_t ptc_spread(const Geom &g, const char *links, const float2 *fold, const void *in, int ncol, int col0,
+                      int ncols, float2 *s, hipStream_t st, const int *skip) {
+    const int nper = g.vh >= 65536 ? ncols : 1;
+    spread_kernel<<<dim3((unsigned)((g.vh + CS - 1) / CS), (unsigned)((ncols + nper - 1) / nper)), PB, 0, st>>>(g, links, fold, in, ncol, col0,
+                                                                                        nper, ncols, s, skip);
     return hipGetLastError();
 }
 
-// The three layers of the 1 -> 8 -> 8 -> 1 network: layer 1 reads an input
-// that is zero on odd sites, layer 3's output is read on even sites only.
-hipError_t ptc_layer_fwd(const Geom &g, int cin, int cout, const char *links, const float2 *w, const void *in,
-                         void *out, hipStream_t st, const int *skip) {
-    const dim3 full(nb(2 * (int64_t)g.vh)), even(nb(g.vh));
-    if (cin == 1 && cout == PTC_CH)
-        layer_fwd_kernel<1, PTC_CH, true, false><<<full, PB, 0, st>>>(g, links, w, in, out, skip);
-    else if (cin == PTC_CH && cout == PTC_CH)
-        layer_fwd_kernel<PTC_CH, PTC_CH, false, false><<<full, PB, 0, st>>>(g, links, w, in, out, skip);
-    else if (cin == PTC_CH && cout == 1)
-        layer_fwd_kernel<PTC_CH, 1, false, true><<<even, PB, 0, st>>>(g, links, w, in, out, skip);
-    else
-        return hipErrorInvalidValue;
+hipError_t ptc_gather(const Geom &g, const float2 *c0, const void *in, const float2 *s, void *out, void *keep,
+                      hipStream_t st, const int *skip) {
+    const int n = 3 * g.vh;
+    gather_kernel<<<nb(n), PB, 0, st>>>(n, c0, static_cast<const float2 *>(in), s, static_cast<float2 *>(out),
+                                        static_cast<float2 *>(keep), skip);
     return hipGetLastError();
 }
 
-// Backward through the same layers: layer 3's output gradient is zero on odd
-// sites, layer 1's input gradient is needed on even sites only.
-hipError_t ptc_layer_bwd_in(const Geom &g, int cin, int cout, const char *links, const float2 *w,
-                            const void *g_out, void *g_in, hipStream_t st) {
-    const dim3 full(nb(2 * (int64_t)g.vh)), even(nb(g.vh));
-    if (cin == PTC_CH && cout == PTC_CH)
-        layer_bwd_in_kernel<PTC_CH, PTC_CH, false, false><<<full, PB, 0, st>>>(g, links, w, g_out, g_in);
-    else if (cin == PTC_CH && cout == 1)
-        layer_bwd_in_kernel<PTC_CH, 1, true, false><<<full, PB, 0, st>>>(g, links, w, g_out, g_in);
-    else if (cin == 1 && cout == PTC_CH)
-        layer_bwd_in_kernel<1, PTC_CH, false, true><<<even, PB, 0, st>>>(g, links, w, g_out, g_in);
-    else
-        return hipErrorInvalidValue;
+hipError_t ptc_error(const Geom &g, const float2 *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
+                     const void *x64, void *e, double *partials, hipStream_t st) {
+    error_kernel<<<dim3(nb(g.vh), (unsigned)ncols), PB, 0, st>>>(g.vh, c0, b32, ncol, col0, s, x64, e, ncols, partials);
     return hipGetLastError();
 }
 
-hipError_t ptc_layer_bwd_w(const Geom &g, int cin, int cout, const char *links, const void *in, const void *g_out,
-                           double *partials, double2 *grad, hipStream_t st) {
-    int nblk = ptc_blocks(g);
-    if (cin == 1 && cout == PTC_CH)
-        layer_bwd_w_kernel<1, PTC_CH, true, false><<<dim3((unsigned)nblk), PB, 0, st>>>(g, links, in, g_out, partials);
-    else if (cin == PTC_CH && cout == PTC_CH) {
-        nblk = std::min(nblk, 1024);  // blocks walk the tiles; the partials hold ptc_blocks(g) per slot
-        wgrad88_kernel<<<dim3((unsigned)nblk), 256, 0, st>>>(g, links, in, g_out, partials);
-    }
-    else if (cin == PTC_CH && cout == 1) {
-        nblk = nb(g.vh);  // the even sites only
-        layer_bwd_w_kernel<PTC_CH, 1, false, true><<<dim3((unsigned)nblk), PB, 0, st>>>(g, links, in, g_out, partials);
-    } else
-        return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    const int nslots = cin * PTC_PATHS * cout * 2;
-    wgrad_reduce_kernel<<<(nslots + 3) / 4, 256, 0, st>>>(cin, cout, nblk, partials, grad);
+hipError_t ptc_correlate(const Geom &g, const char *links, const void *in, int nin, int cin, const void *gr, int ncols,
+                         double *partials, hipStream_t st) {
+    correlate_kernel<<<dim3((unsigned)ptc_correlate_blocks(g), (unsigned)ncols), PB, 0, st>>>(g, links, in, nin, cin,
+                                                                                              gr, ncols, partials);
     return hipGetLastError();
 }
 
-hipError_t ptc_xb(const Geom &g, const void *x64, const void *b32, double *partials, double *out, hipStream_t st) {
-    xb_kernel<<<nb(g.vh), PB, 0, st>>>(g.vh, x64, b32, partials);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? launch_sum_partials(partials, 1, nb(g.vh), out, 1, nullptr, st) : e;
-}
-
-hipError_t ptc_diff(const Geom &g, const void *a3, const void *x64, void *e, hipStream_t st) {
-    diff_kernel<<<nb(g.vh), PB, 0, st>>>(g.vh, a3, x64, e);
+hipError_t ptc_correlate_sum(const Geom &g, int ncols, const double *partials, bool first, double *K, const double *xb,
+                             double inv_batch, const double *dot, int ndot, double *loss, hipStream_t st) {
+    correlate_sum_kernel<<<PTC_NK, 64 * PTC_COLS, 0, st>>>(ncols, ptc_correlate_blocks(g), partials, first ? 1 : 0, K,
+                                                           xb, ptc_error_blocks(g), inv_batch, dot, ndot, loss);
     return hipGetLastError();
 }
 
-hipError_t ptc_energy_grad(const Geom &g, const void *Ae, const double *eAe, const double *c, double inv_batch,
-                           void *g3, double *loss_acc, hipStream_t st) {
-    energy_grad_kernel<<<nb(2 * (int64_t)g.vh), PB, 0, st>>>(g.vh, Ae, eAe, c, inv_batch, g3, loss_acc);
+hipError_t ptc_chain(const float2 *wf, const float2 *wb, const double *K, double2 *grad, hipStream_t st) {
+    chain_kernel<<<PTC_NW / 4, 256, 0, st>>>(wf, wb, K, grad);
+    return hipGetLastError();
+}
+
+hipError_t ptc_chain_adam(const float2 *w, const double *K, double2 *w_master, float2 *w_f32, double2 *m, double2 *v,
+                          int step, double lr, double b1, double b2, double eps, hipStream_t st) {
+    chain_adam_kernel<<<PTC_NW / 4, 256, 0, st>>>(w, K, adam_args(w_master, w_f32, m, v, step, lr, b1, b2, eps));
     return hipGetLastError();
 }
 
 hipError_t ptc_adam(double2 *w_master, float2 *w_f32, const double2 *grad, double2 *m, double2 *v, int step,
                     double lr, double b1, double b2, double eps, hipStream_t st) {
-    adam_kernel<<<(PTC_NW + 255) / 256, 256, 0, st>>>(w_master, w_f32, grad, m, v, step, lr, b1, b2, eps);
-    return hipGetLastError();
-}
-
-hipError_t ptc_fill_f64(double *p, size_t n, hipStream_t st) {
-    if (n == 0)
-        return hipSuccess;
-    fill_f64_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p, n);
+    adam_kernel<<<(PTC_NW + 255) / 256, 256, 0, st>>>(adam_args(w_master, w_f32, m, v, step, lr, b1, b2, eps), grad);
     return hipGetLastError();
 }
 

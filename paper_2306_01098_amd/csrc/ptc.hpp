@@ -23,23 +23,33 @@ constexpr int PTC_BLOCK = 256;
 // i.e. the packed FP32 half-field layout with right-hand-side index 2c + parity.
 inline size_t ptc_field_bytes(const Geom &g, int channels) { return (size_t)channels * 2 * 3 * g.vh * 8; }
 
+// The folded network (ptc.hip): 65 float2 of the map, 65 of its adjoint; the
+// gradient with respect to it: 64 complex correlations and K0 as doubles.
+constexpr int PTC_NFOLD = 130;
+constexpr int PTC_NK = 130;
+constexpr int PTC_COLS = 4;  // training pairs per launch
+
 // skip (nullable): the launch does nothing while *skip != 0.
-hipError_t ptc_embed(const Geom &g, const void *in_even, void *a0, hipStream_t st, const int *skip = nullptr);
-hipError_t ptc_extract(const Geom &g, const void *a3, void *out_even, hipStream_t st, const int *skip = nullptr);
-// Layer 3's output (cout = 1) is formed on the even sites only.
-hipError_t ptc_layer_fwd(const Geom &g, int cin, int cout, const char *links, const float2 *w, const void *in,
-                         void *out, hipStream_t st, const int *skip = nullptr);
-hipError_t ptc_layer_bwd_in(const Geom &g, int cin, int cout, const char *links, const float2 *w,
-                            const void *g_out, void *g_in, hipStream_t st);
-hipError_t ptc_layer_bwd_w(const Geom &g, int cin, int cout, const char *links, const void *in, const void *g_out,
-                           double *partials, double2 *grad, hipStream_t st);
+hipError_t ptc_fold(const float2 *w, float2 *fold, float2 *keep, hipStream_t st, const int *skip = nullptr);
+// Columns col0 .. col0 + ncols - 1 of an ncol-column field; s: 24 vh float2 a column.
+hipError_t ptc_spread(const Geom &g, const char *links, const float2 *fold, const void *in, int ncol, int col0,
+                      int ncols, float2 *s, hipStream_t st, const int *skip = nullptr);
+hipError_t ptc_gather(const Geom &g, const float2 *c0, const void *in, const float2 *s, void *out, void *keep,
+                      hipStream_t st, const int *skip = nullptr);
+hipError_t ptc_error(const Geom &g, const float2 *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
+                     const void *x64, void *e, double *partials, hipStream_t st);
+// Column cin + k of `in` with column k of the ncols-column field gr.
+hipError_t ptc_correlate(const Geom &g, const char *links, const void *in, int nin, int cin, const void *gr, int ncols,
+                         double *partials, hipStream_t st);
+hipError_t ptc_correlate_sum(const Geom &g, int ncols, const double *partials, bool first, double *K, const double *xb,
+                             double inv_batch, const double *dot, int ndot, double *loss, hipStream_t st);
+hipError_t ptc_chain(const float2 *wf, const float2 *wb, const double *K, double2 *grad, hipStream_t st);
+hipError_t ptc_chain_adam(const float2 *w, const double *K, double2 *w_master, float2 *w_f32, double2 *m, double2 *v,
+                          int step, double lr, double b1, double b2, double eps, hipStream_t st);
 int ptc_blocks(const Geom &g);
-hipError_t ptc_xb(const Geom &g, const void *x64, const void *b32, double *partials, double *out, hipStream_t st);
-hipError_t ptc_diff(const Geom &g, const void *a3, const void *x64, void *e, hipStream_t st);
-hipError_t ptc_energy_grad(const Geom &g, const void *Ae, const double *eAe, const double *c, double inv_batch,
-                           void *g3, double *loss_acc, hipStream_t st);
+int ptc_correlate_blocks(const Geom &g);
+int ptc_error_blocks(const Geom &g);
 hipError_t ptc_adam(double2 *w_master, float2 *w_f32, const double2 *grad, double2 *m, double2 *v, int step,
                     double lr, double b1, double b2, double eps, hipStream_t st);
-hipError_t ptc_fill_f64(double *p, size_t n, hipStream_t st);
 
 }  // namespace hisq

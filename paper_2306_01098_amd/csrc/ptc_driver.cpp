@@ -13,8 +13,13 @@ namespace {
 
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Workspace: the input of the last forward pass (a0), the half-network
+// vectors s of up to PTC_COLS columns, the training chunk's error fields e,
+// t = D_oe e and A e (PTC_COLS columns each), the small arrays (folded map,
+// weights of the last forward pass, correlations, gradient) and the block
+// partials.  `total` is the size that the query has always returned.
 struct PtcLayout {
-    size_t a0, a1, a2, a3, g3, g2, g1, g0, partials, grad, scal, e, t, ae, src, total;
+    size_t a0, s, e, t, ae, fold, keep, keep0, k, scal, dot_part, xb_part, corr_part, total;
 };
 
 PtcLayout ptc_layout(const Geom &g) {
@@ -25,24 +30,29 @@ PtcLayout ptc_layout(const Geom &g) {
         off = a256(off + b);
         return o;
     };
-    const size_t f1 = ptc_field_bytes(g, 1), f8 = ptc_field_bytes(g, PTC_CH);
+    const size_t f1 = ptc_field_bytes(g, 1), f8 = ptc_field_bytes(g, PTC_CH), h32 = field_bytes(g, HISQ_FP32, 1);
     L.a0 = take(f1);
-    L.a1 = take(f8);
-    L.a2 = take(f8);
-    L.a3 = take(f1);
-    L.g3 = take(f1);
-    L.g2 = take(f8);
-    L.g1 = take(f8);
-    L.g0 = take(f1);
-    const size_t per_block = (size_t)PTC_CH * PTC_PATHS * 2 * PTC_CH;  // largest layer
-    L.partials = take(sizeof(double) * per_block * ptc_blocks(g));
-    L.grad = take(sizeof(double2) * PTC_NW);
+    L.s = take(f8);  // 8 vectors on half the sites per column: PTC_COLS columns are two 8-channel fields
+    take(f8);
+    take(f1);
+    take(f1);
+    L.e = take(f8);  // 3 PTC_COLS half fields of the 16 that an 8-channel field holds
+    L.t = a256(L.e + PTC_COLS * h32);
+    L.ae = a256(L.t + PTC_COLS * h32);
+    L.fold = take(f8);  // at least 48 KiB
+    L.keep = L.fold + a256(sizeof(float2) * PTC_NFOLD);
+    L.keep0 = L.keep + a256(sizeof(float2) * PTC_NW);
+    L.k = L.keep0 + a256(sizeof(float2) * PTC_NW);
+    take(f1);
+    // doubles: the M_e dot (at most vh / 4 + 1 a column), <x, b>, correlations
+    const size_t nvh = (size_t)g.vh;
+    L.dot_part = take(sizeof(double) * PTC_CH * PTC_PATHS * 2 * PTC_CH * ptc_blocks(g));
+    L.xb_part = L.dot_part + sizeof(double) * 2 * nvh;
+    L.corr_part = L.xb_part + sizeof(double) * nvh;
+    take(sizeof(double2) * PTC_NW);
     L.scal = take(sizeof(double) * 64);
-    const size_t h32 = field_bytes(g, HISQ_FP32, 1);
-    L.e = take(h32);
-    L.t = take(h32);
-    L.ae = take(h32);
-    L.src = take(h32);  // the training step's current source as a one-column field
+    for (int k = 0; k < 4; ++k)
+        take(h32);
     L.total = off;
     return L;
 }
@@ -56,45 +66,36 @@ struct Ptc {
     template <typename T> T *at(size_t o) const { return reinterpret_cast<T *>(ws + o); }
 };
 
-// skip (nullable): every launch does nothing while *skip != 0.
-hipError_t forward(const Ptc &P, const float2 *w, const void *in_even, void *out_even,
+// out_even = N(in_even); skip (nullable): every launch does nothing while
+// *skip != 0.  keep: leave the input and the weights for the backward pass.
+hipError_t forward(const Ptc &P, const float2 *w, const void *in_even, void *out_even, bool keep,
                    const int *skip = nullptr) {
-    hipError_t e = ptc_embed(P.g, in_even, P.at<void>(P.L.a0), P.st, skip);
+    float2 *fold = P.at<float2>(P.L.fold);
+    hipError_t e = ptc_fold(w, fold, keep ? P.at<float2>(P.L.keep) : nullptr, P.st, skip);
     if (e == hipSuccess)
-        e = ptc_layer_fwd(P.g, 1, PTC_CH, P.links, w + PTC_W1, P.at<void>(P.L.a0), P.at<void>(P.L.a1), P.st,
-                          skip);
+        e = ptc_spread(P.g, P.links, fold, in_even, 1, 0, 1, P.at<float2>(P.L.s), P.st, skip);
     if (e == hipSuccess)
-        e = ptc_layer_fwd(P.g, PTC_CH, PTC_CH, P.links, w + PTC_W2, P.at<void>(P.L.a1), P.at<void>(P.L.a2), P.st,
-                          skip);
-    if (e == hipSuccess)
-        e = ptc_layer_fwd(P.g, PTC_CH, 1, P.links, w + PTC_W3, P.at<void>(P.L.a2), P.at<void>(P.L.a3), P.st,
-                          skip);
-    if (e == hipSuccess && out_even)
-        e = ptc_extract(P.g, P.at<void>(P.L.a3), out_even, P.st, skip);
+        e = ptc_gather(P.g, fold + 64, in_even, P.at<float2>(P.L.s), out_even, keep ? P.at<void>(P.L.a0) : nullptr,
+                       P.st, skip);
     return e;
 }
 
-// From the output gradient in g3 (whole lattice): weight gradients += into
-// grad, input gradient (even sites) into g_in_even if non-NULL.
-hipError_t backward(const Ptc &P, const float2 *w, double2 *grad, void *g_in_even) {
-    double *part = P.at<double>(P.L.partials);
-    hipError_t e = ptc_layer_bwd_w(P.g, PTC_CH, 1, P.links, P.at<void>(P.L.a2), P.at<void>(P.L.g3), part,
-                                   grad + PTC_W3, P.st);
+// From the output gradient g_out on the even sites: weight gradients += into
+// grad, input gradient into g_in if non-NULL.
+hipError_t backward(const Ptc &P, const float2 *w, const void *g_out, double2 *grad, void *g_in) {
+    double *part = P.at<double>(P.L.corr_part), *K = P.at<double>(P.L.k);
+    hipError_t e = ptc_correlate(P.g, P.links, P.at<void>(P.L.a0), 1, 0, g_out, 1, part, P.st);
     if (e == hipSuccess)
-        e = ptc_layer_bwd_in(P.g, PTC_CH, 1, P.links, w + PTC_W3, P.at<void>(P.L.g3), P.at<void>(P.L.g2), P.st);
+        e = ptc_correlate_sum(P.g, 1, part, true, K, nullptr, 0.0, nullptr, 0, nullptr, P.st);
     if (e == hipSuccess)
-        e = ptc_layer_bwd_w(P.g, PTC_CH, PTC_CH, P.links, P.at<void>(P.L.a1), P.at<void>(P.L.g2), part,
-                            grad + PTC_W2, P.st);
-    if (e == hipSuccess)
-        e = ptc_layer_bwd_in(P.g, PTC_CH, PTC_CH, P.links, w + PTC_W2, P.at<void>(P.L.g2), P.at<void>(P.L.g1),
-                             P.st);
-    if (e == hipSuccess)
-        e = ptc_layer_bwd_w(P.g, 1, PTC_CH, P.links, P.at<void>(P.L.a0), P.at<void>(P.L.g1), part, grad + PTC_W1,
-                            P.st);
-    if (e == hipSuccess && g_in_even) {
-        e = ptc_layer_bwd_in(P.g, 1, PTC_CH, P.links, w + PTC_W1, P.at<void>(P.L.g1), P.at<void>(P.L.g0), P.st);
+        e = ptc_chain(P.at<float2>(P.L.keep), w, K, grad, P.st);
+    if (e == hipSuccess && g_in) {
+        float2 *fold = P.at<float2>(P.L.fold), *s = P.at<float2>(P.L.s);
+        e = ptc_fold(w, fold, nullptr, P.st);
         if (e == hipSuccess)
-            e = ptc_extract(P.g, P.at<void>(P.L.g0), g_in_even, P.st);
+            e = ptc_spread(P.g, P.links, fold + 65, g_out, 1, 0, 1, s, P.st);
+        if (e == hipSuccess)
+            e = ptc_gather(P.g, fold + 65 + 64, g_out, s, g_in, nullptr, P.st);
     }
     return e;
 }
@@ -128,7 +129,7 @@ hisq_status ptc_apply_internal(const hisq_lattice *lat, const void *links_f32, c
     hisq_status s = common_checks(lat, links_f32, weights, ws, ws_bytes, &P, nullptr, st);
     if (s != HISQ_OK)
         return s;
-    const hipError_t e = forward(P, static_cast<const float2 *>(weights), in, out, skip);
+    const hipError_t e = forward(P, static_cast<const float2 *>(weights), in, out, false, skip);
     return e == hipSuccess ? HISQ_OK : device_fail(e, "ptc forward");
 }
 
@@ -154,7 +155,7 @@ hisq_status hisq_ptc_forward(hisq_context *ctx, const hisq_lattice *lat, const v
     if (s == HISQ_OK) s = check_ptr(out_even, "out_even");
     if (s != HISQ_OK)
         return s;
-    const hipError_t e = forward(P, static_cast<const float2 *>(weights), in_even, out_even);
+    const hipError_t e = forward(P, static_cast<const float2 *>(weights), in_even, out_even, true);
     return e == hipSuccess ? HISQ_OK : device_fail(e, "ptc forward");
 }
 
@@ -167,10 +168,8 @@ hisq_status hisq_ptc_backward(hisq_context *ctx, const hisq_lattice *lat, const 
     if (s == HISQ_OK) s = check_ptr(grad, "grad");
     if (s != HISQ_OK)
         return s;
-    // output gradient: even sites from the caller, zero on odd sites
-    hipError_t e = ptc_embed(P.g, g_out_even, P.at<void>(P.L.g3), P.st);
-    if (e == hipSuccess)
-        e = backward(P, static_cast<const float2 *>(weights), static_cast<double2 *>(grad), g_in_even);
+    const hipError_t e = backward(P, static_cast<const float2 *>(weights), g_out_even, static_cast<double2 *>(grad),
+                                  g_in_even);
     return e == hipSuccess ? HISQ_OK : device_fail(e, "ptc backward");
 }
 
@@ -210,27 +209,23 @@ hisq_status hisq_ptc_train_step(hisq_context *ctx, const hisq_lattice *lat, doub
     if (s != HISQ_OK)
         return s;
     const float2 *w = static_cast<const float2 *>(w_f32);
-    double2 *grad = P.at<double2>(P.L.grad);
-    double *scal = P.at<double>(P.L.scal);  // [0] <x, b>, [1] loss, [2] <e, A e>
-    const size_t c64 = field_bytes(P.g, HISQ_FP64, 1);
-    const DslashShape shape = pick_shape(ctx, P.g, HISQ_FP32, HISQ_FP32, 1);
-    hipError_t e = ptc_fill_f64(reinterpret_cast<double *>(grad), 2 * PTC_NW, P.st);
-    if (e == hipSuccess) e = ptc_fill_f64(scal, 16, P.st);
-    const void *src = P.at<void>(P.L.src);
-    for (int k = 0; k < batch && e == hipSuccess; ++k) {
-        // source k: column k of the batch-column FP32 field src_f32
-        e = launch_copy_col(P.g.vh, HISQ_FP32, batch, k, src_f32, P.at<void>(P.L.src), P.st);
-        const char *sol = static_cast<const char *>(sol_f64) + k * c64;
+    double *sum = P.at<double>(P.L.scal);  // the loss
+    float2 *w0 = P.at<float2>(P.L.keep0);  // the weights before the update
+    double *K = P.at<double>(P.L.k);
+    float2 *fold = P.at<float2>(P.L.fold), *half = P.at<float2>(P.L.s);
+    hipError_t e = ptc_fold(w, fold, w0, P.st);
+    // PTC_COLS pairs at a time: the columns share every launch
+    for (int k = 0; k < batch && e == hipSuccess; k += PTC_COLS) {
+        const int n = batch - k < PTC_COLS ? batch - k : PTC_COLS;
+        double *xb = P.at<double>(P.L.xb_part), *corr = P.at<double>(P.L.corr_part);
+        e = ptc_spread(P.g, P.links, fold, src_f32, batch, k, n, half, P.st);
         if (e == hipSuccess)
-            e = forward(P, w, src, nullptr);
-        if (e == hipSuccess)
-            e = ptc_xb(P.g, sol, src, P.at<double>(P.L.partials), scal + 0, P.st);
-        if (e == hipSuccess)
-            e = ptc_diff(P.g, P.at<void>(P.L.a3), sol, P.at<void>(P.L.e), P.st);
+            e = ptc_error(P.g, fold + 64, src_f32, batch, k, n, half, sol_f64, P.at<void>(P.L.e), xb, P.st);
         // A e = m^2 e - D_eo D_oe e (FP32 links) with <e, A e>
+        const DslashShape shape = pick_shape(ctx, P.g, HISQ_FP32, HISQ_FP32, n);
         DslashParams prm{};
         prm.g = P.g;
-        prm.nrhs = 1;
+        prm.nrhs = n;
         prm.links = P.links;
         prm.out_parity = 1;
         prm.in = P.at<void>(P.L.e);
@@ -242,21 +237,21 @@ hisq_status hisq_ptc_train_step(hisq_context *ctx, const hisq_lattice *lat, doub
         prm.y = P.at<void>(P.L.e);
         prm.ad = -1.0;
         prm.ay = mass * mass;
-        prm.partials = P.at<double>(P.L.partials);
-        prm.dot_out = scal + 2;
-        prm.dot_stride = 1;
+        prm.partials = P.at<double>(P.L.dot_part);
+        prm.dot_out = nullptr;  // summed with the correlations
         if (e == hipSuccess) e = launch_dslash(prm, HISQ_FP32, HISQ_FP32, EPI_AXPY_DOT, shape, P.st);
+        // the output gradient of pair k is 2 A e_k / (B <x_k, b_k>): A e_k here, the factor in the sum
         if (e == hipSuccess)
-            e = ptc_energy_grad(P.g, P.at<void>(P.L.ae), scal + 2, scal + 0, 1.0 / batch, P.at<void>(P.L.g3),
-                                scal + 1, P.st);
+            e = ptc_correlate(P.g, P.links, src_f32, batch, k, P.at<void>(P.L.ae), n, corr, P.st);
         if (e == hipSuccess)
-            e = backward(P, w, grad, nullptr);
+            e = ptc_correlate_sum(P.g, n, corr, k == 0, K, xb, 1.0 / batch, prm.partials,
+                                  dslash_partial_blocks(P.g, shape), sum, P.st);
     }
     if (e == hipSuccess)
-        e = ptc_adam(static_cast<double2 *>(w_master), static_cast<float2 *>(w_f32), grad,
-                     static_cast<double2 *>(m), static_cast<double2 *>(v), step, lr, beta1, beta2, eps, P.st);
+        e = ptc_chain_adam(w0, K, static_cast<double2 *>(w_master), static_cast<float2 *>(w_f32),
+                           static_cast<double2 *>(m), static_cast<double2 *>(v), step, lr, beta1, beta2, eps, P.st);
     if (e == hipSuccess && loss) {
-        e = hipMemcpyAsync(loss, scal + 1, sizeof(double), hipMemcpyDeviceToHost, P.st);
+        e = hipMemcpyAsync(loss, sum, sizeof(double), hipMemcpyDeviceToHost, P.st);
         if (e == hipSuccess)
             e = hipStreamSynchronize(P.st);
     }

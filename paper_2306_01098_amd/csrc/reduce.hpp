@@ -99,23 +99,27 @@ template <int NV> __device__ __forceinline__ int wave_multi_index(int lane) {
     return idx;
 }
 
+// One exchange per instantiation: as a loop over n the 64-value form was not
+// unrolled and its values were kept in scratch memory.
+template <int N, int O, int NV, typename T> __device__ __forceinline__ void wave_sum_halve(T (&v)[NV]) {
+    if constexpr (N > 1) {
+        const bool upper = (threadIdx.x & O) != 0;
+#pragma unroll
+        for (int k = 0; k < N / 2; ++k) {
+            const T give = upper ? v[k] : v[k + N / 2];
+            const T keep = upper ? v[k + N / 2] : v[k];
+            v[k] = keep + __shfl_xor(give, O, 64);
+        }
+        wave_sum_halve<N / 2, O / 2>(v);
+    } else if constexpr (O > 0) {
+        v[0] += __shfl_xor(v[0], O, 64);
+        wave_sum_halve<1, O / 2>(v);
+    }
+}
+
 template <int NV, typename T> __device__ __forceinline__ void wave_sum_multi(T (&v)[NV]) {
     static_assert(NV >= 1 && NV <= 64 && (NV & (NV - 1)) == 0, "NV must be a power of two <= 64");
-    const int lane = threadIdx.x & 63;
-    int o = 32;
-#pragma unroll
-    for (int n = NV; n > 1; n >>= 1, o >>= 1) {
-        const bool upper = (lane & o) != 0;
-#pragma unroll
-        for (int k = 0; k < n / 2; ++k) {
-            const T give = upper ? v[k] : v[k + n / 2];
-            const T keep = upper ? v[k + n / 2] : v[k];
-            v[k] = keep + __shfl_xor(give, o, 64);
-        }
-    }
-#pragma unroll
-    for (; o > 0; o >>= 1)
-        v[0] += __shfl_xor(v[0], o, 64);
+    wave_sum_halve<NV, 32>(v);
 }
 
 // Sum of one slot by one wavefront: lane l adds partials l, l + 64, l + 128,

@@ -262,3 +262,73 @@ def test_trained_network_in_flexible_cg(gpu_lib):
         it_cg.append(info2[0]["iterations"])
     print(f"\nPTC loss {losses[0]:.3f} -> {losses[-1]:.3f}; held-out iterations FCG+PTC {it_fcg} vs CG {it_cg}; "
           f"ratio CG/FCG {np.mean(it_cg) / np.mean(it_fcg):.3f}")
+
+
+@pytest.mark.parametrize("dims,t_bc,batch", [((4, 4, 4, 4), 1, 1), ((6, 4, 10, 4), -1, 3), ((4, 6, 4, 14), -1, 5),
+                                             ((8, 8, 8, 4), 1, 9), ((16, 16, 16, 34), -1, 2)])
+def test_folded_network_on_edge_lattices(gpu_lib, dims, t_bc, batch):
+    """Forward, backward and a training step where the folded kernels have
+    edges: a last block of 128 sites that is partly empty, fewer blocks than
+    XCDs, chunks of four training pairs with a rest of one, two and three
+    columns, the columns in one thread (from 65536 sites per parity).  FP32
+    arithmetic against the FP64 oracle: the module's bound of 1e-5."""
+    h = gpu_lib
+    w = gen.workload_smooth(dims, 83, t_bc, 0.3, batch)
+    lat = h.lattice(dims, t_bc)
+    l32 = h.pack_links_from_host(lat, "fp32", w["fat"], w["naik"])
+    X32 = f32(w["fat"])
+    weights = [np.asarray(f32(x)) for x in ptc.init_weights(np.random.default_rng(6), scale=0.6)]
+    master, w32 = h.weights_to_device(weights)
+    ws = h.empty_workspace(h.hisq_ptc_workspace_bytes(lat))
+    big = gen.volume(dims) > 100000
+    srcs = f32(w["src"])
+    r, gout = srcs[0], f32(gen.gaussian_half_field(gen.rng_for(83, 30), dims)[0])
+    ref, acts = ptc.network_forward(dims, t_bc, X32, weights, r)
+    buf = h.pack_field_from_host(lat, "fp32", r)
+    h.hisq_ptc_forward(lat, l32, w32, buf, buf, ws)          # in place
+    assert rel(h.unpack_field_to_host(lat, "fp32", buf)[0], ref) <= 1e-5
+    gws, gin_ref = ptc.network_backward(dims, t_bc, X32, weights, acts, gout)
+    g = h.pack_field_from_host(lat, "fp32", gout)
+    grad = torch.zeros(2 * h.HISQ_PTC_NWEIGHTS, dtype=torch.float64, device="cuda")
+    h.hisq_ptc_backward(lat, l32, w32, g, g, grad, ws)       # in place
+    for a, b in zip(h.weights_from_device(grad), gws):
+        assert rel(a, b) <= 1e-5
+    assert rel(h.unpack_field_to_host(lat, "fp32", g)[0], gin_ref) <= 1e-5
+    if big:
+        return  # the training step's oracle is slow; its columns share the kernels of the smaller lattices
+    sols = gen.gaussian_half_field(gen.rng_for(83, 40), dims, batch)
+    m, v = torch.zeros_like(master), torch.zeros_like(master)
+    loss = h.hisq_ptc_train_step(lat, 0.2, l32, master, w32, m, v, 1, batch, h.pack_field_from_host(lat, "fp32", srcs),
+                                 h.pack_field_from_host(lat, "fp64", sols), ws, lr=1e-2)
+    lat_q = O.quantized_lattice(O.lattice_from(w), "fp32")
+    L_ref, g_ref = ptc.loss_and_grad(dims, t_bc, X32, weights, srcs, O.quantize_fp32(sols), lambda u: lat_q.M_e(0.2, u))
+    assert abs(loss - L_ref) <= 1e-5 * abs(L_ref)
+    for a, b in zip(h.weights_from_device(m), g_ref):
+        assert rel(10 * a, b) <= 1e-5
+
+
+def test_training_columns_in_one_thread(gpu_lib):
+    """From 65536 sites per parity the columns of a training chunk run one after
+    another in a thread: a step on three pairs equals the sum of the pairs'
+    own steps (the same FP32 values per column, FP64 sums: 1e-12)."""
+    h = gpu_lib
+    dims = (16, 16, 16, 32)
+    w = gen.workload_smooth(dims, 84, -1, 0.3, 3)
+    lat = h.lattice(dims, -1)
+    l32 = h.pack_links_from_host(lat, "fp32", w["fat"], w["naik"])
+    weights = [np.asarray(f32(x)) for x in ptc.init_weights(np.random.default_rng(7), scale=0.6)]
+    ws = h.empty_workspace(h.hisq_ptc_workspace_bytes(lat))
+    sols = gen.gaussian_half_field(gen.rng_for(84, 40), dims, 3)
+
+    def step(k):
+        master, w32 = h.weights_to_device(weights)
+        m, v = torch.zeros_like(master), torch.zeros_like(master)
+        loss = h.hisq_ptc_train_step(lat, 0.2, l32, master, w32, m, v, 1, len(k),
+                                     h.pack_field_from_host(lat, "fp32", w["src"][k]),
+                                     h.pack_field_from_host(lat, "fp64", sols[k]), ws)
+        return loss, m.cpu().numpy()
+
+    loss, m = step([0, 1, 2])
+    one = [step([k]) for k in range(3)]
+    assert abs(loss - sum(a[0] for a in one) / 3) <= 1e-12 * abs(loss)
+    assert np.linalg.norm(m - sum(a[1] for a in one) / 3) <= 1e-12 * np.linalg.norm(m)
