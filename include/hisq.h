@@ -342,8 +342,10 @@ hisq_status hisq_chiral_condensate(hisq_context *ctx, const hisq_lattice *lat, d
  * nshift (1..32) shifts at the cost of one operator application per iteration:
  * the Krylov space of the smallest shift is built and the other shifts follow
  * Jegerlehner's recurrences (zeta, alpha_k, beta_k in FP64); a shift is frozen
- * once |zeta_k| ||r|| <= tol[k] ||b||.  Afterwards every shift whose FP64 true
- * residual is above tol[k] is refined by (reliable-update) CG from x[k].
+ * once |zeta_k| ||r|| <= tol[k] ||b|| (with inner = HISQ_FP16N 1e-5 ||b||, other
+ * FP32 vectors 1e-7 ||b|| where tol[k] is smaller: the shared iterates get no
+ * closer in that precision).  Afterwards every shift whose FP64 true residual is
+ * above tol[k] is refined by (reliable-update) CG from x[k].
  *   shifts, tol  host arrays [nshift]; m^2 + shifts[k] > 0.
  *   x            host array of nshift distinct device pointers to packed
  *                HISQ_FP64 fields (overwritten; the initial guess is zero).

@@ -32,8 +32,7 @@ __device__ __forceinline__ double block_pq(const CgVecParams &prm, int rr, doubl
 }
 
 // x += alpha p (FP64 x), r -= alpha q with alpha = rho / <p, A p>, and the
-// block partials of <r, r> for right-hand side blockIdx.y; multi-shift:
-// x_k += alpha_k p_k.
+// block partials of <r, r> for right-hand side blockIdx.y.
 template <int FP>
 __global__ void __launch_bounds__(BLK) cg_xr_kernel(CgVecParams prm) {
     using T = typename Sloppy<FP>::T;
@@ -70,29 +69,6 @@ __global__ void __launch_bounds__(BLK) cg_xr_kernel(CgVecParams prm) {
         }
         FieldIO<HISQ_FP64>::template store<double>(prm.x[rr], prm.vh, 1, 0, i, x);
         FieldIO<FP>::template store<T>(prm.r, prm.vh, prm.nrhs, rr, i, r);
-        if (prm.nshift > 0) {
-            // shifted solutions: alpha_k = alpha zeta_new / zeta (Jegerlehner)
-            const MsGlobal ms = *prm.ms;
-            for (int k = 0; k < prm.nshift; ++k) {
-                const ShiftScalars sk = prm.sh[k];
-                if (!sk.active)
-                    continue;
-                const double den = alpha * ms.beta_old * (sk.zeta_old - sk.zeta) +
-                                   sk.zeta_old * ms.alpha_old * (1.0 + sk.s * alpha);
-                const double zn = sk.zeta * sk.zeta_old * ms.alpha_old / den;
-                const double ak = alpha * zn / sk.zeta;
-                cplx<T> pk[3];
-                cplx<double> xk[3];
-                FieldIO<FP>::template load<T>(prm.ps, prm.vh, 1, k, i, pk);
-                FieldIO<HISQ_FP64>::template load<double>(prm.xs[k], prm.vh, 1, 0, i, xk);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    xk[c].re = fma(ak, (double)pk[c].re, xk[c].re);
-                    xk[c].im = fma(ak, (double)pk[c].im, xk[c].im);
-                }
-                FieldIO<HISQ_FP64>::template store<double>(prm.xs[k], prm.vh, 1, 0, i, xk);
-            }
-        }
     }
     block_sum<1>(part, lds);
     if (threadIdx.x == 0)
@@ -103,19 +79,59 @@ __global__ void __launch_bounds__(BLK) cg_xr_kernel(CgVecParams prm) {
 // right-hand side) and the <p, A p> partials of the D_eo kernel (in the order
 // cg_xr_kernel summed them) and advances the scalars: breakdown check, rho, beta,
 // convergence / reliable-update / iteration-limit flags, and the multi-shift
-// zeta recurrences.
+// zeta recurrences, one shift a lane (as a loop of one thread, three FP64
+// divisions a shift, 13 shifts took 9 us more).  ms->stepped: whether this
+// launch advanced the shifts.
 __global__ void __launch_bounds__(1024) cg_finalize_kernel(CgVecParams prm, int nblk) {
-    if (*prm.skip)
+    if (*prm.skip) {
+        if (threadIdx.x == 0 && prm.nshift > 0)
+            prm.ms->stepped = 0;
         return;
+    }
     __shared__ double tot[HISQ_MAX_RHS];
     __shared__ double totpq[HISQ_MAX_RHS];
-    sum_partials_block(prm.partials, prm.nrhs, nblk, tot);
-    for (int j = threadIdx.x >> 6; j < prm.nrhs; j += blockDim.x >> 6) {
-        const double v = wave_sum_slot<false>(prm.pq_part + (size_t)j * prm.pq_nblk, prm.pq_nblk);
+    for (int k = threadIdx.x >> 6; k < 2 * prm.nrhs; k += blockDim.x >> 6) {  // one wavefront a sum
+        const int j = k >> 1;
+        const double v = k & 1 ? wave_sum_slot<false>(prm.pq_part + (size_t)j * prm.pq_nblk, prm.pq_nblk)
+                               : wave_sum_slot<true>(prm.partials + (size_t)j * nblk, nblk);
         if ((threadIdx.x & 63) == 0)
-            totpq[j] = v;
+            (k & 1 ? totpq : tot)[j] = v;
     }
     __syncthreads();
+    const bool step = prm.nshift > 0 && prm.st[0].active && finite_pos(totpq[0]);
+    if (prm.nshift > 0) {
+        // advance the shifted systems from the base system's alpha and beta
+        const double rho = prm.st[0].rho, a = rho / totpq[0], beta = tot[0] / rho;
+        const int k = threadIdx.x;
+        const MsGlobal ms = *prm.ms;
+        if (step && k < prm.nshift && prm.sh[k].active) {
+            ShiftScalars sk = prm.sh[k];
+            const double den = a * ms.beta_old * (sk.zeta_old - sk.zeta) +
+                               sk.zeta_old * ms.alpha_old * (1.0 + sk.s * a);
+            const double zn = sk.zeta * sk.zeta_old * ms.alpha_old / den;
+            sk.alpha = a * zn / sk.zeta;
+            sk.beta = beta * (zn / sk.zeta) * (zn / sk.zeta);
+            sk.zeta_old = sk.zeta;
+            sk.zeta = zn;
+            sk.zeta_new = zn;
+            sk.iters = prm.st[0].iters + 1;
+            if (!(zn == zn) || zn * zn * tot[0] <= sk.target2) {
+                sk.active = 0;  // converged (or underflowed): frozen
+                sk.flag = FLAG_CONV;
+            }
+            prm.sh[k] = sk;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            MsGlobal next = ms;
+            if (step) {
+                next.alpha_old = a;
+                next.beta_old = beta;
+            }
+            next.stepped = step ? 1 : 0;
+            *prm.ms = next;
+        }
+    }
     if (threadIdx.x != 0)
         return;
     int any = 0;
@@ -127,37 +143,9 @@ __global__ void __launch_bounds__(1024) cg_finalize_kernel(CgVecParams prm, int 
                 s.flag = FLAG_BREAKDOWN;
                 s.active = 0;
             } else {
-                const double a = s.rho / s.pq;
                 const double rho_new = tot[j];
                 s.iters += 1;
                 s.rho_new = rho_new;
-                if (j == 0 && prm.nshift > 0) {
-                    // advance the shifted systems before beta is formed
-                    const double beta = rho_new / s.rho;
-                    MsGlobal ms = *prm.ms;
-                    for (int k = 0; k < prm.nshift; ++k) {
-                        ShiftScalars sk = prm.sh[k];
-                        if (!sk.active)
-                            continue;
-                        const double den = a * ms.beta_old * (sk.zeta_old - sk.zeta) +
-                                           sk.zeta_old * ms.alpha_old * (1.0 + sk.s * a);
-                        const double zn = sk.zeta * sk.zeta_old * ms.alpha_old / den;
-                        sk.alpha = a * zn / sk.zeta;
-                        sk.beta = beta * (zn / sk.zeta) * (zn / sk.zeta);
-                        sk.zeta_old = sk.zeta;
-                        sk.zeta = zn;
-                        sk.zeta_new = zn;
-                        sk.iters = s.iters;
-                        if (!(zn == zn) || zn * zn * rho_new <= sk.target2) {
-                            sk.active = 0;  // converged (or underflowed): frozen
-                            sk.flag = FLAG_CONV;
-                        }
-                        prm.sh[k] = sk;
-                    }
-                    ms.alpha_old = a;
-                    ms.beta_old = beta;
-                    *prm.ms = ms;
-                }
                 if (!(rho_new == rho_new)) {
                     s.flag = FLAG_BREAKDOWN;
                     s.active = 0;
@@ -242,15 +230,43 @@ __global__ void __launch_bounds__(1024) cg_restart_kernel(CgVecParams prm, const
 }
 
 // p = r + beta p for right-hand side rhs0 + blockIdx.y (if active; in restart
-// mode only for a column just restarted by cg_restart_kernel);
-// multi-shift: p_k = zeta_k r + beta_k p_k.
+// mode only for a column just restarted by cg_restart_kernel).  Multi-shift
+// (one right-hand side): block rows 1 .. nshift take the shifts,
+// x_k += alpha_k p_k and p_k = zeta_k r + beta_k p_k, so that p_k is read once
+// and every shift has wavefronts of its own (a loop over the shifts in one
+// thread, x_k in cg_xr_kernel: 24^3x12, 13 shifts 36 us an iteration, see
+// cg_xr_kernel 23 and this kernel 13).  A shift frozen by this iteration still
+// takes its x_k; the base system may have stopped in it.
 template <int FP>
 __global__ void __launch_bounds__(BLK) cg_p_kernel(CgVecParams prm, int rhs0, int restart_only) {
     using T = typename Sloppy<FP>::T;
+    const int i = blockIdx.x * BLK + threadIdx.x;
+    if (prm.nshift > 0 && blockIdx.y > 0) {
+        const int k = blockIdx.y - 1;
+        const ShiftScalars sk = prm.sh[k];
+        if (!prm.ms->stepped || sk.iters != prm.st[0].iters || i >= prm.vh)
+            return;  // no step, or frozen earlier
+        cplx<T> pk[3], r[3];
+        cplx<double> xk[3];
+        FieldIO<FP>::template load<T>(prm.ps, prm.vh, 1, k, i, pk);
+        FieldIO<HISQ_FP64>::template load<double>(prm.xs[k], prm.vh, 1, 0, i, xk);
+        FieldIO<FP>::template load<T>(prm.r, prm.vh, 1, 0, i, r);
+        const T z = (T)sk.zeta, bk = (T)sk.beta;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            xk[c].re = fma(sk.alpha, (double)pk[c].re, xk[c].re);
+            xk[c].im = fma(sk.alpha, (double)pk[c].im, xk[c].im);
+            pk[c].re = fma(bk, pk[c].re, z * r[c].re);
+            pk[c].im = fma(bk, pk[c].im, z * r[c].im);
+        }
+        FieldIO<HISQ_FP64>::template store<double>(prm.xs[k], prm.vh, 1, 0, i, xk);
+        if (sk.active)
+            FieldIO<FP>::template store<T>(prm.ps, prm.vh, 1, k, i, pk);
+        return;
+    }
     if (*prm.skip)
         return;
     const int rr = rhs0 + blockIdx.y;
-    const int i = blockIdx.x * BLK + threadIdx.x;
     const CgScalars st = prm.st[rr];
     if (!(restart_only ? st.restart : st.active) || i >= prm.vh)
         return;
@@ -264,22 +280,6 @@ __global__ void __launch_bounds__(BLK) cg_p_kernel(CgVecParams prm, int rhs0, in
         p[c].im = fma(b, p[c].im, r[c].im);
     }
     FieldIO<FP>::template store<T>(prm.p, prm.vh, prm.nrhs, rr, i, p);
-    if (prm.nshift > 0 && rr == 0) {
-        for (int k = 0; k < prm.nshift; ++k) {
-            const ShiftScalars sk = prm.sh[k];
-            if (!sk.active)
-                continue;
-            cplx<T> pk[3];
-            FieldIO<FP>::template load<T>(prm.ps, prm.vh, 1, k, i, pk);
-            const T z = (T)sk.zeta, bk = (T)sk.beta;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                pk[c].re = fma(bk, pk[c].re, z * r[c].re);
-                pk[c].im = fma(bk, pk[c].im, z * r[c].im);
-            }
-            FieldIO<FP>::template store<T>(prm.ps, prm.vh, 1, k, i, pk);
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -816,10 +816,11 @@ hipError_t launch_cg_xr(const CgVecParams &p, int fp, hipStream_t st) {
 
 hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStream_t st, bool restart_only) {
     const int mode = restart_only ? 1 : 0;
+    const dim3 g = grid_for(p.vh, nrhs + p.nshift);
     if (fp == HISQ_FP64)
-        cg_p_kernel<HISQ_FP64><<<grid_for(p.vh, nrhs), BLK, 0, st>>>(p, rhs0, mode);
+        cg_p_kernel<HISQ_FP64><<<g, BLK, 0, st>>>(p, rhs0, mode);
     else
-        cg_p_kernel<HISQ_FP32><<<grid_for(p.vh, nrhs), BLK, 0, st>>>(p, rhs0, mode);
+        cg_p_kernel<HISQ_FP32><<<g, BLK, 0, st>>>(p, rhs0, mode);
     return hipGetLastError();
 }
 

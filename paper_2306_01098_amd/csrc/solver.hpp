@@ -70,7 +70,7 @@ struct alignas(16) ShiftScalars {
 struct MsGlobal {
     double alpha_old, beta_old;
     int nshift;
-    int pad;
+    int stepped;  // the last finalize advanced the shifts (cg_p_kernel follows it)
 };
 
 constexpr int MAX_SHIFTS = 32;

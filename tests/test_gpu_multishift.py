@@ -220,3 +220,26 @@ def test_multishift_zero_source(gpu_lib):
     assert st == h.OK
     for s in sols:
         assert np.all(s == 0)
+
+
+@pytest.mark.parametrize("inner,shifts", [("fp32", [0.3]), ("fp32", [0.02, 0.0]), ("fp32", [50.0, 0.0, 0.0, 1e-3]),
+                                          ("fp16n", [0.0, 1.0]), ("fp64", [5.0, 0.0, 1e-9])])
+def test_multishift_shift_rows_and_shared_phase_end(gpu_lib, inner, shifts):
+    """The shifts' vectors are rows of their own in the update launch: none,
+    one and several rows, a shift that freezes within a few iterations, two
+    equal to the base, on a lattice whose last block of 256 sites is partly
+    empty.  With FP32 vectors the shared phase ends where the iterates stall
+    (1e-7, FP16N links 1e-5 of ||b||): no later than the Krylov phase asked for
+    that tolerance; with FP64 it goes to tol.  Every shift meets its FP64 true
+    residual by the oracle."""
+    h = gpu_lib
+    w = gen.workload_haar((6, 4, 8, 10), 57, -1)
+    m, tol = 0.3, 1e-10
+    st, info, sols, (lat, l64, lin, b, xs, ws) = run(h, w, inner, shifts, m, tol)
+    assert st == h.OK, info
+    lat_o = O.lattice_from(w)
+    for k, s in enumerate(shifts):
+        assert O.true_residual(lat_o, m, w["src"][0], sols[k], shift=s) <= tol
+    end = {"fp32": 1e-7, "fp16n": 1e-5, "fp64": tol}[inner]
+    _, krylov = h.hisq_multishift_krylov(lat, m, l64, lin, inner, shifts, b, xs, end, 20000, ws)
+    assert [i["shared_iterations"] for i in info] == [i["shared_iterations"] for i in krylov]
