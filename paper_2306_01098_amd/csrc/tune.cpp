@@ -2,6 +2,7 @@
 // buffers with HIP events and keeps the fastest per (extents, precisions,
 // nrhs) in the context.
 #include <algorithm>
+#include <iterator>
 #include <vector>
 
 #include "api_util.hpp"
@@ -9,13 +10,57 @@
 
 namespace hisq {
 
-// Built-in shapes (measured on MI355X at 32^3x8 and 48^3x12): one thread per
-// site (four lanes per site on lattices too small to fill the chip); with
-// several right-hand sides one thread per site holding four of them (FP16N
-// links: two; FP32 links and fields: eight) in blocks of 256 (FP32 and FP16N
-// fields) or 128 (FP64 fields; eight FP32 rhs); FP32 fields of at least four
-// columns on lattices the LDS staging fits: the LDS-staged mapping, four rhs
-// per thread.
+// Launch time of a shape on a lattice of a few ten thousand sites per parity:
+// the latency of its chain of loads, which grows with the right-hand sides a
+// thread carries, and a time per 1000 sites and group of right-hand sides
+// (microseconds, fitted to 14 lattices from 4^4 to 48^3x12 at 1 to 16
+// right-hand sides; within 10 % of nearly all of them below 49152 sites).
+struct ShapeCost {
+    int variant, nin;
+    double fixed, per;
+};
+constexpr ShapeCost COST_FP64[] = {{VAR_DIR, 1, 3.5, 0.239}, {VAR_DIR, 2, 4.1, 0.34},  {VAR_SITE, 1, 4.8, 0.129},
+                                   {VAR_SITE, 2, 6.3, 0.184}, {VAR_SITE, 4, 9.7, 0.295}};
+constexpr ShapeCost COST_FP32[] = {{VAR_DIR, 1, 3.5, 0.148}, {VAR_DIR, 2, 3.8, 0.16},   {VAR_SITE, 1, 4.8, 0.06},
+                                   {VAR_SITE, 2, 6.2, 0.083}, {VAR_SITE, 4, 8.7, 0.141}, {VAR_LDS, 4, 8.2, 0.145}};
+constexpr ShapeCost COST_FP16[] = {{VAR_DIR, 1, 3.5, 0.074}, {VAR_SITE, 1, 4.4, 0.036}};
+
+// Several right-hand sides on a lattice that one thread per site and group of
+// right-hand sides spreads over too few wavefronts.
+DslashShape small_multi_shape(const Geom &g, int fp, int nrhs) {
+    const ShapeCost *c = fp == HISQ_FP64 ? COST_FP64 : fp == HISQ_FP32 ? COST_FP32 : COST_FP16;
+    const int n = fp == HISQ_FP64 ? (int)std::size(COST_FP64)
+                  : fp == HISQ_FP32 ? (int)std::size(COST_FP32) : (int)std::size(COST_FP16);
+    DslashShape best{};
+    double least = 1e30;
+    for (int k = 0; k < n; ++k) {
+        DslashShape s{c[k].variant, c[k].nin, 64, 1};
+        if (s.variant == VAR_LDS)
+            s = DslashShape{VAR_LDS, s.nin, LDS_BAND * g.hx, 2};
+        else if (fp == HISQ_FP16N && s.variant == VAR_SITE && g.vh >= 16384)
+            s.block = 256;
+        if (s.nin >= 2 * nrhs || (s.variant == VAR_LDS && (nrhs < 4 || !dslash_shape_fits(s, g, fp))))
+            continue;
+        if (fp == HISQ_FP64 && s.variant == VAR_SITE && s.nin == 1 && g.vh > 8192)
+            continue;  // 12288 and 16800 sites: 10-30 % slower than two a thread
+        if (s.variant == VAR_SITE && g.vh >= 32768 && g.nz % 8 == 0)
+            s.xcd_remap = 2;
+        const double t = c[k].fixed + c[k].per * 1e-3 * g.vh * ((nrhs + s.nin - 1) / s.nin);
+        if (t < least) {
+            least = t;
+            best = s;
+        }
+    }
+    return best;
+}
+
+// Built-in shapes (measured on MI355X): one thread per site (four lanes per
+// site on lattices too small to fill the chip); with several right-hand sides
+// and enough sites one thread per site holding four of them (FP16N fields: two;
+// FP32 links and fields: eight) in blocks of 256 (FP32 and FP16N fields) or 128
+// (FP64 fields; eight FP32 rhs); FP32 fields of at least four columns on
+// lattices the LDS staging fits: the LDS-staged mapping, four rhs per thread;
+// with several right-hand sides on small lattices: small_multi_shape.
 DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
     // measured on 32^3x8 at one right-hand side and 48^3x12 at 4 and 16:
     // the per-site mapping wins everywhere once the N_outer groups of a site
@@ -32,9 +77,10 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
         // blocks of 256: up to 16384 sites per parity (49152 for FP32 and
         // FP16N links) four lanes per site (8^4 .. 16^3x8: 9.6-16.1 -> 9.2-9.3
         // us FP64; 16^4 FP32 12.2 -> 9.4 us), below 131072 blocks of 64
-        // (24^3x6 FP64 19.4 -> 16.6 us)
+        // (24^3x6 FP64 19.4 -> 16.6 us).  FP64 at 20x12x14x10 (16800): 12.5 ->
+        // 9.0 us, FP64R12 9.6 -> 7.5; at 32768 the two tie.
         const bool wide = lp == HISQ_FP64 || lp == HISQ_FP64R12 || lp == HISQ_FP64W14;
-        if (g.vh <= (wide ? 16384 : 49152)) {
+        if (g.vh <= (wide ? 24576 : 49152)) {
             s.variant = VAR_DIR;
             // inside the CG graph blocks of 64 spread these lattices over more
             // CUs (8^4 FP64 CG 17.3 -> 15.6 ms; the isolated launch is the same)
@@ -57,6 +103,20 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
         }
         return s;
     }
+    // 5 and 16 rhs at 8^4: FP32 11.0 -> 4.6 and 18.4 -> 5.8 us, FP64 13.0 -> 5.8
+    // and 13.2 -> 6.7; 3 rhs at 20x12x14x10: FP32 9.0 -> 7.7, FP16N 11.2 ->
+    // 5.2.  From 49152 sites (FP64: 32768) the shapes below are as fast.  The
+    // smallest lattices that the LDS staging fits (16x8x8x8) keep it: the
+    // solver's test of the staged kernels runs there.
+    const bool staged = fp == HISQ_FP32 && nrhs >= 4 && g.vh <= 4096 &&
+                        dslash_shape_fits(DslashShape{VAR_LDS, 4, LDS_BAND * g.hx, 2}, g, fp);
+    if (!staged && g.vh < (fp == HISQ_FP64 ? 32768 : 49152))
+        return small_multi_shape(g, fp, nrhs);
+    // Five or six FP32 columns as one group of eight instead of two of four: the
+    // links are read once (24^3x12 36.9 -> 26.3 us, 24^4 82 -> 55, 48^3x12
+    // 250-265 -> 205; FP32R12 5 rhs at 32^3x8 45 -> 33, at 48^3x12 194 -> 189).
+    if (fp == HISQ_FP32 && (lp == HISQ_FP32 || lp == HISQ_FP32R12) && (nrhs == 5 || nrhs == 6) && g.vh >= 65536)
+        return DslashShape{VAR_SITE, 8, g.vh >= (1 << 22) ? 256 : 128, g.nz % 8 == 0 ? 2 : 1};  // 256: fewer partials
     // FP32 fields: the x- and y-hop vectors of four rhs per thread staged in
     // LDS where the lattice allows it (16 rhs at 48^3x12: FP32 links 461 ->
     // 421 us, FP32R12 413 -> 365 us; the 16-rhs CG with FP32 links 0.407 ->
@@ -66,8 +126,12 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
         if (dslash_shape_fits(l, g, fp))
             return l;
     }
-    const int cap = lp == HISQ_FP16N ? 2 : 4;
-    s.nin = nrhs >= cap ? cap : 2;
+    // FP16N fields below 262144 sites: one rhs a thread (24^3x12, 3 rhs 20.3 ->
+    // 13.8 us, 16 rhs 55.9 -> 52; at 48^3x12 two are faster, 413 against 472).
+    const int cap = fp == HISQ_FP16N && g.vh < 262144 ? 1 : lp == HISQ_FP16N ? 2 : 4;
+    // FP64 columns of three as one group of four: 24^3x12 57 -> 42 us, 48^3x12
+    // 400 -> 306 (two groups of two read the links twice).
+    s.nin = nrhs >= cap || (fp == HISQ_FP64 && nrhs == 3) ? cap : 2;
     // 16 rhs at 48^3x12, blocks of 64 -> 128: FP32 520 -> 476 us, FP32R12
     // 467 -> 431 us, FP64 995 -> 935 us, FP16N 466 -> 457 us; 128 -> 256 with
     // FP32 fields and FP32-family links: FP32 476-514 -> 473-483 us, FP32R12

@@ -570,3 +570,30 @@ def test_lds_staged_shape_is_refused_where_it_does_not_fit(gpu_lib):
             h.hisq_set_dslash_shape(h.lattice(dims, -1), "fp32", 4, (2, 4, 64, 2), ctx)
     with pytest.raises(h.HisqError):   # FP64, 8 rhs per block at N_x = 64: 172 KiB of staging
         h.hisq_set_dslash_shape(h.lattice((64, 8, 8, 4), -1), "fp64", 8, (2, 8, 64, 2), ctx)
+
+
+@pytest.mark.parametrize("dims,nrhs", [((4, 4, 4, 4), 2), ((4, 4, 4, 4), 16), ((6, 10, 8, 4), 3), ((6, 10, 8, 4), 13),
+                                       ((10, 12, 12, 10), 5), ((10, 12, 12, 10), 8), ((20, 12, 14, 10), 3),
+                                       ((16, 16, 16, 16), 2), ((16, 8, 8, 16), 6), ((24, 16, 24, 16), 3),
+                                       ((24, 16, 24, 16), 6)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16n", "fp32r12"])
+def test_built_in_multi_rhs_shapes(gpu_lib, prec, dims, nrhs):
+    """The built-in shapes of several right-hand sides at the sizes where the
+    rule changes: four lanes per site with one and two columns a lane (odd
+    columns too), one, two, four and eight columns a thread, the LDS staging,
+    last blocks that are partly empty.  First, last and middle column against
+    the oracle on the rounded inputs: 1e-13 (FP64), 1e-6 (FP32), and for FP16N
+    the 2^-11 of a component's storage, of the whole vector."""
+    h = gpu_lib
+    w = gen.workload_haar(dims, 58, -1, nrhs)
+    lat = h.lattice(dims, -1)
+    f = "fp16n" if prec == "fp16n" else prec[:4]
+    links = h.pack_links_from_host(lat, prec, w["fat"], w["naik"])
+    inp = h.pack_field_from_host(lat, f, w["src"])
+    out = h.empty_field(lat, f, nrhs)
+    h.hisq_dslash(lat, prec, 1, links, inp, out, nrhs)
+    got = h.unpack_field_to_host(lat, f, out, nrhs)
+    lat_q = O.quantized_lattice(O.lattice_from(w), prec)
+    for r in sorted({0, nrhs // 2, nrhs - 1}):
+        ref = lat_q.D_oe(w["src"][r] if f == "fp64" else O.quantize_field(w["src"][r], f))
+        assert relerr(got[r], ref) <= {"fp64": 1e-13, "fp32": 1e-6, "fp16n": 2.0 ** -11}[f], (r, prec)
