@@ -21,7 +21,7 @@
 // writes and reads the eight half-lattice vectors (101 MB each) and takes 117
 // us (spread 91, 4.6 TB/s, gather 26, 5.3 TB/s); layer by layer it took 753 us,
 // 460 of them FP32 arithmetic of the 8 -> 8 layer.  The backward pass with
-// input gradient took 2.2 ms; training on four pairs at 16^4 1656 -> 152 us,
+// input gradient took 2.2 ms; training on four pairs at 16^4 1656 -> 135 us,
 // small lattices bound by the launches.
 #include <algorithm>
 #include <cmath>
@@ -113,6 +113,8 @@ __device__ __forceinline__ double2 w3_(const float2 *w, int d, int p) { return w
 
 // The folded map: fold[8 p' + p] = C[p'][p] and fold[64] = c0; the adjoint
 // network in the same form, C'[p'][p] = conj(C[p ^ 1][p' ^ 1]), at fold + 65.
+// c0 and its conjugate also as doubles at fold + 130 and + 132: the rounding of
+// c0 to FP32 would be the same relative error on every site.
 // Eight lanes (the channel d) per entry.  keep (nullable): a copy of the
 // weights.
 __global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, float2 *fold, float2 *keep,
@@ -152,6 +154,12 @@ __global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, float2
     const float2 r = make_float2((float)sum.x, (float)sum.y), rc = make_float2((float)sum.x, (float)-sum.y);
     fold[e] = r;
     fold[65 + (e < 64 ? 8 * ((e & 7) ^ 1) + ((e >> 3) ^ 1) : 64)] = rc;
+    if (e == 64) {
+        double *c0 = reinterpret_cast<double *>(fold + 130);
+        c0[0] = c0[2] = sum.x;
+        c0[1] = sum.y;
+        c0[3] = -sum.y;
+    }
 }
 
 // Two wavefronts work on 64 odd sites, one with the hops in x and y and one
@@ -261,13 +269,13 @@ __global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, c
     }
 }
 
-// c0 in + sum_p s_p of one element
-__device__ __forceinline__ float2 gathered(float2 c0, float2 in, const float2 *s, size_t stride) {
+// c0 in + sum_p s_p of one element (FP64: the kernels wait for memory)
+__device__ __forceinline__ double2 gathered(const double *c0, float2 in, const float2 *s, size_t stride) {
     float2 v[NHOP];
 #pragma unroll
     for (int p = 0; p < NHOP; ++p)
         v[p] = s[p * stride];
-    float2 r = make_float2(fmaf(c0.x, in.x, -c0.y * in.y), fmaf(c0.x, in.y, c0.y * in.x));
+    double2 r = dmul(make_double2(c0[0], c0[1]), wide(in));
 #pragma unroll
     for (int p = 0; p < NHOP; ++p) {
         r.x += v[p].x;
@@ -279,7 +287,7 @@ __device__ __forceinline__ float2 gathered(float2 c0, float2 in, const float2 *s
 // Second half: out = c0 in + sum_p' s_p' on the even sites, one thread per
 // element of the one-column fields (in may be out).  keep (nullable): a copy
 // of the input.
-__global__ void __launch_bounds__(PB) gather_kernel(int n, const float2 *c0, const float2 *in, const float2 *s,
+__global__ void __launch_bounds__(PB) gather_kernel(int n, const double *c0, const float2 *in, const float2 *s,
                                                     float2 *out, float2 *keep, const int *skip) {
     if (skip && *skip)
         return;
@@ -287,16 +295,16 @@ __global__ void __launch_bounds__(PB) gather_kernel(int n, const float2 *c0, con
     if (j >= n)
         return;
     const float2 v = in[j];
-    const float2 r = gathered(*c0, v, s + j, n);
+    const double2 r = gathered(c0, v, s + j, n);
     if (keep)
         keep[j] = v;
-    out[j] = r;
+    out[j] = make_float2((float)r.x, (float)r.y);
 }
 
 // Second half in training, for column blockIdx.y of a chunk: e = N(b) - x
 // (column blockIdx.y of an ne-column field) and the block partials of
 // Re <x, b>, b column col0 + blockIdx.y of the ncol-column sources, x FP64.
-__global__ void __launch_bounds__(PB) error_kernel(int vh, const float2 *c0, const void *b32, int ncol, int col0,
+__global__ void __launch_bounds__(PB) error_kernel(int vh, const double *c0, const void *b32, int ncol, int col0,
                                                    const float2 *s, const void *x64, void *e, int ne,
                                                    double *partials) {
     __shared__ double lds[PB / 64];
@@ -309,10 +317,10 @@ __global__ void __launch_bounds__(PB) error_kernel(int vh, const float2 *c0, con
         FieldIO<HISQ_FP64>::template load<double>(x64, vh, ncol, col0 + k, i, x);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const float2 y = gathered(*c0, make_float2(b[a].re, b[a].im),
+            const double2 y = gathered(c0, make_float2(b[a].re, b[a].im),
                                       s + (size_t)k * 24 * vh + (size_t)a * vh + i, (size_t)3 * vh);
-            d[a].re = (float)((double)y.x - x[a].re);
-            d[a].im = (float)((double)y.y - x[a].im);
+            d[a].re = (float)(y.x - x[a].re);
+            d[a].im = (float)(y.y - x[a].im);
             part[0] += x[a].re * (double)b[a].re + x[a].im * (double)b[a].im;
         }
         FieldIO<HISQ_FP32>::template store<float>(e, vh, ne, k, i, d);
@@ -612,7 +620,7 @@ hipError_t ptc_spread(const Geom &g, const char *links, const float2 *fold, cons
     return hipGetLastError();
 }
 
-hipError_t ptc_gather(const Geom &g, const float2 *c0, const void *in, const float2 *s, void *out, void *keep,
+hipError_t ptc_gather(const Geom &g, const double *c0, const void *in, const float2 *s, void *out, void *keep,
                       hipStream_t st, const int *skip) {
     const int n = 3 * g.vh;
     gather_kernel<<<nb(n), PB, 0, st>>>(n, c0, static_cast<const float2 *>(in), s, static_cast<float2 *>(out),
@@ -620,7 +628,7 @@ hipError_t ptc_gather(const Geom &g, const float2 *c0, const void *in, const flo
     return hipGetLastError();
 }
 
-hipError_t ptc_error(const Geom &g, const float2 *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
+hipError_t ptc_error(const Geom &g, const double *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
                      const void *x64, void *e, double *partials, hipStream_t st) {
     error_kernel<<<dim3(nb(g.vh), (unsigned)ncols), PB, 0, st>>>(g.vh, c0, b32, ncol, col0, s, x64, e, ncols, partials);
     return hipGetLastError();

@@ -66,6 +66,8 @@ struct Ptc {
     template <typename T> T *at(size_t o) const { return reinterpret_cast<T *>(ws + o); }
 };
 
+const double *c0_of(const float2 *fold) { return reinterpret_cast<const double *>(fold + PTC_C0); }
+
 // out_even = N(in_even); skip (nullable): every launch does nothing while
 // *skip != 0.  keep: leave the input and the weights for the backward pass.
 hipError_t forward(const Ptc &P, const float2 *w, const void *in_even, void *out_even, bool keep,
@@ -75,7 +77,7 @@ hipError_t forward(const Ptc &P, const float2 *w, const void *in_even, void *out
     if (e == hipSuccess)
         e = ptc_spread(P.g, P.links, fold, in_even, 1, 0, 1, P.at<float2>(P.L.s), P.st, skip);
     if (e == hipSuccess)
-        e = ptc_gather(P.g, fold + 64, in_even, P.at<float2>(P.L.s), out_even, keep ? P.at<void>(P.L.a0) : nullptr,
+        e = ptc_gather(P.g, c0_of(fold), in_even, P.at<float2>(P.L.s), out_even, keep ? P.at<void>(P.L.a0) : nullptr,
                        P.st, skip);
     return e;
 }
@@ -95,7 +97,7 @@ hipError_t backward(const Ptc &P, const float2 *w, const void *g_out, double2 *g
         if (e == hipSuccess)
             e = ptc_spread(P.g, P.links, fold + 65, g_out, 1, 0, 1, s, P.st);
         if (e == hipSuccess)
-            e = ptc_gather(P.g, fold + 65 + 64, g_out, s, g_in, nullptr, P.st);
+            e = ptc_gather(P.g, c0_of(fold) + 2, g_out, s, g_in, nullptr, P.st);
     }
     return e;
 }
@@ -220,7 +222,7 @@ hisq_status hisq_ptc_train_step(hisq_context *ctx, const hisq_lattice *lat, doub
         double *xb = P.at<double>(P.L.xb_part), *corr = P.at<double>(P.L.corr_part);
         e = ptc_spread(P.g, P.links, fold, src_f32, batch, k, n, half, P.st);
         if (e == hipSuccess)
-            e = ptc_error(P.g, fold + 64, src_f32, batch, k, n, half, sol_f64, P.at<void>(P.L.e), xb, P.st);
+            e = ptc_error(P.g, c0_of(fold), src_f32, batch, k, n, half, sol_f64, P.at<void>(P.L.e), xb, P.st);
         // A e = m^2 e - D_eo D_oe e (FP32 links) with <e, A e>
         const DslashShape shape = pick_shape(ctx, P.g, HISQ_FP32, HISQ_FP32, n);
         DslashParams prm{};
