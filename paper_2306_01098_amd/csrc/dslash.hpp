@@ -534,10 +534,8 @@ __global__ void __launch_bounds__(256) dslash_dir_kernel(const DslashParams prm)
     for (int r = 0; r < NIN; ++r)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            acc[r][a].re += __shfl_xor(acc[r][a].re, 1, 64);
-            acc[r][a].im += __shfl_xor(acc[r][a].im, 1, 64);
-            acc[r][a].re += __shfl_xor(acc[r][a].re, 2, 64);
-            acc[r][a].im += __shfl_xor(acc[r][a].im, 2, 64);
+            acc[r][a].re = lane_xor_add<2>(lane_xor_add<1>(acc[r][a].re));
+            acc[r][a].im = lane_xor_add<2>(lane_xor_add<1>(acc[r][a].im));
         }
 #pragma unroll
     for (int r = 0; r < NIN; ++r) {
@@ -633,14 +631,9 @@ __global__ void __launch_bounds__(256) dslash_hop_kernel(const DslashParams prm)
         for (int r = 0; r < NIN; ++r)
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                A re = eta * acc[r][a].re, im = eta * acc[r][a].im;
-#pragma unroll
-                for (int o = 1; o < 16; o <<= 1) {
-                    re += __shfl_xor(re, o, 64);
-                    im += __shfl_xor(im, o, 64);
-                }
-                acc[r][a].re = re;
-                acc[r][a].im = im;
+                const A re = eta * acc[r][a].re, im = eta * acc[r][a].im;
+                acc[r][a].re = lane_xor_add<8>(lane_xor_add<4>(lane_xor_add<2>(lane_xor_add<1>(re))));
+                acc[r][a].im = lane_xor_add<8>(lane_xor_add<4>(lane_xor_add<2>(lane_xor_add<1>(im))));
             }
 #pragma unroll
         for (int r = 0; r < NIN; ++r) {

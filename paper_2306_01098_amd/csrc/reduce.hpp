@@ -1,4 +1,4 @@
-// Deterministic grid reductions: wave64 shuffles -> LDS -> one partial per
+// Deterministic grid reductions: wave64 butterflies (lane_xor_add) -> LDS -> one partial per
 // block, stored by the reducing kernel; a one-block finalize kernel launched
 // after it sums the partials in block order.  (A "last block finishes"
 // scheme needs an agent-scope release per block, which on the multi-XCD
@@ -61,9 +61,7 @@ __device__ __forceinline__ void block_sum_pair(double (&v)[NV], double *lds) {
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             v[k] += lds[(g * 64 + lane) * NV + k];
-#pragma unroll
-            for (int o = 32; o >= 2; o >>= 1)
-                v[k] += __shfl_xor(v[k], o, 64);
+            v[k] = lane_xor_add<2>(lane_xor_add<4>(lane_xor_add<8>(lane_xor_add<16>(lane_xor_add<32>(v[k])))));
         }
     }
     __syncthreads();
