@@ -349,7 +349,10 @@ hisq_status hisq_chiral_condensate(hisq_context *ctx, const hisq_lattice *lat, d
  *   shifts, tol  host arrays [nshift]; m^2 + shifts[k] > 0.
  *   x            host array of nshift distinct device pointers to packed
  *                HISQ_FP64 fields (overwritten; the initial guess is zero).
- *   ws           workspace of hisq_cg_workspace_bytes(lat, inner, 1, nshift).
+ *   ws           workspace of hisq_cg_workspace_bytes(lat, inner, 1, nshift);
+ *                with up to three packed FP64 fields of min(nshift, 16)
+ *                columns less, the refinement's true residuals are formed
+ *                shift by shift.
  *   info         host array [nshift]; iterations = shared Krylov iterations up
  *                to the freeze (shared_iterations) + refinement iterations
  *                (refine_iterations).

@@ -656,9 +656,9 @@ __global__ void __launch_bounds__(BLK) cgcg_fused_kernel(CgVecParams prm, const 
 
 // r_j = b_j - ax_j for the ncol columns j of the launch (block row
 // blockIdx.y; VecPos) whose tr_skip[j] is 0 (all columns when tr_skip is
-// NULL): FP64 inputs b, ax (packed fields of ncol columns), r stored in the
-// sloppy precision as column col0 + j of the nf-column field r, block
-// partials of ||b_j - ax_j||^2 (FP64 values) in partials[j * gridDim.x +
+// NULL): FP64 inputs b, ax (packed fields of ncol columns; b_cols 0: b is one
+// column that all take), r stored in the sloppy precision as column col0 + j
+// of the nf-column field r, block partials of ||b_j - ax_j||^2 (FP64 values) in partials[j * gridDim.x +
 // block] and, when s and p are not NULL, of Re <r_j, s_j> (the stored r) and
 // Re <p_j, s_j> in spart and ppart (same layout; s and p are nf-column fields
 // like r).  A launch that forms residuals reopens the iteration launches
@@ -666,9 +666,9 @@ __global__ void __launch_bounds__(BLK) cgcg_fused_kernel(CgVecParams prm, const 
 // column it forms.  PAIR needs col0 even.
 template <int FP, bool PAIR>
 __global__ void __launch_bounds__(PAIR ? 2 * BLK : BLK)
-    residual_cols_kernel(int vh, int ncol, int nf, int col0, const void *b, const void *ax, void *r, double *partials,
-                         const int *tr_skip, const void *s, const void *p, double *spart, double *ppart, int *skip,
-                         int *col_off) {
+    residual_cols_kernel(int vh, int ncol, int nf, int col0, const void *b, int b_cols, const void *ax, void *r,
+                         double *partials, const int *tr_skip, const void *s, const void *p, double *spart,
+                         double *ppart, int *skip, int *col_off) {
     using T = typename Sloppy<FP>::T;
     const VecPos<PAIR> at;
     const int j = at.j;
@@ -687,7 +687,7 @@ __global__ void __launch_bounds__(PAIR ? 2 * BLK : BLK)
     const bool sp = s && p;
     if (run && i < vh) {
         cplx<double> bv[3], av[3];
-        FieldIO<HISQ_FP64>::template load<double>(b, vh, ncol, j, i, bv);
+        FieldIO<HISQ_FP64>::template load<double>(b, vh, ncol, b_cols * j, i, bv);
         FieldIO<HISQ_FP64>::template load<double>(ax, vh, ncol, j, i, av);
         cplx<T> rv[3], sv[3], pv[3];
         if (sp) {
@@ -880,20 +880,20 @@ hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_residual_cols(int vh, int ncol, int nf, int col0, int fp, const void *b, const void *ax, void *r,
-                                double *partials, const int *tr_skip, const void *s, const void *p, double *spart,
-                                double *ppart, int *skip, int *col_off, hipStream_t st) {
+hipError_t launch_residual_cols(int vh, int ncol, int nf, int col0, int fp, const void *b, int b_cols, const void *ax,
+                                void *r, double *partials, const int *tr_skip, const void *s, const void *p,
+                                double *spart, double *ppart, int *skip, int *col_off, hipStream_t st) {
     const int bs = cg_vec_block(vh);
     const unsigned nb = (unsigned)cg_vec_blocks(vh);
     if (fp == HISQ_FP64)
         residual_cols_kernel<HISQ_FP64, false><<<dim3(nb, (unsigned)ncol), bs, 0, st>>>(
-            vh, ncol, nf, col0, b, ax, r, partials, tr_skip, s, p, spart, ppart, skip, col_off);
+            vh, ncol, nf, col0, b, b_cols, ax, r, partials, tr_skip, s, p, spart, ppart, skip, col_off);
     else if (ncol >= 2 && col0 % 2 == 0)  // column pairs share 16-byte records
         residual_cols_kernel<HISQ_FP32, true><<<dim3(nb, (unsigned)(ncol + 1) / 2), 2 * bs, 0, st>>>(
-            vh, ncol, nf, col0, b, ax, r, partials, tr_skip, s, p, spart, ppart, skip, col_off);
+            vh, ncol, nf, col0, b, b_cols, ax, r, partials, tr_skip, s, p, spart, ppart, skip, col_off);
     else
         residual_cols_kernel<HISQ_FP32, false><<<dim3(nb, (unsigned)ncol), bs, 0, st>>>(
-            vh, ncol, nf, col0, b, ax, r, partials, tr_skip, s, p, spart, ppart, skip, col_off);
+            vh, ncol, nf, col0, b, b_cols, ax, r, partials, tr_skip, s, p, spart, ppart, skip, col_off);
     return hipGetLastError();
 }
 

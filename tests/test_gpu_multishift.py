@@ -243,3 +243,35 @@ def test_multishift_shift_rows_and_shared_phase_end(gpu_lib, inner, shifts):
     end = {"fp32": 1e-7, "fp16n": 1e-5, "fp64": tol}[inner]
     _, krylov = h.hisq_multishift_krylov(lat, m, l64, lin, inner, shifts, b, xs, end, 20000, ws)
     assert [i["shared_iterations"] for i in info] == [i["shared_iterations"] for i in krylov]
+
+
+@pytest.mark.parametrize("nshift", [2, 5, 17])
+def test_multishift_refinement_columns_packed_or_not(gpu_lib, nshift):
+    """With the workspace that the query returns the refinement packs the x_k
+    (17 shifts: a group of 16 and one of one); with less, down to what a call
+    needs, it works on them where they are, also where they are one packed
+    field themselves.  Each shift meets its FP64 true residual every way, and
+    two solutions of residual tol differ by no more than 2 tol ||b|| / m^2
+    (lambda_min(M_e) >= m^2).  One byte less than needed is refused."""
+    h = gpu_lib
+    w = gen.workload_haar((6, 4, 8, 10), 58, -1)
+    m, tol = 0.3, 1e-10
+    shifts = [0.02 * k * k for k in range(nshift)]
+    st, info, sols, (lat, l64, lin, b, xs, ws) = run(h, w, "fp32", shifts, m, tol)
+    assert st == h.OK, info
+    n = min(nshift, 16)
+    col = h.hisq_field_bytes(lat, "fp64", 1)
+    least = h.hisq_cg_workspace_bytes(lat, "fp32", 1, nshift) - 3 * (-(-col * n // 256) * 256)
+    lat_o = O.lattice_from(w)
+    bound = 2 * tol * np.linalg.norm(w["src"][0]) / m ** 2
+    whole = h.empty_field(lat, "fp64", nshift).view(torch.uint8).reshape(-1)
+    packed = [whole[k * col:(k + 1) * col] for k in range(nshift)]
+    for x2, size in ((xs, least), (packed, least), (packed, ws.numel())):
+        st2, info2 = h.hisq_multishift_cg(lat, m, l64, lin, "fp32", shifts, b, x2, tol, 20000, ws[:size])
+        assert st2 == h.OK, info2
+        for k, s in enumerate(shifts):
+            got = h.unpack_field_to_host(lat, "fp64", x2[k])[0]
+            assert O.true_residual(lat_o, m, w["src"][0], got, shift=s) <= tol
+            assert np.linalg.norm(got - sols[k]) <= bound
+    with pytest.raises(h.HisqError):
+        h.hisq_multishift_cg(lat, m, l64, lin, "fp32", shifts, b, xs, tol, 20000, ws[:least - 1])
