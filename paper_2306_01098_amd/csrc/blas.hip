@@ -307,7 +307,8 @@ __global__ void __launch_bounds__(BLK) cg_p_kernel(CgVecParams prm, int rhs0, in
 // first: done, the iteration limit, or a residual replacement (the reliable
 // update of Clark et al.), after which the same step continues from the
 // replaced r with beta = ||r||^2 / rho, as the two-reduction solver does.
-// Sets s.go (0: no update; 1: update; 2: update with fresh directions).
+// Sets s.go (0: no update; 1: update; 2: update with fresh directions); alpha
+// is that of the last update where no new one follows.
 // *wait: 1 when the column starts waiting for its true residual, 0 when it
 // stopped waiting, unchanged otherwise.
 __device__ __forceinline__ void cgcg_decide(CgScalars &s, const double (&tot)[4], bool decide, int *wait) {
@@ -423,10 +424,17 @@ __device__ __forceinline__ void cgcg_sums(const CgVecParams &prm, int j, size_t 
 // the column's partials and its scalar step.  after_check != 0: the check
 // block ran just before this iteration, so a waiting column (tr_skip == 0) is
 // decided here.
+// x takes alpha p of two updates in the second of them (the update kernel has
+// the older p at hand), so x is moved every second iteration only; a column
+// that stops with one outstanding has it added at once (go = 3), before the
+// check block or the host reads x.
 __global__ void __launch_bounds__(256) cgcg_finalize_kernel(CgVecParams prm, int after_check) {
-    if (*prm.skip)
-        return;
     const int j = blockIdx.x;
+    if (*prm.skip) {
+        if (threadIdx.x == 0 && prm.st[j].go)
+            prm.st[j].go = 0;  // a go = 3 was carried out by the last update
+        return;
+    }
     __shared__ double lds[4];
     double tot[4];
     cgcg_sums<true>(prm, j, 0, tot, lds);
@@ -434,7 +442,15 @@ __global__ void __launch_bounds__(256) cgcg_finalize_kernel(CgVecParams prm, int
         return;
     CgScalars s = prm.st[j];
     int wait = -1;
+    const double alpha_old = s.alpha;
     cgcg_decide(s, tot, after_check && prm.tr_skip[j] == 0, &wait);
+    if (s.go) {
+        s.spare = alpha_old;
+        s.xstep = s.xstep == X_LATER ? X_BOTH : X_LATER;
+    } else if (s.xstep == X_LATER) {
+        s.go = 3;
+        s.xstep = 0;
+    }
     if (wait >= 0)
         prm.tr_skip[j] = wait ? 0 : 1;
     prm.st[j] = s;
@@ -480,7 +496,12 @@ constexpr int vec_lds(int nv, bool pair) { return pair ? (2 * BLK / 128) * 64 * 
 // fresh directions p = r, s = w):
 //   p = r + beta p, s = w + beta s, x += alpha p (FP64 x), r -= alpha s,
 // with the block partials of <r, r>, Re <r, s> and Re <p, s> of the new
-// vectors (their stored values).
+// vectors (their stored values).  Every second update leaves x alone and the
+// next adds both terms, one after the other as two updates would (the same
+// values); go = 3 adds an outstanding term alone.  The kernel is bound by the
+// bytes that it moves (7.2 TB/s), of which x in FP64 was 96 of 264 a site with
+// FP32 vectors: 32^3x8, 16 columns, 77 -> 64 us on average (the solve 58.4 ->
+// 54.6 ms).
 // Block (0, 0) also sets the launch flags of the following kernels: skip while
 // no column is active (a column waiting for its true residual idles until the
 // check block, whose residual kernel clears skip again so that the next
@@ -510,49 +531,66 @@ __global__ void __launch_bounds__(PAIR ? 2 * BLK : BLK) cgcg_update_kernel(CgVec
     __shared__ double lds[vec_lds(3, PAIR)];
     const int i = at.i;
     double part[3] = {0.0, 0.0, 0.0};
+    const bool step = st.go == 1 || st.go == 2;
     if (st.go && i < prm.vh) {
         cplx<T> r[3], w[3], p[3], sv[3];
         cplx<double> x[3];
-        FieldIO<FP>::template load<T>(prm.r, prm.vh, prm.nrhs, j, i, r);
-        FieldIO<FP>::template load<T>(prm.w, prm.vh, prm.nrhs, j, i, w);
-        FieldIO<HISQ_FP64>::template load<double>(prm.x[j], prm.vh, 1, 0, i, x);
         const bool fresh = st.go == 2;
-        if (!fresh) {
+        const bool with_x = st.go == 3 || st.xstep == X_BOTH;
+        if (step) {
+            FieldIO<FP>::template load<T>(prm.r, prm.vh, prm.nrhs, j, i, r);
+            FieldIO<FP>::template load<T>(prm.w, prm.vh, prm.nrhs, j, i, w);
+        }
+        if (with_x)
+            FieldIO<HISQ_FP64>::template load<double>(prm.x[j], prm.vh, 1, 0, i, x);
+        if (!fresh)
             FieldIO<FP>::template load<T>(prm.p, prm.vh, prm.nrhs, j, i, p);
+        if (st.go == 1)
             FieldIO<FP>::template load<T>(prm.s, prm.vh, prm.nrhs, j, i, sv);
-        }
-        const T b = (T)st.beta, a = (T)st.alpha;
-        const double ad = st.alpha;
+        if (with_x) {
+            const double ao = step ? st.spare : st.alpha;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if (fresh) {
-                p[c] = r[c];
-                sv[c] = w[c];
-            } else {
-                p[c].re = fma(b, p[c].re, r[c].re);
-                p[c].im = fma(b, p[c].im, r[c].im);
-                sv[c].re = fma(b, sv[c].re, w[c].re);
-                sv[c].im = fma(b, sv[c].im, w[c].im);
+            for (int c = 0; c < 3; ++c) {
+                x[c].re = fma(ao, (double)p[c].re, x[c].re);
+                x[c].im = fma(ao, (double)p[c].im, x[c].im);
             }
-            x[c].re = fma(ad, (double)p[c].re, x[c].re);
-            x[c].im = fma(ad, (double)p[c].im, x[c].im);
-            r[c].re = fma(-a, sv[c].re, r[c].re);
-            r[c].im = fma(-a, sv[c].im, r[c].im);
-            const double rre = r[c].re, rim = r[c].im, sre = sv[c].re, sim = sv[c].im;
-            part[0] = fma(rre, rre, part[0]);
-            part[0] = fma(rim, rim, part[0]);
-            part[1] = fma(rre, sre, part[1]);
-            part[1] = fma(rim, sim, part[1]);
-            part[2] = fma((double)p[c].re, sre, part[2]);
-            part[2] = fma((double)p[c].im, sim, part[2]);
         }
-        FieldIO<FP>::template store<T>(prm.p, prm.vh, prm.nrhs, j, i, p);
-        FieldIO<FP>::template store<T>(prm.s, prm.vh, prm.nrhs, j, i, sv);
-        FieldIO<HISQ_FP64>::template store<double>(prm.x[j], prm.vh, 1, 0, i, x);
-        FieldIO<FP>::template store<T>(prm.r, prm.vh, prm.nrhs, j, i, r);
+        if (step) {
+            const T b = (T)st.beta, a = (T)st.alpha;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if (fresh) {
+                    p[c] = r[c];
+                    sv[c] = w[c];
+                } else {
+                    p[c].re = fma(b, p[c].re, r[c].re);
+                    p[c].im = fma(b, p[c].im, r[c].im);
+                    sv[c].re = fma(b, sv[c].re, w[c].re);
+                    sv[c].im = fma(b, sv[c].im, w[c].im);
+                }
+                if (with_x) {
+                    x[c].re = fma(st.alpha, (double)p[c].re, x[c].re);
+                    x[c].im = fma(st.alpha, (double)p[c].im, x[c].im);
+                }
+                r[c].re = fma(-a, sv[c].re, r[c].re);
+                r[c].im = fma(-a, sv[c].im, r[c].im);
+                const double rre = r[c].re, rim = r[c].im, sre = sv[c].re, sim = sv[c].im;
+                part[0] = fma(rre, rre, part[0]);
+                part[0] = fma(rim, rim, part[0]);
+                part[1] = fma(rre, sre, part[1]);
+                part[1] = fma(rim, sim, part[1]);
+                part[2] = fma((double)p[c].re, sre, part[2]);
+                part[2] = fma((double)p[c].im, sim, part[2]);
+            }
+            FieldIO<FP>::template store<T>(prm.p, prm.vh, prm.nrhs, j, i, p);
+            FieldIO<FP>::template store<T>(prm.s, prm.vh, prm.nrhs, j, i, sv);
+            FieldIO<FP>::template store<T>(prm.r, prm.vh, prm.nrhs, j, i, r);
+        }
+        if (with_x)
+            FieldIO<HISQ_FP64>::template store<double>(prm.x[j], prm.vh, 1, 0, i, x);
     }
     vec_block_sum<3, PAIR>(part, lds);
-    if (at.leader() && st.go) {
+    if (at.leader() && step) {
         const size_t o = (size_t)j * gridDim.x + blockIdx.x;
         prm.rr_part[o] = part[0];
         prm.rs_part[o] = part[1];
@@ -864,11 +902,7 @@ hipError_t launch_cg_restart(const CgVecParams &p, const double *trpart, hipStre
 int cg_vec_block(int vh) { return vh <= 32768 ? 64 : BLK; }
 int cg_vec_blocks(int vh) { return (vh + cg_vec_block(vh) - 1) / cg_vec_block(vh); }
 
-hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipStream_t st) {
-    cgcg_finalize_kernel<<<dim3((unsigned)p.nrhs), 256, 0, st>>>(p, after_check);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
+hipError_t launch_cgcg_update(const CgVecParams &p, int fp, hipStream_t st) {
     const int b = cg_vec_block(p.vh);
     const unsigned nb = (unsigned)cg_vec_blocks(p.vh);
     if (fp == HISQ_FP64)
@@ -878,6 +912,12 @@ hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipSt
     else
         cgcg_update_kernel<HISQ_FP32, false><<<dim3(nb, 1u), b, 0, st>>>(p);
     return hipGetLastError();
+}
+
+hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipStream_t st) {
+    cgcg_finalize_kernel<<<dim3((unsigned)p.nrhs), 256, 0, st>>>(p, after_check);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_cgcg_update(p, fp, st) : e;
 }
 
 hipError_t launch_residual_cols(int vh, int ncol, int nf, int col0, int fp, const void *b, int b_cols, const void *ax,

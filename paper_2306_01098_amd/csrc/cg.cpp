@@ -803,6 +803,23 @@ static hisq_status run_cg(Solver &S, const Columns &C, int nrhs, int max_iter, d
     if (launched > read)
         std::memcpy(hs.data(), pin.slot((int)(launched - 1)), sizeof(CgScalars) * nrhs);
 
+    // launches ended with columns still running: x may lack their last alpha p
+    bool x_later = false;
+    for (int j = 0; j < nrhs; ++j) {
+        x_later |= hs[j].xstep == X_LATER;
+        hs[j].go = hs[j].xstep == X_LATER ? 3 : 0;
+        hs[j].xstep = 0;
+    }
+    if (x_later) {
+        e = hipMemcpyAsync(dst, hs.data(), sizeof(CgScalars) * nrhs, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess)
+            e = launch_cgcg_update(vp, L.fs, st);
+        if (e == hipSuccess)
+            e = hipStreamSynchronize(st);
+        if (e != hipSuccess)
+            return device_fail(e, "cg end");
+    }
+
     // final report
     hisq_status result = HISQ_OK;
     for (int j = 0; j < nrhs; ++j) {

@@ -39,7 +39,9 @@ struct alignas(16) CgScalars {
     double delta2;   // reliable-update threshold delta^2 (0: only at convergence)
     double rho_new;  // <r, r> after the last update (kept when a flag is raised)
     double rtrue2;   // ||b - A x||^2 (FP64) at the last true-residual check
-    double spare;    // the batch solver's stop time stamp
+    // the batch solver's stop time stamp; single-reduction CG: the step length
+    // of the update before the last
+    double spare;
     double alpha;    // single-reduction CG: the step length of the last update
     int active;      // 1 while the recurrence runs
     int flag;        // FLAG_*
@@ -50,9 +52,13 @@ struct alignas(16) CgScalars {
     // redone; single-reduction CG: 1 while the next step starts the
     // directions afresh (p = r, s = w)
     int restart;
-    int go;          // single-reduction CG: the update kernel steps this column now
-    int pad;
+    int go;          // single-reduction CG: what the update kernel does to this column now
+    // single-reduction CG in two launches: X_LATER while x lacks the last
+    // update's alpha p, which the next one adds with its own (X_BOTH)
+    int xstep;
 };
+
+enum { X_LATER = 1, X_BOTH = 2 };
 
 // Per shift k of the multi-shift solver (Jegerlehner's recurrences, FP64).
 struct alignas(16) ShiftScalars {

@@ -241,3 +241,23 @@ def test_repeated_solves_on_the_same_buffers(gpu_lib):
         assert st == h.OK, (mass, nrhs, tol, info)
         res, _ = oracle_residuals(h, w, lat, x, nrhs, mass, w["src"][:nrhs])
         assert max(res) <= tol, (mass, nrhs, tol, res)
+
+
+@pytest.mark.parametrize("inner,nrhs", [("fp32", 2), ("fp32", 3)])
+@pytest.mark.parametrize("iters", [1, 2, 5, 6])
+def test_stop_after_odd_and_even_updates(gpu_lib, inner, nrhs, iters):
+    """The two-launch step moves x every second iteration: stopped at the
+    iteration limit after an odd and an even number, x has every term.  It is
+    the oracle's iterate to the FP32 rounding of a few operator applications
+    (each below 100 eps = 1.2e-5 of its result); the last term is far larger."""
+    h = gpu_lib
+    w = gen.workload_haar((6, 4, 8, 10), 48, -1, nrhs)
+    lat, l64, lin, b, x, ws = setup(h, w, inner, nrhs)
+    st, info = h.hisq_cg(lat, 0.5, l64, lin, inner, nrhs, b, x, 1e-12, iters, ws)
+    assert st == h.NOT_CONVERGED and [i["iterations"] for i in info] == [iters] * nrhs
+    _, xs = oracle_residuals(h, w, lat, x, nrhs, 0.5, w["src"])
+    for j in range(nrhs):
+        ref = O.cg(O.lattice_from(w), 0.5, w["src"][j], 1e-12, iters).x
+        before = O.cg(O.lattice_from(w), 0.5, w["src"][j], 1e-12, iters - 1).x if iters > 1 else 0 * ref
+        assert O.norm(ref - before) > 1e-2 * O.norm(ref)
+        assert O.norm(xs[j] - ref) <= 1e-4 * O.norm(ref)
