@@ -111,6 +111,8 @@ __host__ __device__ constexpr int field_prec_of(int prec) {
                                                           : prec;
 }
 
+constexpr size_t MALL_BYTES = (size_t)256 << 20;  // the last-level cache
+
 inline size_t links_bytes(const Geom &g, int prec) {
     return (size_t)2 * 4 * (size_t)g.vh * (link_matrix_bytes(prec) + link_matrix_bytes_w(prec));
 }

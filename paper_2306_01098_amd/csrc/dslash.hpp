@@ -161,34 +161,77 @@ template <int NIN, typename A> struct HopBuf {
 };
 
 // Whether column r (< NIN, unrolled) of a group of nr >= 1 columns is there.
-// ONE: the caller knows that the group is one column, and the test folds away,
-// which keeps the loads and their use out of a branch.  A field load in a
-// branch of its own had its binary16 conversion placed beside it in that
-// branch, so every hop of the FP16N one-column kernel waited for all of the
-// next hop's loads before computing the current one (32^3x8 FP16N 14.5 ->
-// 13.9 us, FP64 47.9 -> 46.8 us).  The one-column site kernel takes it with
-// every epilogue (FP64 CG 16.9 -> 16.6 ms; before eta was folded into the hop
-// signs the FP64 kernel with the fused dot product ran 46 -> 53 us with it);
-// with several columns the compiler hoisted more loads than the register file
-// holds.
-template <bool ONE> __device__ __forceinline__ constexpr bool has_col(int r, int nr) { return ONE || r < nr; }
+// ALL: the group is treated as one of all NIN columns (col_at), and the test
+// folds away, which keeps the loads and their use out of branches of their own.  A
+// branch around each column ended the compiler's scheduling region (with one
+// column, the FP16N field's binary16 conversion sat in the branch of its load,
+// so every hop waited for all of the next hop's loads: 32^3x8 14.5 -> 13.9 us).
+template <bool ALL> __device__ __forceinline__ constexpr bool has_col(int r, int nr) { return ALL || r < nr; }
+
+// Ends a group's hops: the sums are in registers here.  Without it the
+// compiler sinks a column's arithmetic to where its result is next used, behind
+// the branches of the epilogue, and holds every link and vector until there.
+template <bool ALL, int NIN, typename A> __device__ __forceinline__ void hops_done(cplx<A> (&acc)[NIN][3]) {
+    if constexpr (ALL && NIN > 1) {
+#pragma unroll
+        for (int r = 0; r < NIN; ++r)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                asm volatile("" : "+v"(acc[r][a].re), "+v"(acc[r][a].im));
+    }
+}
+
+// The column that slot r of a group stands for: past the last one (ALL) the
+// last one again, or the last pair where columns are loaded in pairs (its
+// second slot may be unused); the result is the same once more.
+template <int FP, int NIN, bool ALL> __device__ __forceinline__ int col_at(int r0, int r, int nr) {
+    if (!ALL || NIN == 1 || r < nr)
+        return r0 + r;
+    return FP == HISQ_FP32 && NIN % 2 == 0 ? r0 + ((nr - 1) & ~1) + (r & 1) : r0 + nr - 1;
+}
+
+// Hops that the loads of links run ahead with several columns: two where four
+// columns a thread leave the registers for it (16 rhs FP32 at 32^3x8: 92 -> 82
+// us; NIN 8 72 -> 73; FP32R12, whose third row is rebuilt in registers, 24^3x12
+// 48.2 -> 49.9).
+template <int LP, int FP, int NIN, bool ALL> __device__ __forceinline__ constexpr int links_ahead() {
+    return ALL && NIN == 4 && FP != HISQ_FP64 && !LinkIO<LP>::rebuild ? 2 : 1;
+}
+
+// Between the loads of the next hops and the arithmetic of this one, for
+// groups of several columns without branches: left alone, the compiler moves
+// each load down to its use to hold fewer registers, and nothing is in flight
+// while it computes (16 rhs FP32 at 48^3x12, one thread per site with NIN 8:
+// 459 us with a branch per column, 567 without, 427 with this; LDS-staged with
+// NIN 8: 399, 390, 384; 32^3x8, NIN 8: 90, 105, 74).
+template <bool ALL, int NIN> __device__ __forceinline__ void keep_loads_ahead() {
+    if constexpr (ALL && NIN > 1)
+        __builtin_amdgcn_sched_barrier(0);
+}
 
 // tmp += U v (or -U^+ v) with v = sg * (neighbour vectors in b); row 2 of a
 // compressed link (field f) is rebuilt here, after its loads have landed.
-template <int LP, int NIN, typename A, bool ONE = false>
+template <int LP, int NIN, typename A, bool ALL = false>
 __device__ __forceinline__ void hop_apply(const HopBuf<NIN, A> &bin, bool back, A sg, int nr,
                                           cplx<A> (&tmp)[NIN][3], int f) {
     HopBuf<NIN, A> b = bin;
     if constexpr (LinkIO<LP>::rebuild)
         LinkIO<LP>::finish(b.m, f);
+    // the sign goes to the 18 reals of the link where they are fewer than those
+    // of the vectors (the same products: a change of sign is exact)
+    if constexpr (NIN >= 4) {
+#pragma unroll
+        for (int e = 0; e < 18; ++e)
+            b.m[e] *= sg;
+    }
 #pragma unroll
     for (int r = 0; r < NIN; ++r) {
-        if (has_col<ONE>(r, nr)) {
+        if (has_col<ALL>(r, nr)) {
             cplx<A> v[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                v[c].re = b.v[r][c].re * sg;
-                v[c].im = b.v[r][c].im * sg;
+                v[c].re = NIN >= 4 ? b.v[r][c].re : b.v[r][c].re * sg;
+                v[c].im = NIN >= 4 ? b.v[r][c].im : b.v[r][c].im * sg;
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a)
@@ -215,35 +258,46 @@ __device__ __forceinline__ void hop_load(HopBuf<NIN, A> &b, const char *blk, int
 // 16-byte access per colour (r0 is a multiple of NIN, so the group starts on
 // a pair; the pair of an odd last column has an unused second slot, which
 // is loaded and never used, and stored as zero).
-template <int FP, int NIN, typename A, bool ONE = false>
+template <int FP, int NIN, typename A, bool ALL = false>
 __device__ __forceinline__ void load_group(const void *f, int vh, int ncol, int r0, int nr, int i,
                                            cplx<A> (&v)[NIN][3]) {
     if constexpr (FP == HISQ_FP32 && NIN % 2 == 0) {
 #pragma unroll
         for (int r = 0; r < NIN; r += 2)
-            if (has_col<ONE>(r, nr))
-                FieldIO<FP>::template load_pair<A>(f, vh, (r0 + r) >> 1, i, v[r], v[r + 1]);
+            if (has_col<ALL>(r, nr))
+                FieldIO<FP>::template load_pair<A>(f, vh, col_at<FP, NIN, ALL>(r0, r, nr) >> 1, i, v[r], v[r + 1]);
     } else {
 #pragma unroll
         for (int r = 0; r < NIN; ++r)
-            if (has_col<ONE>(r, nr))
-                FieldIO<FP>::template load<A>(f, vh, ncol, r0 + r, i, v[r]);
+            if (has_col<ALL>(r, nr))
+                FieldIO<FP>::template load<A>(f, vh, ncol, col_at<FP, NIN, ALL>(r0, r, nr), i, v[r]);
     }
 }
 
-template <int FP, int NIN, typename A, bool ONE = false>
+template <int FP, int NIN, typename A, bool ALL = false>
 __device__ __forceinline__ void store_group(void *f, int vh, int ncol, int r0, int nr, int i,
                                             const cplx<A> (&v)[NIN][3]) {
+    // ALL: slots past the last column hold its values once more and store them
+    // once more; a store in a branch would take the column's arithmetic into
+    // that branch.  The second slot of an odd last column's pair gets zero.
     if constexpr (FP == HISQ_FP32 && NIN % 2 == 0) {
 #pragma unroll
         for (int r = 0; r < NIN; r += 2)
-            if (has_col<ONE>(r, nr))
-                FieldIO<FP>::template store_pair<A>(f, vh, (r0 + r) >> 1, i, v[r], v[r + 1]);
+            if (has_col<ALL>(r, nr)) {
+                cplx<A> w[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const bool none = ALL && (nr & 1) && r + 1 >= nr;
+                    w[c].re = none ? (A)0 : v[r + 1][c].re;
+                    w[c].im = none ? (A)0 : v[r + 1][c].im;
+                }
+                FieldIO<FP>::template store_pair<A>(f, vh, col_at<FP, NIN, ALL>(r0, r, nr) >> 1, i, v[r], w);
+            }
     } else {
 #pragma unroll
         for (int r = 0; r < NIN; ++r)
-            if (has_col<ONE>(r, nr))
-                FieldIO<FP>::template store<A>(f, vh, ncol, r0 + r, i, v[r]);
+            if (has_col<ALL>(r, nr))
+                FieldIO<FP>::template store<A>(f, vh, ncol, col_at<FP, NIN, ALL>(r0, r, nr), i, v[r]);
     }
 }
 
@@ -326,7 +380,7 @@ __device__ __forceinline__ HopAddr hop_addr(const Geom &g, int p, const char *li
 // accumulators and their zeroing: 16 rhs FP32 NIN 4 216 -> 149 VGPRs, FP64
 // NIN 2 256 -> 192; 48^3x12 16 rhs FP16N links 475 -> 439 us, FP64 950 -> 924
 // us, 32^3x8 FP64 47.0 -> 46.2 us).
-template <int LP, int FP, int NIN, typename A, bool NT, bool ONE = false>
+template <int LP, int FP, int NIN, typename A, bool NT, bool ALL = false>
 __device__ __forceinline__ void dslash_site(const Geom &g, int p, const char *links, const void *in, int i,
                                             int ncol, int r0, int nr, cplx<A> (&acc)[NIN][3]) {
     const Site s = site_coords(g, p, i);
@@ -340,39 +394,49 @@ __device__ __forceinline__ void dslash_site(const Geom &g, int p, const char *li
         // several right-hand sides: the neighbour vectors two hops ahead, the
         // links one (16 rhs at 48^3x12: FP64 948 -> 918 us, FP32 534 -> 522 us;
         // at one rhs the FP64 kernel was 2 % slower, so it keeps one hop)
-        HopBuf<NIN, A> lb[2];
-        cplx<A> vb[3][NIN][3];
-        A sgv[3];
-        bool bkv[3];
+        constexpr int VD = 2, LD = links_ahead<LP, FP, NIN, ALL>();
+        A lm[LD + 1][18];
+        cplx<A> vb[VD + 1][NIN][3];
+        A sgv[VD + 1];
+        bool bkv[VD + 1];
         auto load_link = [&](int k, int slot) {
             A sg;
             const HopAddr h = hop_addr<LP, A>(g, p, links, i, s, k, sg);
-            LinkIO<LP>::template load<NT>(h.blk, g.vh, h.ilink, lb[slot].m, h.f);
+            LinkIO<LP>::template load<NT>(h.blk, g.vh, h.ilink, lm[slot], h.f);
         };
         auto load_vec = [&](int k, int slot) {
             A sg;
             const HopAddr h = hop_addr<LP, A>(g, p, links, i, s, k, sg);
-            load_group<FP, NIN, A>(in, g.vh, ncol, r0, nr, h.ipsi, vb[slot]);
+            load_group<FP, NIN, A, ALL>(in, g.vh, ncol, r0, nr, h.ipsi, vb[slot]);
             sgv[slot] = sg * eta(k);
             bkv[slot] = h.back;
         };
-        load_vec(0, 0);
-        load_link(0, 0);
-        load_vec(1, 1);
+#pragma unroll
+        for (int k = 0; k < VD; ++k)
+            load_vec(k, k);
+#pragma unroll
+        for (int k = 0; k < LD; ++k)
+            load_link(k, k);
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const int cur = k & 1, vc = k % 3;
-            if (k + 2 < 16)
-                load_vec(k + 2, (k + 2) % 3);
-            if (k + 1 < 16)
-                load_link(k + 1, cur ^ 1);
+            const int lc = k % (LD + 1), vc = k % (VD + 1);
+            if (k + VD < 16)
+                load_vec(k + VD, (k + VD) % (VD + 1));
+            if (k + LD < 16)
+                load_link(k + LD, (k + LD) % (LD + 1));
+            keep_loads_ahead<ALL, NIN>();
+            HopBuf<NIN, A> cur;
+#pragma unroll
+            for (int e = 0; e < 18; ++e)
+                cur.m[e] = lm[lc][e];
 #pragma unroll
             for (int r = 0; r < NIN; ++r)
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
-                    lb[cur].v[r][c] = vb[vc][r][c];
-            hop_apply<LP, NIN, A>(lb[cur], bkv[vc], sgv[vc], nr, acc, (k & 3) >> 1);
+                    cur.v[r][c] = vb[vc][r][c];
+            hop_apply<LP, NIN, A, ALL>(cur, bkv[vc], sgv[vc], nr, acc, (k & 3) >> 1);
         }
+        hops_done<ALL, NIN, A>(acc);
         return;
     }
     HopBuf<NIN, A> buf[2];
@@ -382,7 +446,7 @@ __device__ __forceinline__ void dslash_site(const Geom &g, int p, const char *li
         A sg;
         const HopAddr h = hop_addr<LP, A>(g, p, links, i, s, k, sg);
         LinkIO<LP>::template load<NT>(h.blk, g.vh, h.ilink, buf[slot].m, h.f);
-        load_group<FP, NIN, A, ONE>(in, g.vh, ncol, r0, nr, h.ipsi, buf[slot].v);
+        load_group<FP, NIN, A, ALL>(in, g.vh, ncol, r0, nr, h.ipsi, buf[slot].v);
         sgn[slot] = sg * eta(k);
         back[slot] = h.back;
     };
@@ -392,7 +456,7 @@ __device__ __forceinline__ void dslash_site(const Geom &g, int p, const char *li
         const int cur = k & 1;
         if (k + 1 < 16)
             load(k + 1, cur ^ 1);
-        hop_apply<LP, NIN, A, ONE>(buf[cur], back[cur], sgn[cur], nr, acc, (k & 3) >> 1);
+        hop_apply<LP, NIN, A, ALL>(buf[cur], back[cur], sgn[cur], nr, acc, (k & 3) >> 1);
     }
 }
 
@@ -464,9 +528,9 @@ __device__ __forceinline__ void dslash_dot_reduce(const DslashParams &prm, doubl
 
 // NT: link loads with the non-temporal hint (chosen by the launcher when
 // each link is read once: one group of right-hand sides, FP64 or FP32 links).
-template <int LP, int FP, int NIN, int EPI, bool NT>
+// ALL: see has_col (chosen by the launcher, groups_whole).
+template <int LP, int FP, int NIN, int EPI, bool NT, bool ALL>
 __global__ void __launch_bounds__(256) dslash_site_kernel(const DslashParams prm) {
-    constexpr bool ONE = NIN == 1;  // has_col
     using A = typename Prec<LP>::acc;
     if (prm.skip && *prm.skip)
         return;
@@ -484,16 +548,16 @@ __global__ void __launch_bounds__(256) dslash_site_kernel(const DslashParams prm
         dot[r] = 0.0;
     if (valid) {
         cplx<A> acc[NIN][3];
-        dslash_site<LP, FP, NIN, A, NT, ONE>(prm.g, prm.out_parity, prm.links, prm.in, i, prm.nrhs, r0, nr, acc);
+        dslash_site<LP, FP, NIN, A, NT, ALL>(prm.g, prm.out_parity, prm.links, prm.in, i, prm.nrhs, r0, nr, acc);
         if constexpr (EPI != EPI_PLAIN) {
             cplx<A> yv[NIN][3];
-            load_group<FP, NIN, A>(prm.y, prm.g.vh, prm.nrhs, r0, nr, i, yv);
+            load_group<FP, NIN, A, ALL>(prm.y, prm.g.vh, prm.nrhs, r0, nr, i, yv);
 #pragma unroll
             for (int r = 0; r < NIN; ++r)
-                if (r < nr)
-                    dot[r] = epilogue_y<EPI, A>(prm, r0 + r, yv[r], acc[r]);
+                if (has_col<ALL>(r, nr))
+                    dot[r] = epilogue_y<EPI, A>(prm, col_at<FP, NIN, ALL>(r0, r, nr), yv[r], acc[r]);
         }
-        store_group<FP, NIN, A, ONE>(prm.out, prm.g.vh, prm.nrhs, r0, nr, i, acc);
+        store_group<FP, NIN, A, ALL>(prm.out, prm.g.vh, prm.nrhs, r0, nr, i, acc);
     }
     if (EPI == EPI_AXPY_DOT)
         dslash_dot_reduce<NIN>(prm, dot, bp);
@@ -671,7 +735,7 @@ constexpr int LDS_BAND = 8;
 constexpr int LDS_HALO = 3;
 
 template <int FP> struct StageElem;
-template <> struct StageElem<HISQ_FP64> { using T = double2; };
+template <> struct StageElem<HISQ_FP64> { using T = nt_d2; };
 template <> struct StageElem<HISQ_FP32> { using T = float2; };
 
 // Bytes of LDS a VAR_LDS block needs for nin right-hand sides.
@@ -679,7 +743,8 @@ __host__ __device__ inline size_t lds_stage_bytes(const Geom &g, int fp, int nin
     return (size_t)nin * 3 * (LDS_BAND + 2 * LDS_HALO) * g.hx * (fp == HISQ_FP64 ? 16 : 8);
 }
 
-template <int LP, int FP, int NIN, int EPI, bool NT>
+// ALL: see has_col.
+template <int LP, int FP, int NIN, int EPI, bool NT, bool ALL>
 __global__ void __launch_bounds__(256) dslash_lds_kernel(const DslashParams prm) {
     using A = typename Prec<LP>::acc;
     using E = typename StageElem<FP>::T;
@@ -707,68 +772,68 @@ __global__ void __launch_bounds__(256) dslash_lds_kernel(const DslashParams prm)
     const int nrow = LDS_BAND + 2 * LDS_HALO;
     const int r0 = bp.r0, nr = bp.nr;
     // stage rows y0 - 3 .. y0 + band + 2 (periodic in y) of the input parity:
-    // blockDim = LDS_BAND * hx threads and NIN * 3 * nrow * hx elements, so
-    // each thread copies at most PER of them; all its loads are issued
-    // before the first LDS store
-    // FP32 fields with NIN even: whole column pairs, one 16-byte record per
-    // (pair, colour, site), staged as such
+    // of each (column, colour) a thread copies the site that is its own place
+    // in rows 0 .. band - 1 of the staged rows and, if it is in the first six
+    // rows, also that of the last six; all its loads are issued before the
+    // first LDS store.  (A list of elements dealt out to the threads in turn
+    // cost two integer divisions an element, 600 of the 3650 vector
+    // instructions of a wavefront.)  FP32 fields with NIN even: whole column
+    // pairs, one 16-byte record per (pair, colour, site), staged as such.
     constexpr bool PAIRS = FP == HISQ_FP32 && NIN % 2 == 0;
-    if constexpr (PAIRS) {
-        constexpr int PER = ((NIN / 2) * 3 * (LDS_BAND + 2 * LDS_HALO) + LDS_BAND - 1) / LDS_BAND;
+    const int ry = threadIdx.x / g.hx, xh = threadIdx.x - ry * g.hx;
+    {
+        const bool second = ry < 2 * LDS_HALO;
+        int gy0 = y0 - LDS_HALO + ry;
+        gy0 = gy0 < 0 ? gy0 + g.ny : gy0;
+        // threads without a second site load one of the piece and do not store
+        // it (unconditional loads keep the staged values in registers)
+        int gy1 = second ? y0 - LDS_HALO + LDS_BAND + ry : y0;
+        gy1 = gy1 >= g.ny ? gy1 - g.ny : gy1;
+        const int i0 = plane + gy0 * g.hx + xh, i1 = plane + gy1 * g.hx + xh;
         const int per_rc = nrow * g.hx;
-        const int total = ((nr + 1) / 2) * 3 * per_rc;
-        const nt_f4 *src = reinterpret_cast<const nt_f4 *>(prm.in);
-        nt_f4 *stage4 = reinterpret_cast<nt_f4 *>(lds_raw);
-        nt_f4 v[PER];
+        // past the group's columns: the last one again (col_at)
+        if constexpr (PAIRS) {
+            constexpr int PER = 3 * NIN / 2;
+            const int last = (nr + 1) / 2 - 1;
+            const nt_f4 *src = reinterpret_cast<const nt_f4 *>(prm.in) + (size_t)(r0 / 2) * 3 * g.vh;
+            nt_f4 *stage4 = reinterpret_cast<nt_f4 *>(lds_raw);
+            nt_f4 v[2][PER];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            // past the staged records: the group's first record, loaded and
-            // not stored (unconditional loads keep v in registers)
-            const int e0 = threadIdx.x + j * blockDim.x;
-            const int e = e0 < total ? e0 : 0;
-            const int pc = e / per_rc, rem = e - pc * per_rc;
-            const int row = rem / g.hx, xh = rem - row * g.hx;
-            int gy = y0 - LDS_HALO + row;
-            gy = gy < 0 ? gy + g.ny : (gy >= g.ny ? gy - g.ny : gy);
-            v[j] = src[((size_t)(r0 / 2) * 3 + pc) * g.vh + plane + gy * g.hx + xh];
-        }
+            for (int e = 0; e < PER; ++e) {
+                const nt_f4 *f = src + (size_t)(3 * min(e / 3, last) + e % 3) * g.vh;
+                v[0][e] = f[i0];
+                v[1][e] = f[i1];
+            }
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int e = threadIdx.x + j * blockDim.x;
-            if (e < total)
-                stage4[e] = v[j];
-        }
-    } else {
-        constexpr int PER = (NIN * 3 * (LDS_BAND + 2 * LDS_HALO) + LDS_BAND - 1) / LDS_BAND;
-        const int per_rc = nrow * g.hx;
-        const int total = nr * 3 * per_rc;
-        const E *src = reinterpret_cast<const E *>(prm.in);
-        E v[PER];
+            for (int e = 0; e < PER; ++e) {
+                stage4[e * per_rc + threadIdx.x] = v[0][e];
+                if (second)
+                    stage4[e * per_rc + LDS_BAND * g.hx + threadIdx.x] = v[1][e];
+            }
+        } else {
+            constexpr int PER = 3 * NIN;
+            const E *src = reinterpret_cast<const E *>(prm.in);
+            E v[2][PER];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            // past the staged elements: the group's first element, loaded and
-            // not stored (unconditional loads keep v in registers)
-            const int e0 = threadIdx.x + j * blockDim.x;
-            const int e = e0 < total ? e0 : 0;
-            const int rc = e / per_rc, rem = e - rc * per_rc;
-            const int row = rem / g.hx, xh = rem - row * g.hx;
-            int gy = y0 - LDS_HALO + row;
-            gy = gy < 0 ? gy + g.ny : (gy >= g.ny ? gy - g.ny : gy);
-            const int site = plane + gy * g.hx + xh;
-            if constexpr (FP == HISQ_FP32)
-                v[j] = src[f32_index(g.vh, prm.nrhs, r0 + rc / 3, rc % 3, site)];
-            else
-                v[j] = src[(size_t)(r0 * 3 + rc) * g.vh + site];
-        }
+            for (int e = 0; e < PER; ++e) {
+                const int col = r0 + min(e / 3, nr - 1);
+                if constexpr (FP == HISQ_FP32) {
+                    v[0][e] = src[f32_index(g.vh, prm.nrhs, col, e % 3, i0)];
+                    v[1][e] = src[f32_index(g.vh, prm.nrhs, col, e % 3, i1)];
+                } else {
+                    v[0][e] = src[(size_t)(3 * col + e % 3) * g.vh + i0];
+                    v[1][e] = src[(size_t)(3 * col + e % 3) * g.vh + i1];
+                }
+            }
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int e = threadIdx.x + j * blockDim.x;
-            if (e < total)
-                stage[e] = v[j];
+            for (int e = 0; e < PER; ++e) {
+                stage[e * per_rc + threadIdx.x] = v[0][e];
+                if (second)
+                    stage[e * per_rc + LDS_BAND * g.hx + threadIdx.x] = v[1][e];
+            }
         }
     }
     __syncthreads();
-    const int ry = threadIdx.x / g.hx, xh = threadIdx.x - ry * g.hx;
     const int y = y0 + ry;
     const int i = plane + y * g.hx + xh;
     Site s;
@@ -783,16 +848,18 @@ __global__ void __launch_bounds__(256) dslash_lds_kernel(const DslashParams prm)
         const int par = (mu >= 1 ? s.x : 0) + (mu >= 2 ? s.y : 0) + (mu >= 3 ? s.z : 0);
         return (par & 1) ? (A)-1 : (A)1;
     };
-    HopBuf<NIN, A> buf[2];
-    A sgn[2];
-    bool back[2];
+    // loads run one hop ahead, two with four columns (16 rhs FP32 at 48^3x12: 424 -> 414 us; NIN 8 381 -> 434)
+    constexpr int D = links_ahead<LP, FP, NIN, ALL>();
+    HopBuf<NIN, A> buf[D + 1];
+    A sgn[D + 1];
+    bool back[D + 1];
     auto load = [&](int k, int slot) {
         A sg;
         const HopAddr h = hop_addr<LP, A>(g, p, prm.links, i, s, k, sg);
         LinkIO<LP>::template load<NT>(h.blk, g.vh, h.ilink, buf[slot].m, h.f);
         const int mu = k >> 2;
         if (mu >= 2) {
-            load_group<FP, NIN, A>(prm.in, g.vh, prm.nrhs, r0, nr, h.ipsi, buf[slot].v);
+            load_group<FP, NIN, A, ALL>(prm.in, g.vh, prm.nrhs, r0, nr, h.ipsi, buf[slot].v);
         } else {
             // LDS row and column of the neighbour: x-hops stay in the row,
             // y-hops move rows (the staged rows start at y0 - 3)
@@ -825,7 +892,7 @@ __global__ void __launch_bounds__(256) dslash_lds_kernel(const DslashParams prm)
             } else {
 #pragma unroll
                 for (int r = 0; r < NIN; ++r) {
-                    if (r < nr) {
+                    if (has_col<ALL>(r, nr)) {
 #pragma unroll
                         for (int c = 0; c < 3; ++c) {
                             const E e = stage[((r * 3 + c) * nrow + row) * g.hx + col];
@@ -839,27 +906,31 @@ __global__ void __launch_bounds__(256) dslash_lds_kernel(const DslashParams prm)
         sgn[slot] = sg * eta(k);
         back[slot] = h.back;
     };
-    load(0, 0);
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+        load(k, k);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        const int cur = k & 1;
-        if (k + 1 < 16)
-            load(k + 1, cur ^ 1);
-        hop_apply<LP, NIN, A>(buf[cur], back[cur], sgn[cur], nr, acc, (k & 3) >> 1);
+        const int cur = k % (D + 1);
+        if (k + D < 16)
+            load(k + D, (k + D) % (D + 1));
+        keep_loads_ahead<ALL, NIN>();
+        hop_apply<LP, NIN, A, ALL>(buf[cur], back[cur], sgn[cur], nr, acc, (k & 3) >> 1);
     }
+    hops_done<ALL, NIN, A>(acc);
     double dot[NIN];
 #pragma unroll
     for (int r = 0; r < NIN; ++r)
         dot[r] = 0.0;
     if constexpr (EPI != EPI_PLAIN) {
         cplx<A> yv[NIN][3];
-        load_group<FP, NIN, A>(prm.y, g.vh, prm.nrhs, r0, nr, i, yv);
+        load_group<FP, NIN, A, ALL>(prm.y, g.vh, prm.nrhs, r0, nr, i, yv);
 #pragma unroll
         for (int r = 0; r < NIN; ++r)
-            if (r < nr)
-                dot[r] = epilogue_y<EPI, A>(prm, r0 + r, yv[r], acc[r]);
+            if (has_col<ALL>(r, nr))
+                dot[r] = epilogue_y<EPI, A>(prm, col_at<FP, NIN, ALL>(r0, r, nr), yv[r], acc[r]);
     }
-    store_group<FP, NIN, A>(prm.out, g.vh, prm.nrhs, r0, nr, i, acc);
+    store_group<FP, NIN, A, ALL>(prm.out, g.vh, prm.nrhs, r0, nr, i, acc);
     if (EPI == EPI_AXPY_DOT)
         dslash_dot_reduce<NIN>(prm, dot, bp);
 }

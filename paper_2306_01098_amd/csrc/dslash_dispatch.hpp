@@ -12,9 +12,21 @@ namespace hisq {
 // right-hand sides), the format profits (FP64, FP32, W14) and the link set
 // exceeds the MALL, so that ordinary loads would leave nothing cached for the
 // next application.
-constexpr size_t MALL_BYTES = (size_t)256 << 20;
 template <int LP> inline bool links_stream(const Geom &g, int nouter) {
     return LinkIO<LP>::stream && nouter == 1 && links_bytes(g, LP) > MALL_BYTES;
+}
+
+// Whether the groups of right-hand sides run as whole ones (has_col): the
+// columns past the last group's end cost their arithmetic, so at most a
+// quarter of the real ones.  FP64: with four columns a thread the loads kept
+// ahead leave one wavefront per SIMD (16 rhs, one thread per site, 48^3x12:
+// 920 -> 962 us; LDS-staged 1550 -> 905), with eight they do not fit.
+template <int FP, int NIN, int VAR> constexpr bool whole_groups_fit() {
+    return FP != HISQ_FP64 || NIN <= (VAR == VAR_LDS ? 4 : 2);
+}
+template <int NIN> inline bool groups_whole(int nrhs) {
+    const int nouter = (nrhs + NIN - 1) / NIN;
+    return 4 * (nouter * NIN - nrhs) <= nrhs;
 }
 
 template <int LP, int FP, int NIN, int EPI>
@@ -31,11 +43,17 @@ hipError_t dslash_go(const DslashParams &prm, DslashShape s, hipStream_t st) {
             p.band = LDS_BAND;
             const size_t shm = lds_stage_bytes(prm.g, FP, NIN);
             const bool nt = links_stream<LP>(prm.g, nouter);
-            if (nt)
-                dslash_lds_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream>
-                    <<<dim3((unsigned)(nsb * nouter)), threads, shm, st>>>(p);
+            constexpr bool W = whole_groups_fit<FP, NIN, VAR_LDS>();
+            const bool whole = W && groups_whole<NIN>(prm.nrhs);
+            const dim3 grid((unsigned)(nsb * nouter));
+            if (nt && whole)
+                dslash_lds_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream, W><<<grid, threads, shm, st>>>(p);
+            else if (nt)
+                dslash_lds_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream, NIN == 1><<<grid, threads, shm, st>>>(p);
+            else if (whole)
+                dslash_lds_kernel<LP, FP, NIN, EPI, false, W><<<grid, threads, shm, st>>>(p);
             else
-                dslash_lds_kernel<LP, FP, NIN, EPI, false><<<dim3((unsigned)(nsb * nouter)), threads, shm, st>>>(p);
+                dslash_lds_kernel<LP, FP, NIN, EPI, false, NIN == 1><<<grid, threads, shm, st>>>(p);
             hipError_t e = hipGetLastError();
             if (e == hipSuccess && EPI == EPI_AXPY_DOT && p.dot_out != nullptr)
                 e = launch_sum_partials(p.partials, p.nrhs, nsb, p.dot_out, p.dot_stride > 0 ? p.dot_stride : 1,
@@ -68,10 +86,16 @@ hipError_t dslash_go(const DslashParams &prm, DslashShape s, hipStream_t st) {
         else
             dslash_dir_kernel<LP, FP, NIN, EPI, false><<<grid, s.block, 0, st>>>(p);
     } else {
-        if (nt)
-            dslash_site_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream><<<grid, s.block, 0, st>>>(p);
+        constexpr bool W = whole_groups_fit<FP, NIN, VAR_SITE>();
+        const bool whole = W && groups_whole<NIN>(prm.nrhs);
+        if (nt && whole)
+            dslash_site_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream, W><<<grid, s.block, 0, st>>>(p);
+        else if (nt)
+            dslash_site_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream, NIN == 1><<<grid, s.block, 0, st>>>(p);
+        else if (whole)
+            dslash_site_kernel<LP, FP, NIN, EPI, false, W><<<grid, s.block, 0, st>>>(p);
         else
-            dslash_site_kernel<LP, FP, NIN, EPI, false><<<grid, s.block, 0, st>>>(p);
+            dslash_site_kernel<LP, FP, NIN, EPI, false, NIN == 1><<<grid, s.block, 0, st>>>(p);
     }
     hipError_t e = hipGetLastError();
     // dot_out == nullptr: the caller sums the partials itself

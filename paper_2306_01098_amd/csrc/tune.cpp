@@ -22,7 +22,7 @@ struct ShapeCost {
 constexpr ShapeCost COST_FP64[] = {{VAR_DIR, 1, 3.5, 0.239}, {VAR_DIR, 2, 4.1, 0.34},  {VAR_SITE, 1, 4.8, 0.129},
                                    {VAR_SITE, 2, 6.3, 0.184}, {VAR_SITE, 4, 9.7, 0.295}};
 constexpr ShapeCost COST_FP32[] = {{VAR_DIR, 1, 3.5, 0.148}, {VAR_DIR, 2, 3.8, 0.16},   {VAR_SITE, 1, 4.8, 0.06},
-                                   {VAR_SITE, 2, 6.2, 0.083}, {VAR_SITE, 4, 8.7, 0.141}, {VAR_LDS, 4, 8.2, 0.145}};
+                                   {VAR_SITE, 2, 6.2, 0.083}, {VAR_SITE, 4, 8.7, 0.141}, {VAR_LDS, 4, 8.2, 0.135}};
 constexpr ShapeCost COST_FP16[] = {{VAR_DIR, 1, 3.5, 0.074}, {VAR_SITE, 1, 4.4, 0.036}};
 
 // Several right-hand sides on a lattice that one thread per site and group of
@@ -54,20 +54,79 @@ DslashShape small_multi_shape(const Geom &g, int fp, int nrhs) {
     return best;
 }
 
+// Several right-hand sides on lattices that fill the chip.  The lines lie
+// between measured launches at 48^3x12, 32^3x8, 24^3x12 (times below in this
+// order; z-slab order in 8-row y-bands where N_z allows it), a few at 20^3x24,
+// 32^3x16, 48^3x8, 32^2x48x12, 32^2x64x8, 48^2x32x8, 64x32^2x8 and 64^3x6.
+//
+// FP32 fields: groups of eight columns, or of four where that leaves fewer
+// empty places, staged in LDS once links and vectors exceed the MALL (the
+// neighbour rows then come from HBM), else through the caches:
+// FP32 links, 16 rhs: staged 4 / staged 8 / site 8: 414 / 380 / 425, 79 / 84 /
+// 72, - / - / 54 us; 8 rhs: 251 / 212 / 238, 46 / 47 / 43 and site 4 41, site 4
+// / 8 31 / 36; 5 rhs staged 8 190, site 8 205; 40; 26.  FP32R12 links, 16 rhs:
+// 355 / 340 / 379, 70 / 77 / 69; FP32W14 402 / 369 / 411, 79 / 81 / 72.
+DslashShape large_multi_fp32(const Geom &g, int lp, int nrhs) {
+    const int remap = g.nz % 8 == 0 ? 2 : 1;
+    const bool large = links_bytes(g, lp) + 2 * field_bytes(g, HISQ_FP32, nrhs) > MALL_BYTES;
+    const int eights = (nrhs + 7) / 8 * 8 - nrhs <= 3;  // 5 .. 8, 13 .. 16
+    // (from ten columns staged in any case: a solver moves more between two
+    // launches; 32^3x8 at 16 rhs is not large by itself, 72 us with eight through
+    // the caches, but 60 iterations of its CG take 20.7 ms then and 20.0 staged)
+    if (large || nrhs > 9) {
+        const DslashShape l{VAR_LDS, nrhs == 2 ? 2 : eights && large ? 8 : 4, LDS_BAND * g.hx, 2};
+        if (dslash_shape_fits(l, g, HISQ_FP32))
+            return l;
+        // (64x32^2x8, which fits four columns, not eight: staged 4 / site 8, 8
+        // rhs 114 / 101, 16 rhs 225 / 225)
+        if (eights && large && lp != HISQ_FP32R12)  // FP32R12, 16 rhs at 44x36x28x14: site 4 / 8 196 / 204
+            return DslashShape{VAR_SITE, 8, g.vh >= (1 << 22) ? 256 : 128, remap};
+    }
+    if (nrhs == 5 || nrhs == 6)
+        return DslashShape{VAR_SITE, 8, 128, remap};
+    if (nrhs == 2 || (nrhs == 9 && !large))  // 9: 40.5 us against 49 as 4 + 4 + 1
+        return DslashShape{VAR_SITE, 2, 128, remap};
+    return DslashShape{VAR_SITE, 4, nrhs <= 4 || nrhs > 12 ? 128 : 256, remap};
+}
+
+// FP64 fields: four columns a thread, staged in LDS once the links exceed the
+// MALL (16 rhs, site 4 / staged 4: FP64 918 / 906, 203 / 190 us; 8 rhs 538 / 519,
+// 117 / 111; 16 rhs FP64R12 834 / 749, FP64W14 890 / 870, 196 / 179).  Five and
+// six: eight a thread, in registers beyond the first 256, which saves a pass
+// over the links (6 rhs, site 4 / 8: 468 / 406, 100 / 84; 8 rhs gained at two
+// lattices and lost at 24x16x32x44, 236 / 263).  Links within the MALL: two a
+// thread where groups of four would be half empty (6 rhs at 24^3x12: 65 / 55,
+// FP64R12 57 / 45; 14 rhs 112 / 100, 104 / 85, on small lattices only: 32^3x8
+// FP64R12 153 / 164).
+DslashShape large_multi_fp64(const Geom &g, int lp, int nrhs) {
+    const int remap = g.nz % 8 == 0 ? 2 : 1;
+    // (two at 18x16x18x14: blocks of 128 19.6 us, of 64 15.2; 24^3x12 34.6 / 35.6)
+    const DslashShape four{VAR_SITE, nrhs == 2 ? 2 : 4, nrhs == 2 && g.vh < 65536 ? 64 : 128, remap};
+    const bool half = nrhs % 4 == 1 || nrhs % 4 == 2;
+    if (nrhs <= 3)  // three as one group of four: 24^3x12 57 -> 42 us
+        return four;
+    if (links_bytes(g, lp) < MALL_BYTES)
+        return half && (nrhs <= 10 || g.vh < 98304) ? DslashShape{VAR_SITE, 2, 64, remap} : four;
+    if (lp != HISQ_FP64R12 && (nrhs == 5 || nrhs == 6))
+        return DslashShape{VAR_SITE, 8, 128, remap};
+    if (lp != HISQ_FP64R12 && nrhs > 4 && half)  // 14 rhs, site 4 / staged 4: 821 / 864
+        return four;
+    const DslashShape l{VAR_LDS, 4, LDS_BAND * g.hx, 2};
+    return dslash_shape_fits(l, g, HISQ_FP64) ? l : four;
+}
+
+// FP16N fields: two columns a thread; two and three columns one by one below
+// 262144 sites (2 rhs, one / two: 32^3x8 15.1 / 19.5 us, 48^3x12 - / 87).
+DslashShape large_multi_fp16(const Geom &g, int nrhs) {
+    return DslashShape{VAR_SITE, nrhs <= 3 && g.vh < 262144 ? 1 : 2, 256, g.nz % 8 == 0 ? 2 : 1};
+}
+
 // Built-in shapes (measured on MI355X): one thread per site (four lanes per
 // site on lattices too small to fill the chip); with several right-hand sides
-// and enough sites one thread per site holding four of them (FP16N fields: two;
-// FP32 links and fields: eight) in blocks of 256 (FP32 and FP16N fields) or 128
-// (FP64 fields; eight FP32 rhs); FP32 fields of at least four columns on
-// lattices the LDS staging fits: the LDS-staged mapping, four rhs per thread;
-// with several right-hand sides on small lattices: small_multi_shape.
+// large_multi_*, on small lattices small_multi_shape.
 DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
-    // measured on 32^3x8 at one right-hand side and 48^3x12 at 4 and 16:
-    // the per-site mapping wins everywhere once the N_outer groups of a site
-    // range run together; more than 4 (FP16N: 2) accumulators per thread cost
-    // more in occupancy than the shared link loads save.  At one right-hand
-    // side the z-slab block order (when N_z allows it) keeps the t-hops inside
-    // each XCD: 32^3x8 FP64 53.1 -> 48.1 us.
+    // At one right-hand side the z-slab block order (when N_z allows it) keeps
+    // the t-hops inside each XCD: 32^3x8 FP64 53.1 -> 48.1 us.
     DslashShape s;
     s.variant = VAR_SITE;
     s.xcd_remap = 1;
@@ -112,44 +171,11 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
                         dslash_shape_fits(DslashShape{VAR_LDS, 4, LDS_BAND * g.hx, 2}, g, fp);
     if (!staged && g.vh < (fp == HISQ_FP64 ? 32768 : 49152))
         return small_multi_shape(g, fp, nrhs);
-    // Five or six FP32 columns as one group of eight instead of two of four: the
-    // links are read once (24^3x12 36.9 -> 26.3 us, 24^4 82 -> 55, 48^3x12
-    // 250-265 -> 205; FP32R12 5 rhs at 32^3x8 45 -> 33, at 48^3x12 194 -> 189).
-    if (fp == HISQ_FP32 && (lp == HISQ_FP32 || lp == HISQ_FP32R12) && (nrhs == 5 || nrhs == 6) && g.vh >= 65536)
-        return DslashShape{VAR_SITE, 8, g.vh >= (1 << 22) ? 256 : 128, g.nz % 8 == 0 ? 2 : 1};  // 256: fewer partials
-    // FP32 fields: the x- and y-hop vectors of four rhs per thread staged in
-    // LDS where the lattice allows it (16 rhs at 48^3x12: FP32 links 461 ->
-    // 421 us, FP32R12 413 -> 365 us; the 16-rhs CG with FP32 links 0.407 ->
-    // 0.390 s, FP32R12 0.385 -> 0.360 s, FP16N links 0.408 -> 0.348 s)
-    if (fp == HISQ_FP32 && nrhs >= 4) {
-        const DslashShape l{VAR_LDS, 4, LDS_BAND * g.hx, 2};
-        if (dslash_shape_fits(l, g, fp))
-            return l;
-    }
-    // FP16N fields below 262144 sites: one rhs a thread (24^3x12, 3 rhs 20.3 ->
-    // 13.8 us, 16 rhs 55.9 -> 52; at 48^3x12 two are faster, 413 against 472).
-    const int cap = fp == HISQ_FP16N && g.vh < 262144 ? 1 : lp == HISQ_FP16N ? 2 : 4;
-    // FP64 columns of three as one group of four: 24^3x12 57 -> 42 us, 48^3x12
-    // 400 -> 306 (two groups of two read the links twice).
-    s.nin = nrhs >= cap || (fp == HISQ_FP64 && nrhs == 3) ? cap : 2;
-    // 16 rhs at 48^3x12, blocks of 64 -> 128: FP32 520 -> 476 us, FP32R12
-    // 467 -> 431 us, FP64 995 -> 935 us, FP16N 466 -> 457 us; 128 -> 256 with
-    // FP32 fields and FP32-family links: FP32 476-514 -> 473-483 us, FP32R12
-    // 430-465 -> 427-433 us over four boxes (FP64 mixed, 935-1001 -> 970-973);
-    // FP16N fields 452 -> 433 us
-    s.block = (fp == HISQ_FP32 && lp != HISQ_FP16N) || fp == HISQ_FP16N ? 256 : 128;
-    // FP32 links and fields, whole groups of 8: eight rhs per thread in blocks
-    // of 128 (16 rhs at 48^3x12: 476 -> 460 us; the 16-rhs CG 0.421 -> 0.407
-    // s; FP32R12 links gain nothing from it)
-    if (lp == HISQ_FP32 && fp == HISQ_FP32 && nrhs % 8 == 0) {
-        s.nin = 8;
-        s.block = 128;
-    }
-    // z-slab order in 8-row y-bands: 16 rhs at 48^3x12, FP32 606 -> 585 us,
-    // FP64 1231 -> 1105 us
-    if (g.nz % 8 == 0)
-        s.xcd_remap = 2;
-    return s;
+    if (staged)
+        return DslashShape{VAR_LDS, 4, LDS_BAND * g.hx, 2};
+    return fp == HISQ_FP64   ? large_multi_fp64(g, lp, nrhs)
+           : fp == HISQ_FP32 ? large_multi_fp32(g, lp, nrhs)
+                             : large_multi_fp16(g, nrhs);
 }
 
 std::vector<DslashShape> candidate_shapes(const Geom &g, int nrhs, int lp, int fp) {
@@ -168,8 +194,6 @@ std::vector<DslashShape> candidate_shapes(const Geom &g, int nrhs, int lp, int f
                 continue;
             if (var == VAR_HOP && nin > 2)
                 continue;
-            if (var == VAR_SITE && (lp == HISQ_FP64 || lp == HISQ_FP64R12 || lp == HISQ_FP64W14) && nin > 4)
-                continue;  // exceeds the register file (spills)
             for (int block : {64, 128, 256})
                 for (int remap : {0, 1, 2})
                     if (remap != 2 || g.nz % 8 == 0)

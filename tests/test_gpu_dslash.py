@@ -597,3 +597,36 @@ def test_built_in_multi_rhs_shapes(gpu_lib, prec, dims, nrhs):
     for r in sorted({0, nrhs // 2, nrhs - 1}):
         ref = lat_q.D_oe(w["src"][r] if f == "fp64" else O.quantize_field(w["src"][r], f))
         assert relerr(got[r], ref) <= {"fp64": 1e-13, "fp32": 1e-6, "fp16n": 2.0 ** -11}[f], (r, prec)
+
+
+@pytest.mark.parametrize("nrhs", [3, 4, 7, 10, 13, 16])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16n", "fp32w14"])
+def test_whole_and_partial_groups_of_columns(gpu_lib, prec, nrhs):
+    """Groups of 2, 4 and 8 columns a thread, whole, with places past the last
+    column (an odd and an even number of them) and with too many of those for
+    the whole-group kernel, one thread per site and staged in LDS, at the
+    corner sizes of both orders: plain and with the epilogue (M_e), bit for bit
+    the columns one by one (the same terms in the same order), the unused slot
+    of an odd last pair zero."""
+    h = gpu_lib
+    dims = (16, 8, 8, 4)
+    w = gen.workload_haar(dims, 59, -1, nrhs)
+    lat = h.lattice(dims, -1)
+    f = "fp16n" if prec == "fp16n" else prec[:4]
+    links = h.pack_links_from_host(lat, prec, w["fat"], w["naik"])
+    inp = h.pack_field_from_host(lat, f, w["src"])
+    ctx = h.Context(0)
+    tmp = h.empty_field(lat, f, nrhs)
+    refs = None
+    shapes = [(0, 1, 64, 1)] + [(v, n, b, 2) for v, b in ((0, 64), (0, 256), (2, 64)) for n in (2, 4, 8)
+                                if not (v == 2 and (f == "fp16n" or (f == "fp64" and n == 8)))]
+    for shape in shapes:
+        h.hisq_set_dslash_shape(lat, prec, nrhs, shape, ctx)
+        outs = []
+        for call in (lambda o: h.hisq_dslash(lat, prec, 1, links, inp, o, nrhs, ctx=ctx),
+                     lambda o: h.hisq_apply_m(lat, prec, 0.3, links, inp, o, tmp, nrhs, ctx=ctx)):
+            o = torch.zeros_like(inp)
+            call(o)
+            outs.append(o.clone())
+        refs = refs or outs
+        assert all(torch.equal(a, b) for a, b in zip(refs, outs)), shape

@@ -275,3 +275,30 @@ def test_multishift_refinement_columns_packed_or_not(gpu_lib, nshift):
             assert np.linalg.norm(got - sols[k]) <= bound
     with pytest.raises(h.HisqError):
         h.hisq_multishift_cg(lat, m, l64, lin, "fp32", shifts, b, xs, tol, 20000, ws[:least - 1])
+
+
+@pytest.mark.parametrize("shape", [(0, 2, 64, 2), (0, 4, 64, 2), (0, 8, 64, 2), (2, 2, 64, 2), (2, 4, 64, 2),
+                                   (2, 8, 64, 2)])
+@pytest.mark.parametrize("nshift", [7, 13, 14])
+def test_refinement_with_groups_of_columns(gpu_lib, nshift, shape):
+    """Every column of the refinement has its own shift, also in a last group
+    with places past the last column: groups of 2, 4 and 8, one thread per site
+    and staged in LDS.  Each shift meets its FP64 true residual by the oracle
+    within a few times the iterations of the built-in shape."""
+    h = gpu_lib
+    w = gen.workload_haar((16, 8, 8, 4), 59, -1)
+    m, tol = 0.3, 1e-10
+    shifts = [0.05 * k for k in range(nshift)]
+    st, ref, _, (lat, l64, lin, b, xs, ws) = run(h, w, "fp32", shifts, m, tol)
+    assert st == h.OK, ref
+    ctx = h.Context(0)
+    for prec in ("fp32", "fp64"):
+        if not (prec == "fp64" and shape[:2] == (2, 8)):
+            h.hisq_set_dslash_shape(lat, prec, nshift, shape, ctx)
+    st, info = h.hisq_multishift_cg(lat, m, l64, lin, "fp32", shifts, b, xs, tol, 20000, ws, ctx=ctx)
+    assert st == h.OK, info
+    lat_o = O.lattice_from(w)
+    for k, s in enumerate(shifts):
+        got = h.unpack_field_to_host(lat, "fp64", xs[k])[0]
+        assert O.true_residual(lat_o, m, w["src"][0], got, shift=s) <= tol
+        assert info[k]["refine_iterations"] <= 2 * ref[k]["refine_iterations"] + 8
