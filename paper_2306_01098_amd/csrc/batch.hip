@@ -1,8 +1,8 @@
 // Batched CG over many independent problems on lattices of different sizes.
 //
 // One launch covers the sites of every problem: a work list maps each block
-// to (problem, first site), so 64 small solves advance together with four
-// launches per iteration instead of 256, and the sequence is captured once in
+// to (problem, first site), so 64 small solves advance together with five
+// launches per iteration instead of 320, and the sequence is captured once in
 // a HIP graph.  Per-problem Krylov scalars live on the device; each reducing
 // kernel stores block partials and a finalize kernel (one wavefront per
 // problem) sums them in a fixed order and advances the scalars.
@@ -14,7 +14,7 @@ namespace hisq {
 
 namespace {
 
-enum { FIN_PQ = 0, FIN_XR, FIN_RESID, FIN_BNORM, FIN_RESTART };
+enum { FIN_XR = 0, FIN_RESID, FIN_BNORM, FIN_RESTART };
 constexpr int FIN_BLOCK = 256;  // four problems per finalize block
 
 template <int FP> struct SloppyT;
@@ -30,7 +30,7 @@ __device__ __forceinline__ bool participates(const BatchArgs &a, int j, int role
 
 // Dslash over all participating problems.
 //  ROLE_ITER_DOE: t = D_oe p             (sloppy links/fields)
-//  ROLE_ITER_DEO: q = m^2 p - D_eo t, Re<p, q> -> st[j].pq
+//  ROLE_ITER_DEO: q = m^2 p - D_eo t, block partials of Re<p, q>
 //  ROLE_TRUE_DOE: t64 = D_oe x           (FP64)
 //  ROLE_TRUE_DEO: ax = m^2 x - D_eo t64  (FP64)
 template <int LP, int FP, int ROLE, int TB>
@@ -45,9 +45,11 @@ __global__ void __launch_bounds__(TB) batch_dslash_kernel(BatchArgs a) {
     constexpr int parity = (ROLE == ROLE_ITER_DOE || ROLE == ROLE_TRUE_DOE) ? 1 : 0;
     const int blk = blockIdx.x;
     const int j = a.blk_prob[blk];
+    if (!participates(a, j, ROLE))
+        return;  // the whole block is problem j's
     const BatchProb &P = a.probs[j];
     const int i = (blk - P.first_blk) * TB + threadIdx.x;
-    const bool go = participates(a, j, ROLE) && i < P.g.vh;
+    const bool go = i < P.g.vh;
     double dot[1] = {0.0};
     if (go) {
         const char *links = ROLE <= ROLE_ITER_DEO ? P.links_in : P.links64;
@@ -80,7 +82,12 @@ __global__ void __launch_bounds__(TB) batch_dslash_kernel(BatchArgs a) {
         a.partials[blk] = dot[0];
 }
 
-// x += alpha p, r -= alpha q, and block partials of <r, r>.
+// x += alpha p, r -= alpha q, and block partials of <r, r>.  Every block sums
+// the problem's Re <p, q> partials itself, in one order, while its vectors are
+// on the way; a launch between the two that summed them took 4.7 us and a gap
+// of the 128 us an iteration of 24 uneven problems (153.2 -> 149.5 ms).  The <r, r>
+// partials go to t, which D_oe writes afresh: other blocks still read those of
+// Re <p, q>.
 template <int FP, int TB>
 __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
     using T = typename SloppyT<FP>::T;
@@ -91,17 +98,30 @@ __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
     const BatchProb &P = a.probs[j];
     const int i = (blk - P.first_blk) * TB + threadIdx.x;
     const CgScalars st = a.st[j];
-    const bool go = st.active && pos_finite(st.pq) && i < P.g.vh;
-    double part[1] = {0.0};
-    if (go) {
-        const double alpha = st.rho / st.pq;
-        const T al = (T)alpha;
-        cplx<T> p[3], q[3], r[3];
-        cplx<double> x[3];
+    if (!st.active)
+        return;  // the whole block is problem j's
+    const bool mine = i < P.g.vh;
+    cplx<T> p[3], q[3], r[3];
+    cplx<double> x[3];
+    if (mine) {
         FieldIO<FP>::template load<T>(P.p, P.g.vh, 1, 0, i, p);
         FieldIO<FP>::template load<T>(P.q, P.g.vh, 1, 0, i, q);
         FieldIO<FP>::template load<T>(P.r, P.g.vh, 1, 0, i, r);
         FieldIO<HISQ_FP64>::template load<double>(P.x, P.g.vh, 1, 0, i, x);
+    }
+    __shared__ double pq_s;
+    double pq = 0.0;
+    if (threadIdx.x < 64) {
+        pq = wave_sum_slot<false>(a.partials + P.first_blk, P.nblk);
+        if (threadIdx.x == 0)
+            pq_s = pq;
+    }
+    __syncthreads();
+    pq = pq_s;
+    double part[1] = {0.0};
+    if (mine && pos_finite(pq)) {
+        const double alpha = st.rho / pq;
+        const T al = (T)alpha;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             x[c].re = fma(alpha, (double)p[c].re, x[c].re);
@@ -117,13 +137,13 @@ __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
     __shared__ double lds[TB / 64];
     block_sum<1>(part, lds);
     if (threadIdx.x == 0)
-        a.partials[blk] = part[0];
+        static_cast<double *>(P.t)[blk - P.first_blk] = part[0];
 }
 
 // Finalize of the reducing batch kernels: one wavefront per problem sums the
 // problem's block partials (deterministic, see wave_sum_slot), then its lane 0
-//  FIN_PQ:    st[j].pq = total (active problems)
-//  FIN_XR:    advances the problem's scalars and raises its flags; a problem
+//  FIN_XR:    advances the problem's scalars from both sums of the iteration
+//             (<r, r> partials in t) and raises its flags; a problem
 //             that stops leaves the active count (and is stamped with the
 //             device clock, restamped below when its true residual confirms it)
 //  FIN_RESID: st[j].rho_new = total (masked problems)
@@ -135,7 +155,7 @@ __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
 //             recurrence (beta = ||r||^2 / rho, rho = rmax2 = ||r||^2; the
 //             problem rejoins the active count and is marked for p = r + beta p)
 __global__ void __launch_bounds__(FIN_BLOCK) batch_finalize_kernel(BatchArgs a, int mode, double *bnorm2) {
-    if ((mode == FIN_PQ || mode == FIN_XR) && *a.nactive == 0)
+    if (mode == FIN_XR && *a.nactive == 0)
         return;
     const int j = blockIdx.x * (FIN_BLOCK / 64) + (threadIdx.x >> 6);
     if (j >= a.nprob)  // uniform over the wavefront
@@ -174,7 +194,10 @@ __global__ void __launch_bounds__(FIN_BLOCK) batch_finalize_kernel(BatchArgs a, 
         return;
     }
     const BatchProb &P = a.probs[j];
-    const double tot = wave_sum_slot(a.partials + P.first_blk, P.nblk);
+    double tot = wave_sum_slot(a.partials + P.first_blk, P.nblk);
+    const double pq = tot;
+    if (mode == FIN_XR)
+        tot = wave_sum_slot(static_cast<const double *>(P.t), P.nblk);
     if ((threadIdx.x & 63) != 0)
         return;
     if (mode == FIN_BNORM) {
@@ -189,11 +212,8 @@ __global__ void __launch_bounds__(FIN_BLOCK) batch_finalize_kernel(BatchArgs a, 
     CgScalars s = a.st[j];
     if (!s.active)
         return;
-    if (mode == FIN_PQ) {
-        a.st[j].pq = tot;
-        return;
-    }
-    if (!pos_finite(s.pq)) {
+    s.pq = pq;
+    if (!pos_finite(pq)) {
         s.flag = FLAG_BREAKDOWN;
         s.active = 0;
     } else {
@@ -376,8 +396,7 @@ hipError_t launch_batch(const BatchArgs &a, int nblocks, int op, int lp, hipStre
                                     : hipErrorInvalidValue;
     if (e != hipSuccess)
         return e;
-    const int fin = op == BOP_ITER_DEO ? FIN_PQ : op == BOP_XR ? FIN_XR
-                    : (op == BOP_RESIDUAL || op == BOP_RESIDUAL_COPY_P) ? FIN_RESID : -1;
+    const int fin = op == BOP_XR ? FIN_XR : (op == BOP_RESIDUAL || op == BOP_RESIDUAL_COPY_P) ? FIN_RESID : -1;
     if (fin < 0)
         return hipSuccess;
     batch_finalize_kernel<<<(a.nprob + 3) / 4, FIN_BLOCK, 0, st>>>(a, fin, nullptr);
