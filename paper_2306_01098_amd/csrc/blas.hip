@@ -177,60 +177,7 @@ __global__ void __launch_bounds__(1024) cg_finalize_kernel(CgVecParams prm, int 
     *prm.skip = any ? 0 : 1;
 }
 
-// The true-residual check of the columns that raised FLAG_CONV or
-// FLAG_RELIABLE (tr_skip[j] == 0), after r_j = b_j - A x_j and the block
-// partials of ||r_j||^2 (nblk per column in trpart) were formed: the FP64
-// norm decides DONE (target met), MAXIT, or a residual replacement, which
-// restarts the recurrence with beta = ||r||^2 / rho, rho = rmax2 = ||r||^2
-// (p = r + beta p follows in cg_p_kernel's restart mode).  One block.
-__global__ void __launch_bounds__(1024) cg_restart_kernel(CgVecParams prm, const double *trpart, int nblk) {
-    __shared__ double tot[HISQ_MAX_RHS];
-    for (int j = threadIdx.x >> 6; j < prm.nrhs; j += blockDim.x >> 6)
-        if (prm.tr_skip[j] == 0) {
-            const double v = wave_sum_slot<true>(trpart + (size_t)j * nblk, nblk);
-            if ((threadIdx.x & 63) == 0)
-                tot[j] = v;
-        }
-    __syncthreads();
-    if (threadIdx.x != 0)
-        return;
-    int any = 0;
-    for (int j = 0; j < prm.nrhs; ++j) {
-        CgScalars s = prm.st[j];
-        s.restart = 0;
-        if (prm.tr_skip[j] == 0) {
-            const double r2 = tot[j];
-            prm.tr_skip[j] = 1;
-            s.rtrue2 = r2;
-            if (!(r2 >= 0.0 && r2 < 1.0e308)) {
-                s.flag = FLAG_BREAKDOWN;
-                s.active = 0;
-            } else if (r2 <= s.target2) {
-                s.flag = FLAG_DONE;
-                s.active = 0;
-            } else if (s.iters >= s.max_iter) {
-                s.flag = FLAG_MAXIT;
-                s.active = 0;
-            } else {
-                s.nrel += 1;
-                s.beta = r2 / s.rho;
-                s.rho = r2;
-                s.rmax2 = r2;
-                s.flag = FLAG_RUN;
-                s.active = 1;
-                s.restart = 1;
-            }
-        }
-        prm.st[j] = s;
-        any |= s.active;
-    }
-    *prm.skip = any ? 0 : 1;
-    if (prm.nopend)
-        *prm.nopend = 1;
-}
-
-// p = r + beta p for right-hand side rhs0 + blockIdx.y (if active; in restart
-// mode only for a column just restarted by cg_restart_kernel).  Multi-shift
+// p = r + beta p for right-hand side rhs0 + blockIdx.y (if active).  Multi-shift
 // (one right-hand side): block rows 1 .. nshift take the shifts,
 // x_k += alpha_k p_k and p_k = zeta_k r + beta_k p_k, so that p_k is read once
 // and every shift has wavefronts of its own (a loop over the shifts in one
@@ -238,7 +185,7 @@ __global__ void __launch_bounds__(1024) cg_restart_kernel(CgVecParams prm, const
 // cg_xr_kernel 23 and this kernel 13).  A shift frozen by this iteration still
 // takes its x_k; the base system may have stopped in it.
 template <int FP>
-__global__ void __launch_bounds__(BLK) cg_p_kernel(CgVecParams prm, int rhs0, int restart_only) {
+__global__ void __launch_bounds__(BLK) cg_p_kernel(CgVecParams prm, int rhs0) {
     using T = typename Sloppy<FP>::T;
     const int i = blockIdx.x * BLK + threadIdx.x;
     if (prm.nshift > 0 && blockIdx.y > 0) {
@@ -268,7 +215,7 @@ __global__ void __launch_bounds__(BLK) cg_p_kernel(CgVecParams prm, int rhs0, in
         return;
     const int rr = rhs0 + blockIdx.y;
     const CgScalars st = prm.st[rr];
-    if (!(restart_only ? st.restart : st.active) || i >= prm.vh)
+    if (!st.active || i >= prm.vh)
         return;
     cplx<T> p[3], r[3];
     FieldIO<FP>::template load<T>(prm.p, prm.vh, prm.nrhs, rr, i, p);
@@ -880,18 +827,12 @@ hipError_t launch_cg_xr(const CgVecParams &p, int fp, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStream_t st, bool restart_only) {
-    const int mode = restart_only ? 1 : 0;
+hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStream_t st) {
     const dim3 g = grid_for(p.vh, nrhs + p.nshift);
     if (fp == HISQ_FP64)
-        cg_p_kernel<HISQ_FP64><<<g, BLK, 0, st>>>(p, rhs0, mode);
+        cg_p_kernel<HISQ_FP64><<<g, BLK, 0, st>>>(p, rhs0);
     else
-        cg_p_kernel<HISQ_FP32><<<g, BLK, 0, st>>>(p, rhs0, mode);
-    return hipGetLastError();
-}
-
-hipError_t launch_cg_restart(const CgVecParams &p, const double *trpart, hipStream_t st) {
-    cg_restart_kernel<<<1, 1024, 0, st>>>(p, trpart, blas_blocks(p.vh));
+        cg_p_kernel<HISQ_FP32><<<g, BLK, 0, st>>>(p, rhs0);
     return hipGetLastError();
 }
 

@@ -50,10 +50,7 @@ int blas_blocks(int vh);
 int cg_vec_block(int vh);
 int cg_vec_blocks(int vh);
 hipError_t launch_cg_xr(const CgVecParams &p, int fp, hipStream_t st);
-hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStream_t st, bool restart_only = false);
-// The true-residual check after r = b - A x of the waiting columns (partials
-// in trpart, blas_blocks(vh) per column).
-hipError_t launch_cg_restart(const CgVecParams &p, const double *trpart, hipStream_t st);
+hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStream_t st);
 // Single-reduction CG: the per-column scalar step (after_check: decide the
 // columns whose FP64 true residual the check block just formed) and the
 // fused vector update with the <r, r> partials of the new residual.
