@@ -169,6 +169,11 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
     // solver's test of the staged kernels runs there.
     const bool staged = fp == HISQ_FP32 && nrhs >= 4 && g.vh <= 4096 &&
                         dslash_shape_fits(DslashShape{VAR_LDS, 4, LDS_BAND * g.hx, 2}, g, fp);
+    // three FP32 columns: two a thread from 40960 sites (one / two: FP32 links
+    // 16x8x32x22 16.8 / 14.1 us, FP32R12 10x18x20x26 14.0 / 12.2, 16^3x22 13.8 /
+    // 12.4, at 14^2x18x20 11.0 / 11.5)
+    if (fp == HISQ_FP32 && nrhs == 3 && g.vh >= 40960 && g.vh < 49152)
+        return DslashShape{VAR_SITE, 2, 128, g.nz % 8 == 0 ? 2 : 1};
     if (!staged && g.vh < (fp == HISQ_FP64 ? 32768 : 49152))
         return small_multi_shape(g, fp, nrhs);
     if (staged)
