@@ -2,8 +2,8 @@
 //
 // One launch covers the sites of every problem: a work list maps each block
 // to (problem, first site), so 64 small solves advance together with five
-// launches per iteration instead of 320, and the sequence is captured once in
-// a HIP graph.  Per-problem Krylov scalars live on the device; each reducing
+// launches per iteration (six with a large problem among them) instead of 320,
+// and the sequence is captured once in a HIP graph.  Per-problem Krylov scalars live on the device; each reducing
 // kernel stores block partials and a finalize kernel (one wavefront per
 // problem) sums them in a fixed order and advances the scalars.
 #include "batch.hpp"
@@ -14,7 +14,7 @@ namespace hisq {
 
 namespace {
 
-enum { FIN_XR = 0, FIN_RESID, FIN_BNORM, FIN_RESTART };
+enum { FIN_PQ = 0, FIN_XR, FIN_RESID, FIN_BNORM, FIN_RESTART };
 constexpr int FIN_BLOCK = 256;  // four problems per finalize block
 
 template <int FP> struct SloppyT;
@@ -82,12 +82,11 @@ __global__ void __launch_bounds__(TB) batch_dslash_kernel(BatchArgs a) {
         a.partials[blk] = dot[0];
 }
 
-// x += alpha p, r -= alpha q, and block partials of <r, r>.  Every block sums
-// the problem's Re <p, q> partials itself, in one order, while its vectors are
-// on the way; a launch between the two that summed them took 4.7 us and a gap
-// of the 128 us an iteration of 24 uneven problems (153.2 -> 149.5 ms).  The <r, r>
-// partials go to t, which D_oe writes afresh: other blocks still read those of
-// Re <p, q>.
+// x += alpha p, r -= alpha q, and block partials of <r, r>.  Re <p, q> was
+// summed by FIN_PQ (a.sum_pq), or every block sums the problem's partials
+// itself, in the same order, while its vectors are on the way (batch.hpp on
+// which of the two).  The <r, r> partials go to t, which D_oe writes afresh:
+// other blocks still read those of Re <p, q>.
 template <int FP, int TB>
 __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
     using T = typename SloppyT<FP>::T;
@@ -110,14 +109,16 @@ __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
         FieldIO<HISQ_FP64>::template load<double>(P.x, P.g.vh, 1, 0, i, x);
     }
     __shared__ double pq_s;
-    double pq = 0.0;
-    if (threadIdx.x < 64) {
-        pq = wave_sum_slot<false>(a.partials + P.first_blk, P.nblk);
-        if (threadIdx.x == 0)
-            pq_s = pq;
+    double pq = st.pq;
+    if (!a.sum_pq) {
+        if (threadIdx.x < 64) {
+            pq = wave_sum_slot<false>(a.partials + P.first_blk, P.nblk);
+            if (threadIdx.x == 0)
+                pq_s = pq;
+        }
+        __syncthreads();
+        pq = pq_s;
     }
-    __syncthreads();
-    pq = pq_s;
     double part[1] = {0.0};
     if (mine && pos_finite(pq)) {
         const double alpha = st.rho / pq;
@@ -142,6 +143,7 @@ __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
 
 // Finalize of the reducing batch kernels: one wavefront per problem sums the
 // problem's block partials (deterministic, see wave_sum_slot), then its lane 0
+//  FIN_PQ:    st[j].pq = total (active problems; launched with a.sum_pq only)
 //  FIN_XR:    advances the problem's scalars from both sums of the iteration
 //             (<r, r> partials in t) and raises its flags; a problem
 //             that stops leaves the active count (and is stamped with the
@@ -155,7 +157,7 @@ __global__ void __launch_bounds__(TB) batch_xr_kernel(BatchArgs a) {
 //             recurrence (beta = ||r||^2 / rho, rho = rmax2 = ||r||^2; the
 //             problem rejoins the active count and is marked for p = r + beta p)
 __global__ void __launch_bounds__(FIN_BLOCK) batch_finalize_kernel(BatchArgs a, int mode, double *bnorm2) {
-    if (mode == FIN_XR && *a.nactive == 0)
+    if (mode <= FIN_XR && *a.nactive == 0)
         return;
     const int j = blockIdx.x * (FIN_BLOCK / 64) + (threadIdx.x >> 6);
     if (j >= a.nprob)  // uniform over the wavefront
@@ -194,10 +196,13 @@ __global__ void __launch_bounds__(FIN_BLOCK) batch_finalize_kernel(BatchArgs a, 
         return;
     }
     const BatchProb &P = a.probs[j];
-    double tot = wave_sum_slot(a.partials + P.first_blk, P.nblk);
-    const double pq = tot;
-    if (mode == FIN_XR)
+    double tot = 0.0, pq = 0.0;
+    if (mode != FIN_XR || !a.sum_pq)
+        tot = wave_sum_slot(a.partials + P.first_blk, P.nblk);
+    if (mode == FIN_XR) {
+        pq = a.sum_pq ? a.st[j].pq : tot;
         tot = wave_sum_slot(static_cast<const double *>(P.t), P.nblk);
+    }
     if ((threadIdx.x & 63) != 0)
         return;
     if (mode == FIN_BNORM) {
@@ -212,6 +217,10 @@ __global__ void __launch_bounds__(FIN_BLOCK) batch_finalize_kernel(BatchArgs a, 
     CgScalars s = a.st[j];
     if (!s.active)
         return;
+    if (mode == FIN_PQ) {
+        a.st[j].pq = tot;
+        return;
+    }
     s.pq = pq;
     if (!pos_finite(pq)) {
         s.flag = FLAG_BREAKDOWN;
@@ -396,7 +405,8 @@ hipError_t launch_batch(const BatchArgs &a, int nblocks, int op, int lp, hipStre
                                     : hipErrorInvalidValue;
     if (e != hipSuccess)
         return e;
-    const int fin = op == BOP_XR ? FIN_XR : (op == BOP_RESIDUAL || op == BOP_RESIDUAL_COPY_P) ? FIN_RESID : -1;
+    const int fin = op == BOP_ITER_DEO && a.sum_pq ? FIN_PQ : op == BOP_XR ? FIN_XR
+                    : (op == BOP_RESIDUAL || op == BOP_RESIDUAL_COPY_P) ? FIN_RESID : -1;
     if (fin < 0)
         return hipSuccess;
     batch_finalize_kernel<<<(a.nprob + 3) / 4, FIN_BLOCK, 0, st>>>(a, fin, nullptr);

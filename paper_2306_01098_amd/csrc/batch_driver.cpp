@@ -165,11 +165,13 @@ hisq_status hisq_cg_batch(hisq_context *ctx, int32_t nproblems, const hisq_probl
         B.ax = W + L.ax[j];
         B.t64 = W + L.t64[j];
     }
+    BatchArgs a{};
     // work list for `bb` sites per block: problem j owns blocks
     // [first_blk, first_blk + nblk); returns the number of blocks.  With
     // `keep`, problems outside it get no blocks (nblk = 0).
     auto assign = [&](int bb, const std::vector<char> *keep = nullptr) -> int {
         int total = 0;
+        a.sum_pq = 0;
         for (int j = 0; j < n; ++j) {
             const int nb = (keep && !(*keep)[j]) ? 0 : (probs[j].g.vh + bb - 1) / bb;
             probs[j].first_blk = total;
@@ -177,10 +179,10 @@ hisq_status hisq_cg_batch(hisq_context *ctx, int32_t nproblems, const hisq_probl
             for (int b = 0; b < nb; ++b)
                 blk[total + b] = j;
             total += nb;
+            a.sum_pq |= nb > BATCH_PQ_BLOCKS;
         }
         return total;
     };
-    BatchArgs a{};
     a.probs = reinterpret_cast<const BatchProb *>(W + L.probs);
     a.nprob = n;
     a.blk_prob = reinterpret_cast<const int *>(W + L.blk);

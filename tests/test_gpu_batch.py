@@ -133,3 +133,46 @@ def test_batch_compaction_and_iteration_limit(gpu_lib):
             assert r > 1e-10 and abs(r - info[0]["true_residual"]) <= 1e-9 * r, (r, info[0])
         else:
             assert r <= 1e-10 and info[k]["iterations"] < 100, (k, r, info[k])
+
+
+@pytest.mark.parametrize("inner", ["fp32", "fp64"])
+def test_batch_with_a_problem_of_thousands_of_blocks(gpu_lib, inner):
+    """Above 3072 blocks of a problem (here 3456 of the largest tile, 256 sites)
+    Re <p, q> is summed by a launch of its own, for the small problems of the
+    list too; once the large one has finished, the small one goes on without
+    it.  The small solution by the oracle, the large one by the FP64 operator."""
+    h = gpu_lib
+    dims, m, tol = (48, 48, 48, 16), 3.0, 1e-10
+    lat = h.lattice(dims, -1)
+    g = torch.Generator(device="cuda").manual_seed(11)
+
+    def normal(*shape):
+        return torch.view_as_complex(torch.randn(*shape, 2, dtype=torch.float64, device="cuda", generator=g))
+
+    fat, naik = (c * (torch.eye(3, dtype=torch.complex128, device="cuda") + 0.2 * normal(4, *dims[::-1], 3, 3))
+                 for c in (0.5, 0.05))
+    links = {}
+    for prec in {"fp64", inner}:
+        links[prec] = h.empty_links(lat, prec)
+        h.hisq_pack_links(lat, prec, fat, naik, links[prec])
+    del fat, naik
+    vol = 48 * 48 * 48 * 16
+    src = normal(1, vol // 2, 3)
+    b, x, ax, tmp = (h.empty_field(lat, "fp64") for _ in range(4))
+    h.hisq_pack_field(lat, "fp64", 1, src, b)
+    x.zero_()
+    w = gen.workload_haar((6, 4, 4, 8), 820, -1)
+    w["mass"] = 0.2
+    items, _, _, keep = build(h, [w], inner, tol)
+    items.append(dict(lat=lat, mass=m, links_f64=links["fp64"], links_inner=links[inner] if inner != "fp64" else None,
+                      b=b, x=x, tol=tol))
+    probs = h.make_problems(items)
+    ws = h.empty_workspace(h.hisq_cg_batch_workspace_bytes(probs, inner))
+    st, info, lat_s = h.hisq_cg_batch(probs, inner, 5000, ws)
+    assert st == h.OK, info
+    assert info[1]["iterations"] < info[0]["iterations"]
+    h.hisq_apply_m(lat, "fp64", m, links["fp64"], x, ax, tmp)
+    r = b.view(torch.float64) - ax.view(torch.float64)
+    assert float(r.norm() / b.view(torch.float64).norm()) <= tol
+    xs = h.unpack_field_to_host(items[0]["lat"], "fp64", items[0]["x"])[0]
+    assert O.true_residual(O.lattice_from(w), 0.2, w["src"][0], xs) <= tol
