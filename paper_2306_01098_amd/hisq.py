@@ -224,19 +224,20 @@ def _ctx(ctx):
 # ---------------------------------------------------------------------------
 
 # Answers of the size queries, by value: (lattice bytes, precision, columns or
-# -1 for links).  Emptied when a program asks for very many.
+# None for links).  Refusals are not kept, so each one leaves its message in
+# hisq_last_error.  Emptied when a program asks for very many.
 _sizes: dict = {}
 
 
-def _size(lat, prec, nrhs):
+def _size(lat, prec: int, nrhs):
     key = (bytes(lat), prec, nrhs)
     n = _sizes.get(key)
     if n is None:
         if len(_sizes) >= 4096:
             _sizes.clear()
         lib = load()
-        n = int(lib.hisq_links_bytes(ctypes.byref(lat), _prec(prec)) if nrhs < 0
-                else lib.hisq_field_bytes(ctypes.byref(lat), _prec(prec), nrhs))
+        n = int(lib.hisq_links_bytes(ctypes.byref(lat), prec) if nrhs is None
+                else lib.hisq_field_bytes(ctypes.byref(lat), prec, nrhs))
         if n == 0:
             return 0  # refused
         _sizes[key] = n
@@ -244,12 +245,11 @@ def _size(lat, prec, nrhs):
 
 
 def hisq_links_bytes(lat: hisq_lattice, prec) -> int:
-    return _size(lat, prec, -1)
+    return _size(lat, _prec(prec), None)
 
 
 def hisq_field_bytes(lat: hisq_lattice, prec, nrhs: int = 1) -> int:
-    nrhs = int(nrhs)
-    return _size(lat, prec, nrhs) if nrhs >= 0 else 0
+    return _size(lat, _prec(prec), int(nrhs))
 
 
 def empty_links(lat, prec, device="cuda") -> torch.Tensor:

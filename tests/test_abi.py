@@ -226,3 +226,26 @@ def test_largest_volume_is_enforced(lib):
     assert h.hisq_field_bytes(ok, "fp64", 1) == (1 << 29) * 48
     assert h.hisq_links_bytes(big, "fp64") == 0
     assert h.hisq_field_bytes(big, "fp32", 1) == 0
+
+
+def test_size_queries_go_by_value(lib):
+    """The binding keeps the answers of the size queries by the values that
+    were asked for: a precision given as a 0-d array or tensor is its value at
+    the call, and every refusal leaves its own message, a negative number of
+    columns too."""
+    import numpy as np
+    import torch
+
+    from paper_2306_01098_amd import hisq as h
+    lat = h.lattice((4, 4, 4, 6), -1)
+    f64, f32 = (h.hisq_field_bytes(lat, p, 3) for p in ("fp64", "fp32"))
+    assert h.hisq_field_bytes(lat, np.array(h.PRECS["fp64"]), np.array(3)) == f64
+    p = torch.tensor(h.PRECS["fp64"])
+    assert h.hisq_field_bytes(lat, p, 3) == f64
+    p.fill_(h.PRECS["fp32"])
+    assert h.hisq_field_bytes(lat, p, 3) == f32
+    for nrhs in (-1, 0, 17, -1):
+        assert h.hisq_links_bytes(h.lattice((4, 4, 4, 5), -1), "fp64") == 0
+        other = lib.hisq_last_error()
+        assert h.hisq_field_bytes(lat, "fp64", nrhs) == 0
+        assert lib.hisq_last_error() != other and str(nrhs).encode() in lib.hisq_last_error()
