@@ -12,7 +12,9 @@
 //                     + w3[d][p'] w2[d][c][p] w1[c][0] ).
 // The folding (FP64, from the FP32 weights, once per call) replaces the layers
 // 1 -> 8 -> 8 -> 1: a site takes 192 complex multiply-adds instead of about
-// 2000, and no 8-channel activation is written.  The gradient with respect to
+// 2000, and no 8-channel activation is written.  C and c0 stay FP64 and are
+// applied in FP64: a product of three weights may lie outside the range of FP32
+// where every activation of the layers lies inside.  The gradient with respect to
 // C and c0 is one 8 x 8 correlation over the odd sites,
 //   K[p'][p] = sum_y <(T_p in)(y), (T_p'^+ g)(y)>,   K0 = sum_x <in(x), g(x)>,
 // and the gradients of the 720 weights follow from it by the chain rule.
@@ -113,11 +115,9 @@ __device__ __forceinline__ double2 w3_(const float2 *w, int d, int p) { return w
 
 // The folded map: fold[8 p' + p] = C[p'][p] and fold[64] = c0; the adjoint
 // network in the same form, C'[p'][p] = conj(C[p ^ 1][p' ^ 1]), at fold + 65.
-// c0 and its conjugate also as doubles at fold + 130 and + 132: the rounding of
-// c0 to FP32 would be the same relative error on every site.
 // Eight lanes (the channel d) per entry.  keep (nullable): a copy of the
 // weights.
-__global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, float2 *fold, float2 *keep,
+__global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, double2 *fold, float2 *keep,
                                                    const int *skip) {
     if (skip && *skip)
         return;
@@ -151,15 +151,8 @@ __global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, float2
     }
     if (d != 0 || e > 64)
         return;
-    const float2 r = make_float2((float)sum.x, (float)sum.y), rc = make_float2((float)sum.x, (float)-sum.y);
-    fold[e] = r;
-    fold[65 + (e < 64 ? 8 * ((e & 7) ^ 1) + ((e >> 3) ^ 1) : 64)] = rc;
-    if (e == 64) {
-        double *c0 = reinterpret_cast<double *>(fold + 130);
-        c0[0] = c0[2] = sum.x;
-        c0[1] = sum.y;
-        c0[3] = -sum.y;
-    }
+    fold[e] = sum;
+    fold[65 + (e < 64 ? 8 * ((e & 7) ^ 1) + ((e >> 3) ^ 1) : 64)] = make_double2(sum.x, -sum.y);
 }
 
 // Two wavefronts work on 64 odd sites, one with the hops in x and y and one
@@ -207,14 +200,17 @@ __device__ __forceinline__ void swap_halves(cplx<float> (&t)[NHOP][3], HalfLds &
 // t_p = T_p in, for every hop p' the combination u_p', and s_p' = T_p' u_p'
 // delivered to the even site that reads it, through the link that t of the
 // adjoint hop was formed with.  The links stay in registers, so each link of
-// the lattice is read once.  Columns col0 + nper blockIdx.y ... of the
+// the lattice is read once.  C t is summed in FP64, one p at a time with t_p
+// from LDS: with the eight vectors in registers the kernel takes 228 VGPRs and
+// two wavefronts run on a SIMD instead of three (forward at 32^4 125 us; 118 so
+// and 118 with C in FP32).  Columns col0 + nper blockIdx.y ... of the
 // ncol-column field `in`, nper of them in a thread, each to s + column * 24 vh.
-__global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, const float2 *fold, const void *in,
+__global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, const double2 *fold, const void *in,
                                                     int ncol, int col0, int nper, int ncols, float2 *s,
                                                     const int *skip) {
     if (skip && *skip)
         return;
-    __shared__ HalfLds lds;
+    __shared__ float2 lds[PB / 64][12][64];  // t_p of a site: four of its one wavefront, four of the other
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
     const int i = site_block() * CS + (wave >> 1) * 64 + (threadIdx.x & 63);
     const bool valid = i < g.vh;
@@ -228,7 +224,7 @@ __global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, c
     }
     const int j1 = min((int)(blockIdx.y + 1) * nper, ncols);
     for (int j = blockIdx.y * nper; j < j1; ++j) {
-        cplx<float> t[NHOP][3];
+        cplx<float> t[4][3];
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
             cplx<float> v[3];
@@ -238,24 +234,47 @@ __global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, c
             else
                 transport<false>(m[l], v, t[l]);
         }
-        swap_halves(t, lds);
+        __syncthreads();  // the reads of the previous column are done
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                lds[wave][3 * l + a][threadIdx.x & 63] = make_float2(t[l][a].re, t[l][a].im);
+        __syncthreads();
         if (!valid)
             continue;
         float2 *sj = s + (size_t)j * 24 * g.vh;
+        cplx<double> acc[4][3];  // u of the four hops p' that go over this thread's links
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                acc[l][a].re = acc[l][a].im = 0.0;
+#pragma unroll 1
+        for (int p = 0; p < NHOP; ++p) {
+            cplx<double> v[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float2 e = lds[(wave & ~1) + (p >> 2)][3 * (p & 3) + a][threadIdx.x & 63];
+                v[a].re = e.x;
+                v[a].im = e.y;
+            }
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                const double2 c = fold[8 * (4 * half + (l ^ 1)) + p];
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    cmac(acc[l][a], c.x, c.y, v[a]);
+            }
+        }
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
             const int po = 4 * half + (l ^ 1);  // the hop p' whose vector goes over this link
-            const float2 *own = fold + 8 * po + 4 * half, *oth = fold + 8 * po + 4 * (half ^ 1);
             cplx<float> u[3], r[3];
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-                u[a].re = u[a].im = 0.f;
-#pragma unroll
-            for (int p = 0; p < NHOP; ++p) {
-                const float2 c = p < 4 ? own[p] : oth[p - 4];
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    cmac(u[a], c.x, c.y, t[p][a]);
+            for (int a = 0; a < 3; ++a) {
+                u[a].re = (float)acc[l][a].re;
+                u[a].im = (float)acc[l][a].im;
             }
             if (l & 1)
                 transport<false>(m[l], u, r);
@@ -270,12 +289,12 @@ __global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, c
 }
 
 // c0 in + sum_p s_p of one element (FP64: the kernels wait for memory)
-__device__ __forceinline__ double2 gathered(const double *c0, float2 in, const float2 *s, size_t stride) {
+__device__ __forceinline__ double2 gathered(const double2 *c0, float2 in, const float2 *s, size_t stride) {
     float2 v[NHOP];
 #pragma unroll
     for (int p = 0; p < NHOP; ++p)
         v[p] = s[p * stride];
-    double2 r = dmul(make_double2(c0[0], c0[1]), wide(in));
+    double2 r = dmul(*c0, wide(in));
 #pragma unroll
     for (int p = 0; p < NHOP; ++p) {
         r.x += v[p].x;
@@ -287,7 +306,7 @@ __device__ __forceinline__ double2 gathered(const double *c0, float2 in, const f
 // Second half: out = c0 in + sum_p' s_p' on the even sites, one thread per
 // element of the one-column fields (in may be out).  keep (nullable): a copy
 // of the input.
-__global__ void __launch_bounds__(PB) gather_kernel(int n, const double *c0, const float2 *in, const float2 *s,
+__global__ void __launch_bounds__(PB) gather_kernel(int n, const double2 *c0, const float2 *in, const float2 *s,
                                                     float2 *out, float2 *keep, const int *skip) {
     if (skip && *skip)
         return;
@@ -304,7 +323,7 @@ __global__ void __launch_bounds__(PB) gather_kernel(int n, const double *c0, con
 // Second half in training, for column blockIdx.y of a chunk: e = N(b) - x
 // (column blockIdx.y of an ne-column field) and the block partials of
 // Re <x, b>, b column col0 + blockIdx.y of the ncol-column sources, x FP64.
-__global__ void __launch_bounds__(PB) error_kernel(int vh, const double *c0, const void *b32, int ncol, int col0,
+__global__ void __launch_bounds__(PB) error_kernel(int vh, const double2 *c0, const void *b32, int ncol, int col0,
                                                    const float2 *s, const void *x64, void *e, int ne,
                                                    double *partials) {
     __shared__ double lds[PB / 64];
@@ -602,7 +621,7 @@ int ptc_correlate_blocks(const Geom &g) { return std::min((g.vh + CS - 1) / CS, 
 
 int ptc_error_blocks(const Geom &g) { return (int)nb(g.vh); }
 
-hipError_t ptc_fold(const float2 *w, float2 *fold, float2 *keep, hipStream_t st, const int *skip) {
+hipError_t ptc_fold(const float2 *w, double2 *fold, float2 *keep, hipStream_t st, const int *skip) {
     fold_kernel<<<1, 576, 0, st>>>(w, fold, keep, skip);
     return hipGetLastError();
 }
@@ -612,7 +631,7 @@ hipError_t ptc_fold(const float2 *w, float2 *fold, float2 *keep, hipStream_t st,
 // they are blocks of their own.  Training step of four pairs, blocks of their
 // own -> one after another: 24^3x16 300 -> 278 us, 32^4 1192 -> 1058 us, 16^4
 // 153 -> 156 us, 8^4 122 -> 128 us.
-hipError_t ptc_spread(const Geom &g, const char *links, const float2 *fold, const void *in, int ncol, int col0,
+hipError_t ptc_spread(const Geom &g, const char *links, const double2 *fold, const void *in, int ncol, int col0,
                       int ncols, float2 *s, hipStream_t st, const int *skip) {
     const int nper = g.vh >= 65536 ? ncols : 1;
     spread_kernel<<<dim3((unsigned)((g.vh + CS - 1) / CS), (unsigned)((ncols + nper - 1) / nper)), PB, 0, st>>>(g, links, fold, in, ncol, col0,
@@ -620,7 +639,7 @@ hipError_t ptc_spread(const Geom &g, const char *links, const float2 *fold, cons
     return hipGetLastError();
 }
 
-hipError_t ptc_gather(const Geom &g, const double *c0, const void *in, const float2 *s, void *out, void *keep,
+hipError_t ptc_gather(const Geom &g, const double2 *c0, const void *in, const float2 *s, void *out, void *keep,
                       hipStream_t st, const int *skip) {
     const int n = 3 * g.vh;
     gather_kernel<<<nb(n), PB, 0, st>>>(n, c0, static_cast<const float2 *>(in), s, static_cast<float2 *>(out),
@@ -628,7 +647,7 @@ hipError_t ptc_gather(const Geom &g, const double *c0, const void *in, const flo
     return hipGetLastError();
 }
 
-hipError_t ptc_error(const Geom &g, const double *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
+hipError_t ptc_error(const Geom &g, const double2 *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
                      const void *x64, void *e, double *partials, hipStream_t st) {
     error_kernel<<<dim3(nb(g.vh), (unsigned)ncols), PB, 0, st>>>(g.vh, c0, b32, ncol, col0, s, x64, e, ncols, partials);
     return hipGetLastError();

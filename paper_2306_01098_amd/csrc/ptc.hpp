@@ -23,22 +23,22 @@ constexpr int PTC_BLOCK = 256;
 // i.e. the packed FP32 half-field layout with right-hand-side index 2c + parity.
 inline size_t ptc_field_bytes(const Geom &g, int channels) { return (size_t)channels * 2 * 3 * g.vh * 8; }
 
-// The folded network (ptc.hip): 65 float2 of the map, 65 of its adjoint, and
-// both c0 as doubles; the gradient with respect to it: 64 complex correlations
-// and K0 as doubles.
-constexpr int PTC_NFOLD = 134;
-constexpr int PTC_C0 = 130;  // float2 index of c0 as two doubles, the adjoint's two further on
+// The folded network (ptc.hip): 65 double2 of the map, 65 of its adjoint; the
+// gradient with respect to it: 64 complex correlations and K0 as doubles.
+constexpr int PTC_NFOLD = 130;
+constexpr int PTC_ADJOINT = 65;  // where the adjoint network starts
+constexpr int PTC_C0 = 64;       // c0 in each of the two
 constexpr int PTC_NK = 130;
 constexpr int PTC_COLS = 4;  // training pairs per launch
 
 // skip (nullable): the launch does nothing while *skip != 0.
-hipError_t ptc_fold(const float2 *w, float2 *fold, float2 *keep, hipStream_t st, const int *skip = nullptr);
+hipError_t ptc_fold(const float2 *w, double2 *fold, float2 *keep, hipStream_t st, const int *skip = nullptr);
 // Columns col0 .. col0 + ncols - 1 of an ncol-column field; s: 24 vh float2 a column.
-hipError_t ptc_spread(const Geom &g, const char *links, const float2 *fold, const void *in, int ncol, int col0,
+hipError_t ptc_spread(const Geom &g, const char *links, const double2 *fold, const void *in, int ncol, int col0,
                       int ncols, float2 *s, hipStream_t st, const int *skip = nullptr);
-hipError_t ptc_gather(const Geom &g, const double *c0, const void *in, const float2 *s, void *out, void *keep,
+hipError_t ptc_gather(const Geom &g, const double2 *c0, const void *in, const float2 *s, void *out, void *keep,
                       hipStream_t st, const int *skip = nullptr);
-hipError_t ptc_error(const Geom &g, const double *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
+hipError_t ptc_error(const Geom &g, const double2 *c0, const void *b32, int ncol, int col0, int ncols, const float2 *s,
                      const void *x64, void *e, double *partials, hipStream_t st);
 // Column cin + k of `in` with column k of the ncols-column field gr.
 hipError_t ptc_correlate(const Geom &g, const char *links, const void *in, int nin, int cin, const void *gr, int ncols,

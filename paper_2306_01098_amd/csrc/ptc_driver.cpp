@@ -40,7 +40,7 @@ PtcLayout ptc_layout(const Geom &g) {
     L.t = a256(L.e + PTC_COLS * h32);
     L.ae = a256(L.t + PTC_COLS * h32);
     L.fold = take(f8);  // at least 48 KiB
-    L.keep = L.fold + a256(sizeof(float2) * PTC_NFOLD);
+    L.keep = L.fold + a256(sizeof(double2) * PTC_NFOLD);
     L.keep0 = L.keep + a256(sizeof(float2) * PTC_NW);
     L.k = L.keep0 + a256(sizeof(float2) * PTC_NW);
     take(f1);
@@ -66,18 +66,16 @@ struct Ptc {
     template <typename T> T *at(size_t o) const { return reinterpret_cast<T *>(ws + o); }
 };
 
-const double *c0_of(const float2 *fold) { return reinterpret_cast<const double *>(fold + PTC_C0); }
-
 // out_even = N(in_even); skip (nullable): every launch does nothing while
 // *skip != 0.  keep: leave the input and the weights for the backward pass.
 hipError_t forward(const Ptc &P, const float2 *w, const void *in_even, void *out_even, bool keep,
                    const int *skip = nullptr) {
-    float2 *fold = P.at<float2>(P.L.fold);
+    double2 *fold = P.at<double2>(P.L.fold);
     hipError_t e = ptc_fold(w, fold, keep ? P.at<float2>(P.L.keep) : nullptr, P.st, skip);
     if (e == hipSuccess)
         e = ptc_spread(P.g, P.links, fold, in_even, 1, 0, 1, P.at<float2>(P.L.s), P.st, skip);
     if (e == hipSuccess)
-        e = ptc_gather(P.g, c0_of(fold), in_even, P.at<float2>(P.L.s), out_even, keep ? P.at<void>(P.L.a0) : nullptr,
+        e = ptc_gather(P.g, fold + PTC_C0, in_even, P.at<float2>(P.L.s), out_even, keep ? P.at<void>(P.L.a0) : nullptr,
                        P.st, skip);
     return e;
 }
@@ -92,12 +90,13 @@ hipError_t backward(const Ptc &P, const float2 *w, const void *g_out, double2 *g
     if (e == hipSuccess)
         e = ptc_chain(P.at<float2>(P.L.keep), w, K, grad, P.st);
     if (e == hipSuccess && g_in) {
-        float2 *fold = P.at<float2>(P.L.fold), *s = P.at<float2>(P.L.s);
+        double2 *fold = P.at<double2>(P.L.fold), *adj = fold + PTC_ADJOINT;
+        float2 *s = P.at<float2>(P.L.s);
         e = ptc_fold(w, fold, nullptr, P.st);
         if (e == hipSuccess)
-            e = ptc_spread(P.g, P.links, fold + 65, g_out, 1, 0, 1, s, P.st);
+            e = ptc_spread(P.g, P.links, adj, g_out, 1, 0, 1, s, P.st);
         if (e == hipSuccess)
-            e = ptc_gather(P.g, c0_of(fold) + 2, g_out, s, g_in, nullptr, P.st);
+            e = ptc_gather(P.g, adj + PTC_C0, g_out, s, g_in, nullptr, P.st);
     }
     return e;
 }
@@ -214,7 +213,8 @@ hisq_status hisq_ptc_train_step(hisq_context *ctx, const hisq_lattice *lat, doub
     double *sum = P.at<double>(P.L.scal);  // the loss
     float2 *w0 = P.at<float2>(P.L.keep0);  // the weights before the update
     double *K = P.at<double>(P.L.k);
-    float2 *fold = P.at<float2>(P.L.fold), *half = P.at<float2>(P.L.s);
+    double2 *fold = P.at<double2>(P.L.fold);
+    float2 *half = P.at<float2>(P.L.s);
     hipError_t e = ptc_fold(w, fold, w0, P.st);
     // PTC_COLS pairs at a time: the columns share every launch
     for (int k = 0; k < batch && e == hipSuccess; k += PTC_COLS) {
@@ -222,7 +222,7 @@ hisq_status hisq_ptc_train_step(hisq_context *ctx, const hisq_lattice *lat, doub
         double *xb = P.at<double>(P.L.xb_part), *corr = P.at<double>(P.L.corr_part);
         e = ptc_spread(P.g, P.links, fold, src_f32, batch, k, n, half, P.st);
         if (e == hipSuccess)
-            e = ptc_error(P.g, c0_of(fold), src_f32, batch, k, n, half, sol_f64, P.at<void>(P.L.e), xb, P.st);
+            e = ptc_error(P.g, fold + PTC_C0, src_f32, batch, k, n, half, sol_f64, P.at<void>(P.L.e), xb, P.st);
         // A e = m^2 e - D_eo D_oe e (FP32 links) with <e, A e>
         const DslashShape shape = pick_shape(ctx, P.g, HISQ_FP32, HISQ_FP32, n);
         DslashParams prm{};

@@ -332,3 +332,37 @@ def test_training_columns_in_one_thread(gpu_lib):
     one = [step([k]) for k in range(3)]
     assert abs(loss - sum(a[0] for a in one) / 3) <= 1e-12 * abs(loss)
     assert np.linalg.norm(m - sum(a[1] for a in one) / 3) <= 1e-12 * np.linalg.norm(m)
+
+
+RANGES = [(1e14, 1e-20), (1e-14, 1e20)]
+
+
+def scaled_network(h, wscale, fscale):
+    """A network whose weights are scaled by wscale on fields scaled by fscale:
+    the products of three weights (1e42, 1e-42) lie outside the range of FP32,
+    every activation and gradient of a layer-by-layer pass inside."""
+    w = gen.workload_smooth(DIMS, 85, -1, 0.3, 2)
+    weights = [np.asarray(f32(x * wscale)) for x in ptc.init_weights(np.random.default_rng(8), scale=0.6)]
+    r, gout = (f32(v * fscale) for v in w["src"])
+    lat = h.lattice(DIMS, -1)
+    l32 = h.pack_links_from_host(lat, "fp32", w["fat"], w["naik"])
+    _, w32 = h.weights_to_device(weights)
+    inp, g = (h.pack_field_from_host(lat, "fp32", v) for v in (r, gout))
+    out, gin = h.empty_field(lat, "fp32"), h.empty_field(lat, "fp32")
+    grad = torch.zeros(2 * h.HISQ_PTC_NWEIGHTS, dtype=torch.float64, device="cuda")
+    ws = h.empty_workspace(h.hisq_ptc_workspace_bytes(lat))
+    h.hisq_ptc_forward(lat, l32, w32, inp, out, ws)
+    h.hisq_ptc_backward(lat, l32, w32, g, gin, grad, ws)
+    ref, acts = ptc.network_forward(DIMS, -1, f32(w["fat"]), weights, r)
+    gws, gin_ref = ptc.network_backward(DIMS, -1, f32(w["fat"]), weights, acts, gout)
+    y, gi = (h.unpack_field_to_host(lat, "fp32", v)[0] for v in (out, gin))
+    return y, gi, h.weights_from_device(grad), ref, gin_ref, gws
+
+
+@pytest.mark.parametrize("wscale,fscale", RANGES)
+def test_products_of_weights_outside_fp32(gpu_lib, wscale, fscale):
+    """The folded map holds products of three weights: applied where they leave
+    the range of FP32, within the module's bound."""
+    y, gin, _, ref, gin_ref, _ = scaled_network(gpu_lib, wscale, fscale)
+    assert rel(y, ref) <= 1e-5
+    assert rel(gin, gin_ref) <= 1e-5
