@@ -613,8 +613,6 @@ inline unsigned nb(int64_t n) { return (unsigned)((n + PB - 1) / PB); }
 
 }  // namespace
 
-int ptc_blocks(const Geom &g) { return (int)nb(2 * (int64_t)g.vh); }
-
 // Blocks of a column in the correlation: at most 1024, four a CU, which keeps
 // the partials few and a thread's FP32 sums short (4 sites at 32^4).
 int ptc_correlate_blocks(const Geom &g) { return std::min((g.vh + CS - 1) / CS, 1024); }

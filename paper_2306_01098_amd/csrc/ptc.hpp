@@ -19,10 +19,6 @@ constexpr int PTC_W3 = PTC_W2 + PTC_CH * PTC_CH * PTC_PATHS;  // layer 3: [1][8]
 constexpr int PTC_NW = PTC_W3 + 1 * PTC_CH * PTC_PATHS;  // 720 complex weights
 constexpr int PTC_BLOCK = 256;
 
-// Whole-lattice FP32 fields of C channels: [c][parity][colour][site] float2,
-// i.e. the packed FP32 half-field layout with right-hand-side index 2c + parity.
-inline size_t ptc_field_bytes(const Geom &g, int channels) { return (size_t)channels * 2 * 3 * g.vh * 8; }
-
 // The folded network (ptc.hip): 65 double2 of the map, 65 of its adjoint; the
 // gradient with respect to it: 64 complex correlations and K0 as doubles.
 constexpr int PTC_NFOLD = 130;
@@ -48,7 +44,6 @@ hipError_t ptc_correlate_sum(const Geom &g, int ncols, const double *partials, b
 hipError_t ptc_chain(const float2 *wf, const float2 *wb, const double *K, double2 *grad, hipStream_t st);
 hipError_t ptc_chain_adam(const float2 *w, const double *K, double2 *w_master, float2 *w_f32, double2 *m, double2 *v,
                           int step, double lr, double b1, double b2, double eps, hipStream_t st);
-int ptc_blocks(const Geom &g);
 int ptc_correlate_blocks(const Geom &g);
 int ptc_error_blocks(const Geom &g);
 hipError_t ptc_adam(double2 *w_master, float2 *w_f32, const double2 *grad, double2 *m, double2 *v, int step,

@@ -13,11 +13,11 @@ namespace {
 
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workspace: the input of the last forward pass (a0), the half-network
-// vectors s of up to PTC_COLS columns, the training chunk's error fields e,
-// t = D_oe e and A e (PTC_COLS columns each), the small arrays (folded map,
-// weights of the last forward pass, correlations, gradient) and the block
-// partials.  `total` is the size that the query has always returned.
+// Workspace: the input of the last forward pass (a0), the half-network vectors
+// s, the training chunk's error fields e, t = D_oe e and A e, all for up to
+// PTC_COLS columns, the small arrays (folded map, weights of the last forward
+// pass and of the training step, correlations, loss) and the block partials of
+// <e, A e>, <x, b> and the correlations.
 struct PtcLayout {
     size_t a0, s, e, t, ae, fold, keep, keep0, k, scal, dot_part, xb_part, corr_part, total;
 };
@@ -30,29 +30,20 @@ PtcLayout ptc_layout(const Geom &g) {
         off = a256(off + b);
         return o;
     };
-    const size_t f1 = ptc_field_bytes(g, 1), f8 = ptc_field_bytes(g, PTC_CH), h32 = field_bytes(g, HISQ_FP32, 1);
-    L.a0 = take(f1);
-    L.s = take(f8);  // 8 vectors on half the sites per column: PTC_COLS columns are two 8-channel fields
-    take(f8);
-    take(f1);
-    take(f1);
-    L.e = take(f8);  // 3 PTC_COLS half fields of the 16 that an 8-channel field holds
-    L.t = a256(L.e + PTC_COLS * h32);
-    L.ae = a256(L.t + PTC_COLS * h32);
-    L.fold = take(f8);  // at least 48 KiB
-    L.keep = L.fold + a256(sizeof(double2) * PTC_NFOLD);
-    L.keep0 = L.keep + a256(sizeof(float2) * PTC_NW);
-    L.k = L.keep0 + a256(sizeof(float2) * PTC_NW);
-    take(f1);
-    // doubles: the M_e dot (at most vh / 4 + 1 a column), <x, b>, correlations
-    const size_t nvh = (size_t)g.vh;
-    L.dot_part = take(sizeof(double) * PTC_CH * PTC_PATHS * 2 * PTC_CH * ptc_blocks(g));
-    L.xb_part = L.dot_part + sizeof(double) * 2 * nvh;
-    L.corr_part = L.xb_part + sizeof(double) * nvh;
-    take(sizeof(double2) * PTC_NW);
-    L.scal = take(sizeof(double) * 64);
-    for (int k = 0; k < 4; ++k)
-        take(h32);
+    const size_t h32 = field_bytes(g, HISQ_FP32, 1), cols32 = field_bytes(g, HISQ_FP32, PTC_COLS);
+    L.a0 = take(h32);
+    L.s = take(8 * PTC_COLS * h32);  // eight vectors on half the sites per column
+    L.e = take(cols32);
+    L.t = take(cols32);
+    L.ae = take(cols32);
+    L.fold = take(sizeof(double2) * PTC_NFOLD);
+    L.keep = take(sizeof(float2) * PTC_NW);
+    L.keep0 = take(sizeof(float2) * PTC_NW);
+    L.k = take(sizeof(double) * PTC_NK);
+    L.scal = take(sizeof(double));
+    L.dot_part = take(sizeof(double) * PTC_COLS * (g.vh / 4 + 1));  // a Dslash block holds at least 4 sites
+    L.xb_part = take(sizeof(double) * PTC_COLS * ptc_error_blocks(g));
+    L.corr_part = take(sizeof(double) * PTC_COLS * PTC_NK * ptc_correlate_blocks(g));
     L.total = off;
     return L;
 }

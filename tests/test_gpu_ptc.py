@@ -366,3 +366,38 @@ def test_products_of_weights_outside_fp32(gpu_lib, wscale, fscale):
     y, gin, _, ref, gin_ref, _ = scaled_network(gpu_lib, wscale, fscale)
     assert rel(y, ref) <= 1e-5
     assert rel(gin, gin_ref) <= 1e-5
+
+
+@pytest.mark.parametrize("dims,batch", [((4, 4, 4, 4), 1), ((4, 4, 4, 4), 7), ((4, 6, 4, 14), 4), ((8, 8, 8, 8), 5)])
+def test_workspace_of_the_query_is_enough(gpu_lib, dims, batch):
+    """Forward, backward and a training step in a workspace of exactly the bytes
+    that the query returns, filled with NaN, with the Dslash shape that has the
+    most partial sums (four sites a block): not a byte behind it changes, and
+    the results are those in a larger one, bit for bit."""
+    h = gpu_lib
+    w = gen.workload_smooth(dims, 86, -1, 0.3, batch)
+    lat = h.lattice(dims, -1)
+    l32 = h.pack_links_from_host(lat, "fp32", w["fat"], w["naik"])
+    weights = [np.asarray(f32(x)) for x in ptc.init_weights(np.random.default_rng(9), scale=0.6)]
+    src, sol = h.pack_field_from_host(lat, "fp32", w["src"]), h.pack_field_from_host(lat, "fp64", w["src"])
+    one = h.pack_field_from_host(lat, "fp32", w["src"][0])
+    ctx = h.Context(0)
+    for n in range(1, 5):
+        h.hisq_set_dslash_shape(lat, "fp32", n, (3, 1, 64, 1), ctx)
+    size, tail = h.hisq_ptc_workspace_bytes(lat), 1 << 16
+
+    def results(extra):
+        buf = h.empty_workspace(size + extra + tail)
+        buf.fill_(0xFF)
+        ws = buf[:size + extra]
+        master, w32 = h.weights_to_device(weights)
+        m, v, grad = (torch.zeros_like(master) for _ in range(3))
+        out, gin = torch.zeros_like(one), torch.zeros_like(one)
+        h.hisq_ptc_forward(lat, l32, w32, one, out, ws, ctx=ctx)
+        h.hisq_ptc_backward(lat, l32, w32, out, gin, grad, ws, ctx=ctx)
+        loss = h.hisq_ptc_train_step(lat, 0.2, l32, master, w32, m, v, 1, batch, src, sol, ws, ctx=ctx)
+        assert bool((buf[size + extra:] == 0xFF).all())
+        assert np.isfinite(loss) and all(bool(torch.isfinite(x.view(torch.float32)).all()) for x in (out, gin))
+        return [out, gin, grad, master, m, v, torch.tensor(loss)]
+
+    assert all(torch.equal(a, b) for a, b in zip(results(0), results(1 << 20)))
