@@ -155,46 +155,11 @@ __global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, double
     fold[65 + (e < 64 ? 8 * ((e & 7) ^ 1) + ((e >> 3) ^ 1) : 64)] = make_double2(sum.x, -sum.y);
 }
 
-// Two wavefronts work on 64 odd sites, one with the hops in x and y and one
-// with those in z and t: four links a thread.  With all eight hops in a thread
-// the links and vectors take over 256 VGPRs and one wavefront per SIMD is left
-// (spread 118 us at 32^4), and the 64 accumulators of the correlation spill.
+// Two wavefronts spread 64 odd sites, one with the hops in x and y and one with
+// those in z and t: four links a thread.  With all eight hops in a thread the
+// links and vectors take over 256 VGPRs and one wavefront per SIMD is left (118
+// us at 32^4 instead of 91).
 constexpr int CS = PB / 2;  // sites of a block
-
-using HalfLds = float4[PB / 64][6][64];
-
-// t[4..7] = the four vectors t[0..3] of the other wavefront of the same sites.
-__device__ __forceinline__ void swap_halves(cplx<float> (&t)[NHOP][3], HalfLds &lds) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float flat[24];
-#pragma unroll
-    for (int l = 0; l < 4; ++l)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            flat[6 * l + 2 * a] = t[l][a].re;
-            flat[6 * l + 2 * a + 1] = t[l][a].im;
-        }
-    __syncthreads();  // the reads of the previous exchange are done
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-        lds[wave][j][lane] = make_float4(flat[4 * j], flat[4 * j + 1], flat[4 * j + 2], flat[4 * j + 3]);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const float4 v = lds[wave ^ 1][j][lane];
-        flat[4 * j] = v.x;
-        flat[4 * j + 1] = v.y;
-        flat[4 * j + 2] = v.z;
-        flat[4 * j + 3] = v.w;
-    }
-#pragma unroll
-    for (int l = 0; l < 4; ++l)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            t[4 + l][a].re = flat[6 * l + 2 * a];
-            t[4 + l][a].im = flat[6 * l + 2 * a + 1];
-        }
-}
 
 // First half of the folded network on the odd sites y: the transported vectors
 // t_p = T_p in, for every hop p' the combination u_p', and s_p' = T_p' u_p'
@@ -210,7 +175,7 @@ __global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, c
                                                     const int *skip) {
     if (skip && *skip)
         return;
-    __shared__ float2 lds[PB / 64][12][64];  // t_p of a site: four of its one wavefront, four of the other
+    __shared__ float2 lds[PB / 64][12][64];  // t_p: four of a site's in one wavefront, four in the other
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
     const int i = site_block() * CS + (wave >> 1) * 64 + (threadIdx.x & 63);
     const bool valid = i < g.vh;
@@ -234,7 +199,7 @@ __global__ void __launch_bounds__(PB) spread_kernel(Geom g, const char *links, c
             else
                 transport<false>(m[l], v, t[l]);
         }
-        __syncthreads();  // the reads of the previous column are done
+        __syncthreads();  // the vectors of the previous column have been read
 #pragma unroll
         for (int l = 0; l < 4; ++l)
 #pragma unroll
@@ -350,100 +315,118 @@ __global__ void __launch_bounds__(PB) error_kernel(int vh, const double2 *c0, co
 }
 
 // Block partials of K[p'][p] and K0 for column blockIdx.y of the pair (in, g),
-// both even-site fields.  A block walks groups of CS odd sites: a thread forms
-// four t_p = T_p in and four h_q = T_q g with its four links, takes the other
-// four t_p of its site through LDS and adds conj(t_p) h_q to 32 accumulators
-// (q = p' ^ 1: T_p'^+ = T_q).  A thread's sums over its sites and the sums over
-// the wavefront are FP32 (halving exchanges), from there on FP64; slot
-// 2 (8 p' + p) + re/im, then K0, at partials[(column * 130 + slot) * gridDim.x +
-// block].
-__global__ void __launch_bounds__(PB) correlate_kernel(Geom g, const char *links, const void *in, int nin, int cin,
-                                                       const void *gr, int ngr, double *partials) {
-    __shared__ HalfLds lds;
-    __shared__ double sums[PB / 64][66];
+// both even-site fields.  A block walks groups of 64 odd sites, one wavefront
+// per direction: a thread forms two t_p = T_p in and two h_q = T_q g with its
+// two links, takes the eight t_p of its site through LDS and adds conj(t_p) h_q
+// to 16 accumulators (q = p' ^ 1: T_p'^+ = T_q), all products and sums in FP64:
+// a sum over a lattice has no bound on its length, and a product of two fields
+// may lie outside FP32.  FP64 and FP32 products issue at the same rate here, so
+// the kernel stays bound by its loads and their latency: with sums and chain
+// rule 82 us at 32^4, 78 with products and sums in FP32, whose error grew with
+// the lattice (64^3x48 3e-7 of the gradient, now 7e-8).  With two wavefronts on
+// 64 sites a thread's 32 accumulators take it past 256 VGPRs; h_q goes through
+// LDS as well, 162 VGPRs and three wavefronts a SIMD instead of 174 and two (90
+// -> 86 us).  Slot 2 (8 p' + p) + re/im, then K0, at
+// partials[(column * 130 + slot) * gridDim.x + block].
+constexpr int KS = 64;  // sites of a group
+
+__global__ void __launch_bounds__(PB, 3) correlate_kernel(Geom g, const char *links, const void *in, int nin, int cin,
+                                                          const void *gr, int ngr, double *partials) {
+    __shared__ float2 hops[4][6][KS], back[4][6][KS];
+    __shared__ double sums[PTC_NK];
     const int k = blockIdx.y, lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
-    float acc[64];              // [own q][own p, then the other half's p] re, then im
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double acc[32];             // re [q][p], then im
 #pragma unroll
-    for (int e = 0; e < 64; ++e)
-        acc[e] = 0.f;
-    float k0r = 0.f, k0i = 0.f;
-    const int ngroups = (g.vh + CS - 1) / CS;
+    for (int e = 0; e < 32; ++e)
+        acc[e] = 0.0;
+    double k0r = 0.0, k0i = 0.0;
+    const int ngroups = (g.vh + KS - 1) / KS;
     for (int gi = site_block(); gi < ngroups; gi += gridDim.x) {
-        const int i = gi * CS + (wave >> 1) * 64 + lane;
-        cplx<float> t[NHOP][3], hq[4][3];
+        const int i = gi * KS + lane;
+        cplx<float> t[2][3], hf[2][3];
         if (i < g.vh) {
             const Site st = site_coords(g, 1, i);
 #pragma unroll
-            for (int l = 0; l < 4; ++l) {
-                const Hop h = odd_hop(g, st, i, 4 * half + l);
+            for (int l = 0; l < 2; ++l) {
+                const Hop h = odd_hop(g, st, i, 2 * mu + l);
                 float m[18];
                 cplx<float> v[3], w[3];
-                load_link(links, g.vh, 2 * half + (l >> 1), h, m);
+                load_link(links, g.vh, mu, h, m);
                 FieldIO<HISQ_FP32>::template load<float>(in, g.vh, nin, cin + k, h.nb, v);
                 FieldIO<HISQ_FP32>::template load<float>(gr, g.vh, ngr, k, h.nb, w);
-                if (l & 1) {
-                    transport<true>(m, v, t[l]);
-                    transport<true>(m, w, hq[l]);
-                } else {
+                if (l == 0) {
                     transport<false>(m, v, t[l]);
-                    transport<false>(m, w, hq[l]);
+                    transport<false>(m, w, hf[l]);
+                } else {
+                    transport<true>(m, v, t[l]);
+                    transport<true>(m, w, hf[l]);
                 }
             }
         } else {
 #pragma unroll
-            for (int l = 0; l < 4; ++l)
+            for (int l = 0; l < 2; ++l)
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    t[l][a].re = t[l][a].im = hq[l][a].re = hq[l][a].im = 0.f;
+                    t[l][a].re = t[l][a].im = hf[l][a].re = hf[l][a].im = 0.f;
         }
-        swap_halves(t, lds);
+        __syncthreads();  // the vectors of the previous group have been read
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int p = 0; p < NHOP; ++p)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    float &re = acc[8 * q + p], &im = acc[32 + 8 * q + p];
-                    re = fmaf(t[p][a].re, hq[q][a].re, re);
-                    re = fmaf(t[p][a].im, hq[q][a].im, re);
-                    im = fmaf(t[p][a].re, hq[q][a].im, im);
-                    im = fmaf(-t[p][a].im, hq[q][a].re, im);
-                }
-        if (half == 0 && i < g.vh) {  // K0 on the even site of the same index
-            cplx<float> v[3], w[3];
-            FieldIO<HISQ_FP32>::template load<float>(in, g.vh, nin, cin + k, i, v);
-            FieldIO<HISQ_FP32>::template load<float>(gr, g.vh, ngr, k, i, w);
+        for (int l = 0; l < 2; ++l)
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                k0r = fmaf(v[a].re, w[a].re, fmaf(v[a].im, w[a].im, k0r));
-                k0i = fmaf(v[a].re, w[a].im, fmaf(-v[a].im, w[a].re, k0i));
+                hops[mu][3 * l + a][lane] = make_float2(t[l][a].re, t[l][a].im);
+                back[mu][3 * l + a][lane] = make_float2(hf[l][a].re, hf[l][a].im);
+            }
+        __syncthreads();
+        cplx<double> h[2][3];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float2 e = back[mu][3 * q + a][lane];
+                h[q][a].re = e.x;
+                h[q][a].im = e.y;
+            }
+#pragma unroll
+        for (int p = 0; p < NHOP; ++p)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float2 e = hops[p >> 1][3 * (p & 1) + a][lane];
+                const double tr = e.x, ti = e.y;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    double &re = acc[8 * q + p], &im = acc[16 + 8 * q + p];
+                    re = fma(tr, h[q][a].re, re);
+                    re = fma(ti, h[q][a].im, re);
+                    im = fma(tr, h[q][a].im, im);
+                    im = fma(-ti, h[q][a].re, im);
+                }
+            }
+        if (mu == 0 && i < g.vh) {  // K0 on the even site of the same index
+            cplx<double> v[3], w[3];
+            FieldIO<HISQ_FP32>::template load<double>(in, g.vh, nin, cin + k, i, v);
+            FieldIO<HISQ_FP32>::template load<double>(gr, g.vh, ngr, k, i, w);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                k0r = fma(v[a].re, w[a].re, fma(v[a].im, w[a].im, k0r));
+                k0i = fma(v[a].re, w[a].im, fma(-v[a].im, w[a].re, k0i));
             }
         }
     }
-    wave_sum_multi<64>(acc);
-    k0r = wave_sum(k0r);
-    k0i = wave_sum(k0i);
-    sums[wave][wave_multi_index<64>(lane)] = (double)acc[0];
-    if (lane == 0) {
-        sums[wave][64] = (double)k0r;
-        sums[wave][65] = (double)k0i;
+    wave_sum_multi<32>(acc);
+    // the value [re/im][q][p] of this lane goes to slot 2 (8 p' + p) + re/im, p' = (2 mu + q) ^ 1
+    const int e = wave_multi_index<32>(lane), po = (2 * mu + ((e >> 3) & 1)) ^ 1;
+    sums[2 * (8 * po + (e & 7)) + (e >> 4)] = acc[0];
+    if (mu == 0) {
+        k0r = wave_sum(k0r);
+        k0i = wave_sum(k0i);
+        sums[128] = k0r;
+        sums[129] = k0i;
     }
     __syncthreads();
-    if (threadIdx.x < PTC_NK) {
-        int hf = 0, e = 64 + (threadIdx.x & 1);
-        if (threadIdx.x < 128) {
-            const int q = (threadIdx.x >> 4) ^ 1, p = (threadIdx.x >> 1) & 7;
-            hf = q >> 2;
-            // the other half's p follow a thread's own in its accumulators
-            e = 32 * (threadIdx.x & 1) + 8 * (q & 3) + (p & 3) + ((p >> 2) == hf ? 0 : 4);
-        }
-        double tot = 0.0;
-#pragma unroll
-        for (int wv = 0; wv < PB / 64; wv += 2)
-            tot += sums[wv + hf][e];
-        partials[((size_t)k * PTC_NK + threadIdx.x) * gridDim.x + blockIdx.x] = tot;
-    }
+    if (threadIdx.x < PTC_NK)
+        partials[((size_t)k * PTC_NK + threadIdx.x) * gridDim.x + blockIdx.x] = sums[threadIdx.x];
 }
 
 // Sum of n block partials by one wavefront, eight loads in flight a lane.
@@ -613,9 +596,14 @@ inline unsigned nb(int64_t n) { return (unsigned)((n + PB - 1) / PB); }
 
 }  // namespace
 
-// Blocks of a column in the correlation: at most 1024, four a CU, which keeps
-// the partials few and a thread's FP32 sums short (4 sites at 32^4).
-int ptc_correlate_blocks(const Geom &g) { return std::min((g.vh + CS - 1) / CS, 1024); }
+// Blocks of a column in the correlation: as many as run at once over all
+// columns, three on each of 256 CUs.  Limits of 512 / 768 / 1024 a column: one
+// column at 32^4 87 / 82 / 86 us (sums and chain rule too), 48^4 389 / 360 / 380;
+// training step on four pairs, limits of 128 / 256 / 768 a column: 32^4 1027 /
+// 1034 / 1084 us, 24^3x16 279 / 288 / 306, 16^4 155 / 156 / 159.
+int ptc_correlate_blocks(const Geom &g, int ncols) {
+    return std::min((g.vh + KS - 1) / KS, (768 + ncols - 1) / ncols);
+}
 
 int ptc_error_blocks(const Geom &g) { return (int)nb(g.vh); }
 
@@ -653,15 +641,16 @@ hipError_t ptc_error(const Geom &g, const double2 *c0, const void *b32, int ncol
 
 hipError_t ptc_correlate(const Geom &g, const char *links, const void *in, int nin, int cin, const void *gr, int ncols,
                          double *partials, hipStream_t st) {
-    correlate_kernel<<<dim3((unsigned)ptc_correlate_blocks(g), (unsigned)ncols), PB, 0, st>>>(g, links, in, nin, cin,
-                                                                                              gr, ncols, partials);
+    const dim3 grid((unsigned)ptc_correlate_blocks(g, ncols), (unsigned)ncols);
+    correlate_kernel<<<grid, PB, 0, st>>>(g, links, in, nin, cin, gr, ncols, partials);
     return hipGetLastError();
 }
 
 hipError_t ptc_correlate_sum(const Geom &g, int ncols, const double *partials, bool first, double *K, const double *xb,
                              double inv_batch, const double *dot, int ndot, double *loss, hipStream_t st) {
-    correlate_sum_kernel<<<PTC_NK, 64 * PTC_COLS, 0, st>>>(ncols, ptc_correlate_blocks(g), partials, first ? 1 : 0, K,
-                                                           xb, ptc_error_blocks(g), inv_batch, dot, ndot, loss);
+    correlate_sum_kernel<<<PTC_NK, 64 * PTC_COLS, 0, st>>>(ncols, ptc_correlate_blocks(g, ncols), partials,
+                                                           first ? 1 : 0, K, xb, ptc_error_blocks(g), inv_batch, dot,
+                                                           ndot, loss);
     return hipGetLastError();
 }
 

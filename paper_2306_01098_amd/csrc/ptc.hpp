@@ -44,7 +44,7 @@ hipError_t ptc_correlate_sum(const Geom &g, int ncols, const double *partials, b
 hipError_t ptc_chain(const float2 *wf, const float2 *wb, const double *K, double2 *grad, hipStream_t st);
 hipError_t ptc_chain_adam(const float2 *w, const double *K, double2 *w_master, float2 *w_f32, double2 *m, double2 *v,
                           int step, double lr, double b1, double b2, double eps, hipStream_t st);
-int ptc_correlate_blocks(const Geom &g);
+int ptc_correlate_blocks(const Geom &g, int ncols);
 int ptc_error_blocks(const Geom &g);
 hipError_t ptc_adam(double2 *w_master, float2 *w_f32, const double2 *grad, double2 *m, double2 *v, int step,
                     double lr, double b1, double b2, double eps, hipStream_t st);

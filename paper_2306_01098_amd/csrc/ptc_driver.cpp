@@ -43,7 +43,7 @@ PtcLayout ptc_layout(const Geom &g) {
     L.scal = take(sizeof(double));
     L.dot_part = take(sizeof(double) * PTC_COLS * (g.vh / 4 + 1));  // a Dslash block holds at least 4 sites
     L.xb_part = take(sizeof(double) * PTC_COLS * ptc_error_blocks(g));
-    L.corr_part = take(sizeof(double) * PTC_COLS * PTC_NK * ptc_correlate_blocks(g));
+    L.corr_part = take(sizeof(double) * PTC_COLS * PTC_NK * ptc_correlate_blocks(g, PTC_COLS));  // fewer columns take no more
     L.total = off;
     return L;
 }

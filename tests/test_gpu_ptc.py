@@ -401,3 +401,56 @@ def test_workspace_of_the_query_is_enough(gpu_lib, dims, batch):
         return [out, gin, grad, master, m, v, torch.tensor(loss)]
 
     assert all(torch.equal(a, b) for a, b in zip(results(0), results(1 << 20)))
+
+
+@pytest.mark.parametrize("wscale,fscale", RANGES)
+def test_gradient_of_fields_outside_fp32_squared(gpu_lib, wscale, fscale):
+    """The weight gradient is formed from products of two fields (1e-40, 1e40),
+    which lie outside the range of FP32 where those of activations and
+    gradients in a layer-by-layer pass lie inside: within the module's bound."""
+    _, _, grad, _, _, gws = scaled_network(gpu_lib, wscale, fscale)
+    for a, b in zip(grad, gws):
+        assert rel(a, b) <= 1e-5
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 16), (32, 32, 32, 32), (48, 48, 32, 48)])
+def test_gradient_of_large_lattices(gpu_lib, dims):
+    """The sums of the weight gradient over 4096 (one group of 64 sites a block),
+    524288 (ten or eleven groups) and 1769472 sites per parity (36), for g = the
+    input of the pass (all diagonal terms of the same sign).  With unit links and a constant field c on
+    the even sites every hop of it is c, so the gradient of each weight is the
+    chain rule's number times vh |c|^2: products and sums in FP64, 1e-10 (FP32
+    sums of equal terms are off by 1e-9 and more from eight sites on)."""
+    h = gpu_lib
+    lat = h.lattice(dims, 1)
+    vh = gen.volume(dims) // 2
+    unit = torch.zeros(4, *dims[::-1], 3, 3, dtype=torch.complex128, device="cuda")
+    unit[..., range(3), range(3)] = 1.0
+    l32 = h.empty_links(lat, "fp32")
+    h.hisq_pack_links(lat, "fp32", unit, unit, l32)
+    del unit
+    c = np.asarray(f32(np.array([0.7 - 0.3j, 0.1 + 0.9j, -0.4 + 0.2j])))
+    half = torch.from_numpy(c).cuda().expand(1, vh, 3).contiguous()
+    inp, out = h.empty_field(lat, "fp32"), h.empty_field(lat, "fp32")
+    h.hisq_pack_field(lat, "fp32", 1, half, inp)
+    weights = [np.asarray(f32(x)) for x in ptc.init_weights(np.random.default_rng(10), scale=0.6)]
+    _, w32 = h.weights_to_device(weights)
+    grad = torch.zeros(2 * h.HISQ_PTC_NWEIGHTS, dtype=torch.float64, device="cuda")
+    ws = h.empty_workspace(h.hisq_ptc_workspace_bytes(lat))
+    h.hisq_ptc_forward(lat, l32, w32, inp, out, ws)
+    h.hisq_ptc_backward(lat, l32, w32, inp, None, grad, ws)
+    # the network on one even and one odd site: a hop takes the other one's value
+    w1, w2, w3 = weights
+    even, odd = w1[:, 0, 0], w1[:, 0, 1:].sum(1)
+    k, ident = vh * np.vdot(c, c).real, [w[:, :, 0] for w in weights]
+    hops = [w[:, :, 1:].sum(2) for w in weights]
+    e2, o2 = ident[1] @ even + hops[1] @ odd, ident[1] @ odd + hops[1] @ even
+    ge2, go2 = ident[2][0].conj() * k, hops[2][0].conj() * k
+    ge1, go1 = ident[1].conj().T @ ge2 + hops[1].conj().T @ go2, ident[1].conj().T @ go2 + hops[1].conj().T @ ge2
+    want = [np.empty_like(w) for w in weights]
+    want[2][0, :, 0], want[2][0, :, 1:] = e2.conj() * k, (o2.conj() * k)[:, None]
+    want[1][:, :, 0] = np.outer(ge2, even.conj()) + np.outer(go2, odd.conj())
+    want[1][:, :, 1:] = (np.outer(ge2, odd.conj()) + np.outer(go2, even.conj()))[:, :, None]
+    want[0][:, 0, 0], want[0][:, 0, 1:] = ge1, go1[:, None]
+    for a, b in zip(h.weights_from_device(grad), want):
+        assert rel(a, b) <= 1e-10
