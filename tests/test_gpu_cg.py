@@ -261,3 +261,87 @@ def test_stop_after_odd_and_even_updates(gpu_lib, inner, nrhs, iters):
         before = O.cg(O.lattice_from(w), 0.5, w["src"][j], 1e-12, iters - 1).x if iters > 1 else 0 * ref
         assert O.norm(ref - before) > 1e-2 * O.norm(ref)
         assert O.norm(xs[j] - ref) <= 1e-4 * O.norm(ref)
+
+
+# Four sites a block: 4096 partial sums a column on 16^3 x 8, more than the fused
+# step takes (2048), so these solves run the two-launch step as large lattices do.
+UNFUSED, UNFUSED_DIMS = (3, 1, 64, 1), (16, 16, 16, 8)
+
+
+def unfused(h, w, inner, nrhs, src=None):
+    lat, l64, lin, b, x, ws = setup(h, w, inner, nrhs, src=src)
+    ctx = h.Context(0)
+    for prec in {inner, "fp64"}:
+        h.hisq_set_dslash_shape(lat, prec, nrhs, UNFUSED, ctx)
+    return lat, l64, lin, b, x, ws, ctx
+
+
+@pytest.fixture(scope="module")
+def unfused_workload():
+    return gen.workload_haar(UNFUSED_DIMS, 49, -1, 4)
+
+
+@pytest.fixture(scope="module")
+def unfused_iterates(unfused_workload):
+    """The oracle's CG iterates 0 .. 6 for m = 0.5, column by column."""
+    w = unfused_workload
+    lat = O.lattice_from(w)
+    zero = np.zeros_like(w["src"][0])
+    return [[zero] + [O.cg(lat, 0.5, w["src"][j], 1e-14, k).x for k in range(1, 7)] for j in range(2)]
+
+
+@pytest.mark.parametrize("inner,nrhs", [("fp64", 1), ("fp64", 2), ("fp32", 1), ("fp32", 2)])
+@pytest.mark.parametrize("iters", [1, 2, 5, 6])
+def test_two_launch_step_stops_after_odd_and_even_updates(gpu_lib, unfused_workload, unfused_iterates, inner, nrhs, iters):
+    """As above for one column a block and for column pairs of the two-launch
+    step: the oracle's iterate to the rounding of a few operator applications
+    (FP32: each below 100 eps = 1.2e-5 of its result; FP64: 1e-12)."""
+    h = gpu_lib
+    w = unfused_workload
+    lat, l64, lin, b, x, ws, ctx = unfused(h, w, inner, nrhs)
+    st, info = h.hisq_cg(lat, 0.5, l64, lin, inner, nrhs, b, x, 1e-14, iters, ws, ctx=ctx)
+    assert st == h.NOT_CONVERGED and [i["iterations"] for i in info] == [iters] * nrhs
+    xs = h.unpack_field_to_host(lat, "fp64", x, nrhs)
+    for j in range(nrhs):
+        ref, before = unfused_iterates[j][iters], unfused_iterates[j][iters - 1]
+        assert O.norm(ref - before) > 1e-2 * O.norm(ref)
+        assert O.norm(xs[j] - ref) <= (1e-12 if inner == "fp64" else 1e-4) * O.norm(ref)
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32"])
+def test_two_launch_step_columns_stop_apart(gpu_lib, unfused_workload, unfused_iterates, inner):
+    """Columns that start from different iterates stop after different numbers
+    of updates, odd and even, while others go on: each converges to the
+    tolerance by the oracle.  In FP64 the recurrence's residual is the true one
+    to far less than the tolerance, so no column needs its residual replaced: a
+    term of x left out at a stop would show as one."""
+    h = gpu_lib
+    w = unfused_workload
+    start = ((0, 0), (0, 3), (1, 2), (1, 6), (0, 5), (1, 4))
+    nrhs, m, tol = len(start), 0.5, 1e-9
+    src = w["src"][[j for j, _ in start]]
+    lat, l64, lin, b, x, ws, ctx = unfused(h, w, inner, nrhs, src=src)
+    x.copy_(h.pack_field_from_host(lat, "fp64", np.stack([unfused_iterates[j][k] for j, k in start])))
+    st, info = h.hisq_cg(lat, m, l64, lin, inner, nrhs, b, x, tol, 5000, ws, ctx=ctx)
+    assert st == h.OK, info
+    stops = [i["iterations"] for i in info]
+    print(f"\n{inner}: stopped after {stops}")
+    assert len(set(stops)) > 1
+    if inner == "fp64":
+        assert {n % 2 for n in stops} == {0, 1} and not any(i["reliable_updates"] for i in info)
+    res, _ = oracle_residuals(h, w, lat, x, nrhs, m, src)
+    assert max(res) <= tol, res
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "fp32r12"])
+def test_two_launch_step_single_column_solve(gpu_lib, inner):
+    """One column: a reliable-update solve (FP64: a plain one) to the tolerance, in
+    the step that a 48^3 x 12 lattice takes."""
+    h = gpu_lib
+    w = gen.workload_smooth(UNFUSED_DIMS, 50, -1, 0.3, 1)
+    lat, l64, lin, b, x, ws, ctx = unfused(h, w, inner, 1)
+    st, info = h.hisq_cg(lat, 0.05, l64, lin, inner, 1, b, x, 1e-10, 20000, ws, ctx=ctx)
+    assert st == h.OK, info
+    res, _ = oracle_residuals(h, w, lat, x, 1, 0.05, w["src"])
+    assert res[0] <= 1e-10
+    assert inner == "fp64" or info[0]["reliable_updates"] >= 1
