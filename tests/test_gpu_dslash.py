@@ -630,3 +630,75 @@ def test_whole_and_partial_groups_of_columns(gpu_lib, prec, nrhs):
             outs.append(o.clone())
         refs = refs or outs
         assert all(torch.equal(a, b) for a, b in zip(refs, outs)), shape
+
+
+def _device_links(dims, seed, naik_phase):
+    """Random SU(3) fat and U(3) Naik links drawn on the GPU (the third row from the other two)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    out = []
+    for phase in (0.0, naik_phase):
+        z = torch.view_as_complex(torch.randn(4, *dims[::-1], 2, 3, 2, dtype=torch.float64, device="cuda", generator=g))
+        a = z[..., 0, :] / torch.linalg.vector_norm(z[..., 0, :], dim=-1, keepdim=True)
+        b = z[..., 1, :] - a * (a.conj() * z[..., 1, :]).sum(-1, keepdim=True)
+        b = b / torch.linalg.vector_norm(b, dim=-1, keepdim=True)
+        u = torch.stack((a, b, torch.linalg.cross(a, b, dim=-1).conj()), dim=-2)
+        out.append((u * np.exp(1j * phase)).contiguous())
+    return out
+
+
+# (extents, precision of links and fields, right-hand sides, variant and columns
+# a thread of the built-in shape)
+LARGE_SHAPES = [
+    ((32, 16, 16, 16), "fp32", 10, (2, 4)), ((32, 16, 16, 16), "fp32", 16, (2, 4)),    # ten columns: staged
+    ((32, 16, 16, 16), "fp32", 8, (0, 4)), ((32, 16, 16, 16), "fp32", 6, (0, 8)),
+    ((32, 32, 32, 8), "fp64", 3, (0, 4)), ((32, 32, 32, 8), "fp64", 4, (2, 4)),        # links above 256 MB
+    ((32, 32, 32, 8), "fp64", 5, (0, 8)), ((32, 32, 32, 8), "fp64", 8, (2, 4)),
+    ((32, 32, 32, 8), "fp64", 14, (0, 4)), ((32, 32, 32, 8), "fp64w14", 8, (2, 4)),
+    ((32, 32, 32, 16), "fp32", 2, (2, 2)), ((32, 32, 32, 16), "fp32", 8, (2, 8)),
+    ((32, 32, 32, 16), "fp32", 13, (2, 8)), ((32, 32, 32, 16), "fp32", 16, (2, 8)),
+    ((32, 32, 32, 16), "fp32", 11, (2, 4)), ((32, 32, 32, 16), "fp32w14", 7, (2, 8)),
+    ((64, 32, 32, 8), "fp32", 8, (0, 8)), ((64, 32, 32, 8), "fp32", 15, (0, 8)),       # eight columns do not fit LDS
+    ((24, 24, 24, 48), "fp32r12", 16, (0, 4)), ((32, 32, 32, 16), "fp16n", 16, (0, 2)),
+]
+
+
+def test_built_in_shapes_of_large_lattices_are_those_tested(gpu_lib):
+    h = gpu_lib
+    for dims, prec, nrhs, want in LARGE_SHAPES:
+        assert h.hisq_get_dslash_shape(h.lattice(dims, -1), prec, nrhs, None)[:2] == want, (dims, prec, nrhs)
+
+
+@pytest.mark.parametrize("dims,prec,nrhs,shape", LARGE_SHAPES)
+def test_built_in_shapes_of_large_lattices(gpu_lib, dims, prec, nrhs, shape):
+    """The built-in shapes beyond the last-level cache and the one staged by
+    default, with whole and partial groups and non-temporal link loads (one
+    group of FP64, FP32 or W14 links): plain and with the epilogue, bit for bit
+    the columns one by one, one thread per site."""
+    h = gpu_lib
+    lat = h.lattice(dims, -1)
+    f = "fp16n" if prec == "fp16n" else prec[:4]
+    fat, naik = _device_links(dims, 70, 0.0 if prec.endswith("r12") else 0.3)
+    links = h.empty_links(lat, prec)
+    h.hisq_pack_links(lat, prec, fat, naik, links)
+    del fat, naik
+    g = torch.Generator(device="cuda").manual_seed(71)
+    vh = gen.volume(dims) // 2
+    half = torch.view_as_complex(torch.randn(nrhs, vh, 3, 2, dtype=torch.float64, device="cuda", generator=g))
+    inp = torch.zeros(h.hisq_field_bytes(lat, f, nrhs), dtype=torch.uint8, device="cuda")
+    h.hisq_pack_field(lat, f, nrhs, half, inp)
+    del half
+    one = h.Context(0)
+    h.hisq_set_dslash_shape(lat, prec, nrhs, (0, 1, 64, 1), one)
+    tmp = torch.zeros_like(inp)
+    for parity in (0, 1):
+        got, ref = torch.full_like(inp, 0xFF), torch.zeros_like(inp)
+        h.hisq_dslash(lat, prec, parity, links, inp, got, nrhs)
+        h.hisq_dslash(lat, prec, parity, links, inp, ref, nrhs, ctx=one)
+        if f == "fp32" and nrhs % 2:   # the unused slot of the last pair
+            got, ref = (v.view(torch.float32).view((nrhs + 1) // 2, -1, 2, 2) for v in (got, ref))
+            assert not bool(got[-1, :, 1].any())
+        assert torch.equal(got, ref), parity
+    got, ref = torch.zeros_like(inp), torch.zeros_like(inp)
+    h.hisq_apply_m(lat, prec, 0.3, links, inp, got, tmp, nrhs)
+    h.hisq_apply_m(lat, prec, 0.3, links, inp, ref, tmp, nrhs, ctx=one)
+    assert torch.equal(got, ref)
