@@ -302,3 +302,29 @@ def test_refinement_with_groups_of_columns(gpu_lib, nshift, shape):
         got = h.unpack_field_to_host(lat, "fp64", xs[k])[0]
         assert O.true_residual(lat_o, m, w["src"][0], got, shift=s) <= tol
         assert info[k]["refine_iterations"] <= 2 * ref[k]["refine_iterations"] + 8
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32"])
+@pytest.mark.parametrize("nshift", [7, 14])
+def test_refinement_is_the_same_for_every_grouping(gpu_lib, inner, nshift):
+    """On 16 x 8 x 8 x 4 sites in z-slab order a block of 64 sites is one plane,
+    staged in LDS or not, so every sum of the refinement runs over the same
+    terms in the same order however many columns a thread takes: solutions and
+    iteration counts bit for bit those of one column a thread (a wrong shift in
+    one column would change its iterations, not only its residual)."""
+    h = gpu_lib
+    w = gen.workload_haar((16, 8, 8, 4), 60, -1)
+    m, tol = 0.3, 1e-10
+    shifts = [0.05 * k for k in range(nshift)]
+    st, _, _, (lat, l64, lin, b, xs, ws) = run(h, w, inner, shifts, m, tol)
+    assert st == h.OK
+    ctx = h.Context(0)
+    ref = None
+    for var, nin in ((0, 1), (0, 2), (0, 4), (0, 8), (2, 2), (2, 4), (2, 8)):
+        for prec in ("fp32", "fp64"):
+            h.hisq_set_dslash_shape(lat, prec, nshift, (0 if (var, nin, prec) == (2, 8, "fp64") else var, nin, 64, 2), ctx)
+        st, info = h.hisq_multishift_cg(lat, m, l64, lin, inner, shifts, b, xs, tol, 20000, ws, ctx=ctx)
+        assert st == h.OK, info
+        got = [x.clone() for x in xs], [(i["shared_iterations"], i["refine_iterations"]) for i in info]
+        ref = ref or got
+        assert got[1] == ref[1] and all(torch.equal(a, r) for a, r in zip(got[0], ref[0])), (var, nin)
