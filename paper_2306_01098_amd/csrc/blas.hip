@@ -843,7 +843,11 @@ hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStre
 int cg_vec_block(int vh) { return vh <= 32768 ? 64 : BLK; }
 int cg_vec_blocks(int vh) { return (vh + cg_vec_block(vh) - 1) / cg_vec_block(vh); }
 
-hipError_t launch_cgcg_update(const CgVecParams &p, int fp, hipStream_t st) {
+hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipStream_t st) {
+    cgcg_finalize_kernel<<<dim3((unsigned)p.nrhs), 256, 0, st>>>(p, after_check);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
     const int b = cg_vec_block(p.vh);
     const unsigned nb = (unsigned)cg_vec_blocks(p.vh);
     if (fp == HISQ_FP64)
@@ -853,12 +857,6 @@ hipError_t launch_cgcg_update(const CgVecParams &p, int fp, hipStream_t st) {
     else
         cgcg_update_kernel<HISQ_FP32, false><<<dim3(nb, 1u), b, 0, st>>>(p);
     return hipGetLastError();
-}
-
-hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipStream_t st) {
-    cgcg_finalize_kernel<<<dim3((unsigned)p.nrhs), 256, 0, st>>>(p, after_check);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? launch_cgcg_update(p, fp, st) : e;
 }
 
 hipError_t launch_residual_cols(int vh, int ncol, int nf, int col0, int fp, const void *b, int b_cols, const void *ax,

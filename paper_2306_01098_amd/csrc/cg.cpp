@@ -752,7 +752,9 @@ static hisq_status run_cg(Solver &S, const Columns &C, int nrhs, int max_iter, d
     };
     // every real iteration advances some column's count, and a column that
     // keeps failing its true-residual check still advances once per block
-    // (at least one per `check` iterations, chunks and tails alike)
+    // (at least one per `check` iterations, chunks and tails alike), so every
+    // column is terminal when the launches end, its x complete (the two-launch
+    // step adds an outstanding term where a column stops)
     const long max_launch_iters = (long)max_iter * check + 4L * chunk;
     std::vector<double> prev_rho(nrhs, 0.0);
     std::vector<int> prev_it(nrhs, 0);
@@ -802,23 +804,6 @@ static hisq_status run_cg(Solver &S, const Columns &C, int nrhs, int max_iter, d
         return device_fail(e, "cg chunk");
     if (launched > read)
         std::memcpy(hs.data(), pin.slot((int)(launched - 1)), sizeof(CgScalars) * nrhs);
-
-    // launches ended with columns still running: x may lack their last alpha p
-    bool x_later = false;
-    for (int j = 0; j < nrhs; ++j) {
-        x_later |= hs[j].xstep == X_LATER;
-        hs[j].go = hs[j].xstep == X_LATER ? 3 : 0;
-        hs[j].xstep = 0;
-    }
-    if (x_later) {
-        e = hipMemcpyAsync(dst, hs.data(), sizeof(CgScalars) * nrhs, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = launch_cgcg_update(vp, L.fs, st);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(st);
-        if (e != hipSuccess)
-            return device_fail(e, "cg end");
-    }
 
     // final report
     hisq_status result = HISQ_OK;

@@ -55,8 +55,6 @@ hipError_t launch_cg_p(const CgVecParams &p, int fp, int rhs0, int nrhs, hipStre
 // columns whose FP64 true residual the check block just formed) and the
 // fused vector update with the <r, r> partials of the new residual.
 hipError_t launch_cgcg_step(const CgVecParams &p, int fp, int after_check, hipStream_t st);
-// The second of the two alone, on columns whose go is set.
-hipError_t launch_cgcg_update(const CgVecParams &p, int fp, hipStream_t st);
 // r_j = b_j - ax_j for the ncol columns j of packed fields b (b_cols 0: one
 // column for all), ax (FP64)
 // whose tr_skip[j] is 0 (every column if tr_skip is NULL), stored in the
