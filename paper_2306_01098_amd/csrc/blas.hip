@@ -78,8 +78,7 @@ __global__ void __launch_bounds__(BLK) cg_xr_kernel(CgVecParams prm) {
 // One block: sums the <r, r> partials of cg_xr_kernel (nblk blocks per
 // right-hand side) and the <p, A p> partials of the D_eo kernel (in the order
 // cg_xr_kernel summed them) and advances the scalars: breakdown check, rho, beta,
-// convergence / reliable-update / iteration-limit flags, and the multi-shift
-// zeta recurrences, one shift a lane (as a loop of one thread, three FP64
+// convergence and iteration-limit flags, and the multi-shift zeta recurrences, one shift a lane (as a loop of one thread, three FP64
 // divisions a shift, 13 shifts took 9 us more).  ms->stepped: whether this
 // launch advanced the shifts.
 __global__ void __launch_bounds__(1024) cg_finalize_kernel(CgVecParams prm, int nblk) {
@@ -152,22 +151,12 @@ __global__ void __launch_bounds__(1024) cg_finalize_kernel(CgVecParams prm, int 
                 } else if (rho_new <= s.target2) {
                     s.flag = FLAG_CONV;
                     s.active = 0;
-                    prm.tr_skip[j] = 0;
-                    if (prm.nopend)
-                        *prm.nopend = 0;
-                } else if (s.delta2 > 0.0 && rho_new < s.delta2 * s.rmax2) {
-                    s.flag = FLAG_RELIABLE;
-                    s.active = 0;
-                    prm.tr_skip[j] = 0;
-                    if (prm.nopend)
-                        *prm.nopend = 0;
                 } else if (s.iters >= s.max_iter) {
                     s.flag = FLAG_MAXIT;
                     s.active = 0;
                 } else {
                     s.beta = rho_new / s.rho;
                     s.rho = rho_new;
-                    s.rmax2 = fmax(s.rmax2, rho_new);
                 }
             }
             prm.st[j] = s;
@@ -790,18 +779,6 @@ __global__ void __launch_bounds__(BLK) copy_kernel(int vh, int n, const void *sr
     FieldIO<FD>::template store<T>(dst, vh, n, r, i, v);
 }
 
-// dst (one column) = column k of the n-column field src.
-template <int FP>
-__global__ void __launch_bounds__(BLK) copy_col_kernel(int vh, int n, int k, const void *src, void *dst) {
-    using T = typename Sloppy<FP>::T;
-    const int i = blockIdx.x * BLK + threadIdx.x;
-    if (i >= vh)
-        return;
-    cplx<T> v[3];
-    FieldIO<FP>::template load<T>(src, vh, n, k, i, v);
-    FieldIO<FP>::template store<T>(dst, vh, 1, 0, i, v);
-}
-
 __global__ void __launch_bounds__(BLK) fill_u32_kernel(unsigned *p, size_t n, unsigned v) {
     const size_t i = (size_t)blockIdx.x * BLK + threadIdx.x;
     if (i < n)
@@ -924,16 +901,6 @@ hipError_t launch_copy(int vh, int n, int fs, int fd, const void *src, void *dst
         copy_kernel<HISQ_FP32, HISQ_FP32><<<g, BLK, 0, st>>>(vh, n, src, dst);
     else if (fs == HISQ_FP32 && fd == HISQ_FP64)
         copy_kernel<HISQ_FP32, HISQ_FP64><<<g, BLK, 0, st>>>(vh, n, src, dst);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-hipError_t launch_copy_col(int vh, int fp, int n, int k, const void *src, void *dst, hipStream_t st) {
-    if (fp == HISQ_FP64)
-        copy_col_kernel<HISQ_FP64><<<grid_for(vh), BLK, 0, st>>>(vh, n, k, src, dst);
-    else if (fp == HISQ_FP32)
-        copy_col_kernel<HISQ_FP32><<<grid_for(vh), BLK, 0, st>>>(vh, n, k, src, dst);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

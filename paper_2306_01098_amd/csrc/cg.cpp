@@ -906,9 +906,7 @@ static hisq_status run_multishift(Solver &S, int nshift, const double *shifts, c
         };
         CgScalars c{};
         c.rho = bnorm2;
-        c.rmax2 = bnorm2;
         c.target2 = target2(base);
-        c.delta2 = 0.0;
         c.max_iter = max_iter;
         c.active = 1;
         c.flag = FLAG_RUN;
@@ -945,7 +943,6 @@ static hisq_status run_multishift(Solver &S, int nshift, const double *shifts, c
         vp.st = dst;
         vp.partials = S.partials();
         vp.skip = reinterpret_cast<int *>(S.flags() + F_SKIP);
-        vp.tr_skip = reinterpret_cast<int *>(S.flags() + F_TR0);  // written, not read, here
         vp.nshift = no;
         vp.sh = dsh;
         vp.ms = dms;

@@ -496,26 +496,6 @@ __device__ __forceinline__ double epilogue_y(const DslashParams &prm, int r, con
     return dot;
 }
 
-template <int FP, int EPI, typename A>
-__device__ __forceinline__ double epilogue(const DslashParams &prm, int r, int i, cplx<A> (&v)[3]) {
-    double dot = 0.0;
-    if (EPI != EPI_PLAIN) {
-        cplx<A> yv[3];
-        FieldIO<FP>::template load<A>(prm.y, prm.g.vh, prm.nrhs, r, i, yv);
-        const A ad = (A)prm.ad, ay = (A)ay_of(prm, r);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            v[a].re = fma(ad, v[a].re, ay * yv[a].re);
-            v[a].im = fma(ad, v[a].im, ay * yv[a].im);
-            if (EPI == EPI_AXPY_DOT) {
-                dot = fma((double)yv[a].re, (double)v[a].re, dot);
-                dot = fma((double)yv[a].im, (double)v[a].im, dot);
-            }
-        }
-    }
-    return dot;
-}
-
 // Block partials of the NIN dot products (summed by a finalize kernel).
 template <int NIN>
 __device__ __forceinline__ void dslash_dot_reduce(const DslashParams &prm, double (&dot)[NIN], const BlockPos<NIN> &bp) {

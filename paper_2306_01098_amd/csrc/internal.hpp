@@ -93,8 +93,6 @@ hipError_t launch_stream_read(const void *src, size_t n16, unsigned *sink, hipSt
 hipError_t launch_sum_partials(const double *partials, int nslots, int nblk, double *out, int stride,
                                const int *skip, hipStream_t st);
 hipError_t launch_copy(int vh, int n, int fs, int fd, const void *src, void *dst, hipStream_t st);
-// dst (a one-column field) = column k of the n-column field src (FP64 or FP32).
-hipError_t launch_copy_col(int vh, int fp, int n, int k, const void *src, void *dst, hipStream_t st);
 hipError_t launch_fill_u32(unsigned *p, size_t n, unsigned v, hipStream_t st);
 
 }  // namespace hisq

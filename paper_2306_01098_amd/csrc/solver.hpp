@@ -97,8 +97,8 @@ struct CgVecParams {
     const double *pq_part;
     int pq_nblk;
     int *skip;          // 1 when no right-hand side is active
-    // [nrhs]: 0 while column j waits for its FP64 true residual (set by the
-    // finalize kernel with FLAG_CONV / FLAG_RELIABLE, cleared by the
+    // single-reduction CG, [nrhs]: 0 while column j waits for its FP64 true
+    // residual (set with FLAG_CONV / FLAG_RELIABLE, cleared by the step after the
     // true-residual check), else 1; the check's kernels of column j skip on it
     int *tr_skip;
     int *nopend;  // optional: 0 while any column waits for its true residual, else 1
