@@ -20,8 +20,14 @@ template <int LP> inline bool links_stream(const Geom &g, int nouter) {
 // columns past the last group's end cost their arithmetic, so at most a
 // quarter of the real ones.  FP64: with four columns a thread the loads kept
 // ahead leave one wavefront per SIMD (16 rhs, one thread per site, 48^3x12:
-// 920 -> 962 us; LDS-staged 1550 -> 905), with eight they do not fit.
-template <int FP, int NIN, int VAR> constexpr bool whole_groups_fit() {
+// 920 -> 962 us; LDS-staged 1550 -> 905), with eight they do not fit.  FP16N
+// links with FP32 fields (norms and integers take registers of their own): four
+// columns a thread take 174 to 180 registers so instead of 118 to 141 (M_e with
+// its dot, 16 rhs: one thread per site at 16^3x22 79 us, 63 with the branch;
+// staged at 48^2x24x12 580 and 367; eight a thread staged 420 and 474).
+template <int LP, int FP, int NIN, int VAR> constexpr bool whole_groups_fit() {
+    if (LP == HISQ_FP16N && FP == HISQ_FP32)
+        return NIN <= 2 || (VAR == VAR_LDS && NIN == 8);
     return FP != HISQ_FP64 || NIN <= (VAR == VAR_LDS ? 4 : 2);
 }
 template <int NIN> inline bool groups_whole(int nrhs) {
@@ -43,7 +49,7 @@ hipError_t dslash_go(const DslashParams &prm, DslashShape s, hipStream_t st) {
             p.band = LDS_BAND;
             const size_t shm = lds_stage_bytes(prm.g, FP, NIN);
             const bool nt = links_stream<LP>(prm.g, nouter);
-            constexpr bool W = whole_groups_fit<FP, NIN, VAR_LDS>();
+            constexpr bool W = whole_groups_fit<LP, FP, NIN, VAR_LDS>();
             const bool whole = W && groups_whole<NIN>(prm.nrhs);
             const dim3 grid((unsigned)(nsb * nouter));
             if (nt && whole)
@@ -86,7 +92,7 @@ hipError_t dslash_go(const DslashParams &prm, DslashShape s, hipStream_t st) {
         else
             dslash_dir_kernel<LP, FP, NIN, EPI, false><<<grid, s.block, 0, st>>>(p);
     } else {
-        constexpr bool W = whole_groups_fit<FP, NIN, VAR_SITE>();
+        constexpr bool W = whole_groups_fit<LP, FP, NIN, VAR_SITE>();
         const bool whole = W && groups_whole<NIN>(prm.nrhs);
         if (nt && whole)
             dslash_site_kernel<LP, FP, NIN, EPI, LinkIO<LP>::stream, W><<<grid, s.block, 0, st>>>(p);

@@ -702,3 +702,48 @@ def test_built_in_shapes_of_large_lattices(gpu_lib, dims, prec, nrhs, shape):
     h.hisq_apply_m(lat, prec, 0.3, links, inp, got, tmp, nrhs)
     h.hisq_apply_m(lat, prec, 0.3, links, inp, ref, tmp, nrhs, ctx=one)
     assert torch.equal(got, ref)
+
+
+FP16N_LINK_SHAPES = [(2, 2, 64, 2), (2, 4, 64, 2), (2, 8, 64, 2), (0, 2, 64, 1), (0, 4, 128, 2), (0, 8, 128, 2), None]
+
+
+@pytest.mark.parametrize("nrhs", [3, 4, 6, 7, 8, 13, 14, 16])
+@pytest.mark.parametrize("dims", [(16, 16, 16, 6), (32, 32, 32, 16)])
+def test_fp16n_links_fp32_fields_in_groups(gpu_lib, dims, nrhs):
+    """FP16N links with FP32 fields (the inner operator of FP16N CG), whole and
+    partial groups of two, four and eight columns a thread and the built-in shape
+    (None): the vectors bit for bit those of the columns one by one, the fused
+    <in, M in> within the rounding of sums in another order."""
+    h = gpu_lib
+    lat = h.lattice(dims, -1)
+    fat, naik = _device_links(dims, 72, 0.0)
+    links = h.empty_links(lat, "fp16n")
+    h.hisq_pack_links(lat, "fp16n", fat, naik, links)
+    del fat, naik
+    g = torch.Generator(device="cuda").manual_seed(73)
+    half = torch.view_as_complex(torch.randn(nrhs, gen.volume(dims) // 2, 3, 2, dtype=torch.float64, device="cuda",
+                                             generator=g))
+    inp = torch.zeros(h.hisq_field_bytes(lat, "fp32", nrhs), dtype=torch.uint8, device="cuda")
+    h.hisq_pack_field(lat, "fp32", nrhs, half, inp)
+    del half
+    ws = h.empty_workspace(h.hisq_apply_m_dot_workspace_bytes(lat, nrhs))
+    tmp = torch.zeros_like(inp)
+
+    def run(shape):
+        ctx = h.Context(0)
+        if shape is not None:
+            h.hisq_set_dslash_shape(lat, "fp16n", nrhs, shape, ctx)
+        out = torch.zeros_like(inp)
+        dots = torch.full((nrhs,), float("nan"), dtype=torch.float64, device="cuda")
+        h.hisq_apply_m_dot(lat, "fp16n", "fp32", 0.3, links, inp, out, tmp, dots, ws, nrhs, ctx=ctx)
+        torch.cuda.synchronize()
+        return out, dots
+
+    ref, dref = run((0, 1, 64, 1))
+    for shape in FP16N_LINK_SHAPES:
+        if shape is not None and shape[1] >= 2 * nrhs:
+            continue
+        got, dots = run(shape)
+        assert torch.equal(got, ref), shape
+        # positive terms per site, FP32 within a thread and FP64 from there on
+        assert bool(((dots - dref).abs() <= 1e-6 * dref).all()), shape
