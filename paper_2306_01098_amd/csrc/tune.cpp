@@ -10,41 +10,53 @@
 
 namespace hisq {
 
-// Launch time of a shape on a lattice of a few ten thousand sites per parity:
-// the latency of its chain of loads, which grows with the right-hand sides a
-// thread carries, and a time per 1000 sites and group of right-hand sides
-// (microseconds, fitted to 14 lattices from 4^4 to 48^3x12 at 1 to 16
-// right-hand sides; within 10 % of nearly all of them below 49152 sites).
+// Several right-hand sides below 49152 sites per parity, where a launch is a
+// chain of loads, longer the more columns a thread carries, and a time per 1000
+// sites and group of columns.  The two constants of each shape (microseconds)
+// are those whose least sum picks best among the shapes as measured on 23
+// lattices from 4^3x8 to 10x18x20x26 with 2 to 16 right-hand sides: within 1.5 %
+// of the fastest on average (2 % FP32R12), at worst 20 %.  A launch time by
+// itself is met within 10 to 15 % only.
 struct ShapeCost {
     int variant, nin;
     double fixed, per;
 };
-constexpr ShapeCost COST_FP64[] = {{VAR_DIR, 1, 3.5, 0.239}, {VAR_DIR, 2, 4.1, 0.34},  {VAR_SITE, 1, 4.8, 0.129},
-                                   {VAR_SITE, 2, 6.3, 0.184}, {VAR_SITE, 4, 9.7, 0.295}};
-constexpr ShapeCost COST_FP32[] = {{VAR_DIR, 1, 3.5, 0.148}, {VAR_DIR, 2, 3.8, 0.16},   {VAR_SITE, 1, 4.8, 0.06},
-                                   {VAR_SITE, 2, 6.2, 0.083}, {VAR_SITE, 4, 8.7, 0.141}, {VAR_LDS, 4, 8.2, 0.135}};
-constexpr ShapeCost COST_FP16[] = {{VAR_DIR, 1, 3.5, 0.074}, {VAR_SITE, 1, 4.4, 0.036}};
+constexpr ShapeCost COST_FP64[] = {{VAR_DIR, 1, 0.52, 0.3697},  {VAR_DIR, 2, 1.48, 0.4520},  {VAR_SITE, 1, 3.75, 0.1131},
+                                   {VAR_SITE, 2, 4.74, 0.1673}, {VAR_SITE, 4, 7.44, 0.2526}, {VAR_LDS, 4, 7.65, 0.2481}};
+constexpr ShapeCost COST_FP64R12[] = {{VAR_DIR, 1, 2.56, 0.2299},  {VAR_DIR, 2, 4.12, 0.2066},
+                                      {VAR_SITE, 1, 4.62, 0.1034}, {VAR_SITE, 2, 4.99, 0.1417},
+                                      {VAR_SITE, 4, 11.72, 0.2120}, {VAR_LDS, 4, 7.95, 0.2179}};
+constexpr ShapeCost COST_FP32[] = {{VAR_DIR, 1, 1.95, 0.2409},  {VAR_DIR, 2, 2.53, 0.2152},  {VAR_SITE, 1, 4.31, 0.0634},
+                                   {VAR_SITE, 2, 5.33, 0.0773}, {VAR_SITE, 4, 7.30, 0.1068}, {VAR_LDS, 4, 7.83, 0.0959}};
+constexpr ShapeCost COST_FP32R12[] = {{VAR_DIR, 1, 2.26, 0.1771},  {VAR_DIR, 2, 3.60, 0.1360},
+                                      {VAR_SITE, 1, 4.31, 0.0536}, {VAR_SITE, 2, 5.61, 0.0677},
+                                      {VAR_SITE, 4, 7.74, 0.1036}, {VAR_LDS, 4, 8.77, 0.0894}};
+constexpr ShapeCost COST_FP16[] = {{VAR_DIR, 1, 2.49, 0.0897}, {VAR_SITE, 1, 4.18, 0.0369}, {VAR_SITE, 2, 5.36, 0.0627}};
 
-// Several right-hand sides on a lattice that one thread per site and group of
-// right-hand sides spreads over too few wavefronts.
-DslashShape small_multi_shape(const Geom &g, int fp, int nrhs) {
-    const ShapeCost *c = fp == HISQ_FP64 ? COST_FP64 : fp == HISQ_FP32 ? COST_FP32 : COST_FP16;
-    const int n = fp == HISQ_FP64 ? (int)std::size(COST_FP64)
-                  : fp == HISQ_FP32 ? (int)std::size(COST_FP32) : (int)std::size(COST_FP16);
+DslashShape small_multi_shape(const Geom &g, int lp, int fp, int nrhs) {
+    const ShapeCost *c = COST_FP32;
+    int n = (int)std::size(COST_FP32);
+    if (fp == HISQ_FP64)
+        c = lp == HISQ_FP64R12 ? COST_FP64R12 : COST_FP64;  // as many entries as COST_FP32
+    else if (fp == HISQ_FP16N)
+        c = COST_FP16, n = (int)std::size(COST_FP16);
+    else if (lp == HISQ_FP32R12)
+        c = COST_FP32R12;
     DslashShape best{};
     double least = 1e30;
     for (int k = 0; k < n; ++k) {
+        // blocks of 64 in plain order: the z-slab order gains from 55000 sites on
         DslashShape s{c[k].variant, c[k].nin, 64, 1};
         if (s.variant == VAR_LDS)
             s = DslashShape{VAR_LDS, s.nin, LDS_BAND * g.hx, 2};
-        else if (fp == HISQ_FP16N && s.variant == VAR_SITE && g.vh >= 16384)
-            s.block = 256;
+        else if (fp == HISQ_FP16N && s.nin == 2)
+            s = DslashShape{VAR_SITE, 2, 256, g.nz % 8 == 0 ? 2 : 1};
         if (s.nin >= 2 * nrhs || (s.variant == VAR_LDS && (nrhs < 4 || !dslash_shape_fits(s, g, fp))))
             continue;
-        if (fp == HISQ_FP64 && s.variant == VAR_SITE && s.nin == 1 && g.vh > 8192)
-            continue;  // 12288 and 16800 sites: 10-30 % slower than two a thread
-        if (s.variant == VAR_SITE && g.vh >= 32768 && g.nz % 8 == 0)
-            s.xcd_remap = 2;
+        if (lp == HISQ_FP16N && fp == HISQ_FP32 && (s.nin == 4 || (s.variant == VAR_SITE && s.nin == 2 && nrhs == 3)))
+            continue;  // four: see large_multi_fp32; three columns, one / two a thread at 16^4: 20.5 / 23.1 us
+        if (fp == HISQ_FP64 && lp != HISQ_FP64R12 && s.variant == VAR_SITE && s.nin == 1 && g.vh > 8192)
+            continue;  // 13440 and 16384 sites, two and three columns: 8 to 25 % slower than two a thread
         const double t = c[k].fixed + c[k].per * 1e-3 * g.vh * ((nrhs + s.nin - 1) / s.nin);
         if (t < least) {
             least = t;
@@ -54,65 +66,94 @@ DslashShape small_multi_shape(const Geom &g, int fp, int nrhs) {
     return best;
 }
 
-// Several right-hand sides on lattices that fill the chip.  The lines lie
-// between measured launches at 48^3x12, 32^3x8, 24^3x12 (times below in this
-// order; z-slab order in 8-row y-bands where N_z allows it), a few at 20^3x24,
-// 32^3x16, 48^3x8, 32^2x48x12, 32^2x64x8, 48^2x32x8, 64x32^2x8 and 64^3x6.
+// Several right-hand sides on larger lattices.  The lines lie between launches
+// measured at 16 lattices from 49152 to 331776 sites with 2 to 16 right-hand
+// sides (z-slab order in 8-row y-bands where N_z allows it); times below in
+// microseconds.
 //
 // FP32 fields: groups of eight columns, or of four where that leaves fewer
 // empty places, staged in LDS once links and vectors exceed the MALL (the
-// neighbour rows then come from HBM), else through the caches:
-// FP32 links, 16 rhs: staged 4 / staged 8 / site 8: 414 / 380 / 425, 79 / 84 /
-// 72, - / - / 54 us; 8 rhs: 251 / 212 / 238, 46 / 47 / 43 and site 4 41, site 4
-// / 8 31 / 36; 5 rhs staged 8 190, site 8 205; 40; 26.  FP32R12 links, 16 rhs:
-// 355 / 340 / 379, 70 / 77 / 69; FP32W14 402 / 369 / 411, 79 / 81 / 72.
+// neighbour rows then come from HBM), else through the caches.  16 rhs at
+// 48^3x12, staged 4 / staged 8 / site 8: 414 / 380 / 425, FP32R12 355 / 340 /
+// 379, FP32W14 402 / 369 / 411.  From ten columns staged in any case: a solver
+// moves more between two launches (32^3x8 at 16 rhs, 60 iterations of CG: site 8
+// 20.7 ms, staged 20.0); FP32W14 from seven (48x16^2x24, 8 rhs: site 4 59.2,
+// staged 4 52.7; 32^3x8 43.0 / 42.6).
+// Five and six columns within the MALL: two a thread with FP32R12 (48x16^2x24
+// 41.6, site 8 50.1; 24^3x12 23.1 / 24.7), else eight, which saves a pass over
+// the links (24^3x12, site 2 / 4 / 8: 28.5 / 36.0 / 27.1), but two below 73728
+// sites (24x16^3 19.4 / 19.7 / 20.6, FP32W14 18.6 / 18.8 / 20.5).  FP32R12 beyond
+// the MALL two a thread, staged (32^3x16, 2 / 4 / 8: 70.7 / 84.1 / 72.8).
+// Three columns: two a thread, blocks of 64, between 43008 and 53248 sites (24x16^3,
+// one / two / four a thread: 17.0 / 13.8 / 15.2; 10x18x20x26 16.8 / 12.8 / 13.6,
+// FP32R12 13.9 / 12.2 / 13.7).
+// FP16N links (both halves of the operator): two a thread, whose loads go out
+// ahead of the arithmetic within 128 registers, staged in LDS where that fits,
+// from 262144 sites four (48^2x24x12, staged 2 / staged 4 / site 8: 6 rhs 173 / 177 /
+// 212; 16 rhs 416 / 367 / 462; 32^3x8, 16 rhs 138 / 152 / 173; 24^3x12, site 2 / 4 /
+// 8: 6 rhs 47 / 57 / 56, 16 rhs 102 / 111 / 128).
 DslashShape large_multi_fp32(const Geom &g, int lp, int nrhs) {
     const int remap = g.nz % 8 == 0 ? 2 : 1;
     const bool large = links_bytes(g, lp) + 2 * field_bytes(g, HISQ_FP32, nrhs) > MALL_BYTES;
-    const int eights = (nrhs + 7) / 8 * 8 - nrhs <= 3;  // 5 .. 8, 13 .. 16
-    // (from ten columns staged in any case: a solver moves more between two
-    // launches; 32^3x8 at 16 rhs is not large by itself, 72 us with eight through
-    // the caches, but 60 iterations of its CG take 20.7 ms then and 20.0 staged)
-    if (large || nrhs > 9) {
-        const DslashShape l{VAR_LDS, nrhs == 2 ? 2 : eights && large ? 8 : 4, LDS_BAND * g.hx, 2};
+    const bool r12 = lp == HISQ_FP32R12, five_six = nrhs == 5 || nrhs == 6;
+    const auto staged = [&](int nin) { return DslashShape{VAR_LDS, nin, LDS_BAND * g.hx, 2}; };
+    if (lp == HISQ_FP16N && nrhs >= 4) {
+        const DslashShape l = staged(g.vh >= (1 << 18) && nrhs >= 7 ? 4 : 2);
+        return dslash_shape_fits(l, g, HISQ_FP32) ? l : DslashShape{VAR_SITE, 2, 128, remap};
+    }
+    if (five_six && (r12 || g.vh < 73728))
+        return large && dslash_shape_fits(staged(2), g, HISQ_FP32) ? staged(2) : DslashShape{VAR_SITE, 2, 128, remap};
+    const bool eights = large && (nrhs + 7) / 8 * 8 - nrhs <= 3;  // 5 .. 8, 13 .. 16
+    if (large || nrhs > 9 || (lp == HISQ_FP32W14 && nrhs >= 7)) {
+        const DslashShape l = staged(nrhs == 2 ? 2 : eights ? 8 : 4);
         if (dslash_shape_fits(l, g, HISQ_FP32))
             return l;
         // (64x32^2x8, which fits four columns, not eight: staged 4 / site 8, 8
         // rhs 114 / 101, 16 rhs 225 / 225)
-        if (eights && large && lp != HISQ_FP32R12)  // FP32R12, 16 rhs at 44x36x28x14: site 4 / 8 196 / 204
+        if (eights && !r12)  // FP32R12, 16 rhs at 44x36x28x14: site 4 / 8 196 / 204
             return DslashShape{VAR_SITE, 8, g.vh >= (1 << 22) ? 256 : 128, remap};
     }
-    if (nrhs == 5 || nrhs == 6)
+    if (five_six)
         return DslashShape{VAR_SITE, 8, 128, remap};
-    if (nrhs == 2 || (nrhs == 9 && !large))  // 9: 40.5 us against 49 as 4 + 4 + 1
+    // (9: 24^3x12 40.5 against 49 as 4 + 4 + 1; 3, FP32R12: 24^3x8, two / four 13.4 / 14.6)
+    if (nrhs == 2 || (nrhs == 9 && !large) || (nrhs == 3 && r12 && g.vh < 73728))
         return DslashShape{VAR_SITE, 2, 128, remap};
-    return DslashShape{VAR_SITE, 4, nrhs <= 4 || nrhs > 12 ? 128 : 256, remap};
+    // blocks of 256: four columns, 24^3x8 128 / 256 16.0 / 14.9, but 24^3x12 22.1 / 24.1;
+    // 14 columns, 24^3x8 36.0 / 34.5
+    return DslashShape{VAR_SITE, 4, g.vh < 73728 || (nrhs > 4 && nrhs <= 12) ? 256 : 128, remap};
 }
 
 // FP64 fields: four columns a thread, staged in LDS once the links exceed the
-// MALL (16 rhs, site 4 / staged 4: FP64 918 / 906, 203 / 190 us; 8 rhs 538 / 519,
-// 117 / 111; 16 rhs FP64R12 834 / 749, FP64W14 890 / 870, 196 / 179).  Five and
-// six: eight a thread, in registers beyond the first 256, which saves a pass
-// over the links (6 rhs, site 4 / 8: 468 / 406, 100 / 84; 8 rhs gained at two
-// lattices and lost at 24x16x32x44, 236 / 263).  Links within the MALL: two a
-// thread where groups of four would be half empty (6 rhs at 24^3x12: 65 / 55,
-// FP64R12 57 / 45; 14 rhs 112 / 100, 104 / 85, on small lattices only: 32^3x8
-// FP64R12 153 / 164).
+// MALL (48^3x12 and 32^3x8, 16 rhs, site 4 / staged 4: FP64 918 / 906, 203 / 190;
+// 8 rhs 538 / 519, 117 / 111; 16 rhs FP64R12 834 / 749, FP64W14 890 / 870, 196 /
+// 179).  Where groups of four would be half empty (5, 6, 9, 10, 13, 14): two a
+// thread while the links leave room for the vectors in the MALL (24^3x12, 14
+// rhs, two / four: 103 / 114; 6 rhs FP64R12 45 / 57), beyond that four (30x28x26x10,
+// 9 rhs: 130 / 107, FP64W14 112 / 97, 6 rhs 87 / 82) and five and six eight, in
+// registers beyond the first 256, which saves a pass over the links (30x28x26x10,
+// 6 rhs 79; 48^3x12 468 / 406); FP64R12 staged or, where that does not fit, four
+// in blocks of 64 (28x26x24x18, 9 rhs, two / four 153 / 133; five and six columns
+// stay two a thread up to 256 MB of links: 48x16^2x24, 6 rhs 91 / 98).
 DslashShape large_multi_fp64(const Geom &g, int lp, int nrhs) {
     const int remap = g.nz % 8 == 0 ? 2 : 1;
     // (two at 18x16x18x14: blocks of 128 19.6 us, of 64 15.2; 24^3x12 34.6 / 35.6)
     const DslashShape four{VAR_SITE, nrhs == 2 ? 2 : 4, nrhs == 2 && g.vh < 65536 ? 64 : 128, remap};
-    const bool half = nrhs % 4 == 1 || nrhs % 4 == 2;
     if (nrhs <= 3)  // three as one group of four: 24^3x12 57 -> 42 us
         return four;
-    if (links_bytes(g, lp) < MALL_BYTES)
-        return half && (nrhs <= 10 || g.vh < 98304) ? DslashShape{VAR_SITE, 2, 64, remap} : four;
-    if (lp != HISQ_FP64R12 && (nrhs == 5 || nrhs == 6))
-        return DslashShape{VAR_SITE, 8, 128, remap};
-    if (lp != HISQ_FP64R12 && nrhs > 4 && half)  // 14 rhs, site 4 / staged 4: 821 / 864
-        return four;
+    const bool r12 = lp == HISQ_FP64R12, half = nrhs % 4 == 1 || nrhs % 4 == 2;
+    const size_t links = links_bytes(g, lp);
     const DslashShape l{VAR_LDS, 4, LDS_BAND * g.hx, 2};
-    return dslash_shape_fits(l, g, HISQ_FP64) ? l : four;
+    const bool fits = dslash_shape_fits(l, g, HISQ_FP64);
+    if (half) {
+        if (links < (r12 && nrhs <= 6 ? MALL_BYTES : (size_t)200000000))
+            return DslashShape{VAR_SITE, 2, 64, r12 ? remap : 1};
+        if (nrhs <= 6 && !r12)
+            return DslashShape{VAR_SITE, 8, 128, remap};
+        if (r12 && fits)
+            return l;
+        return links < MALL_BYTES || r12 ? DslashShape{VAR_SITE, 4, 64, 1} : four;
+    }
+    return links >= MALL_BYTES && fits ? l : four;
 }
 
 // FP16N fields: two columns a thread; two and three columns one by one below
@@ -162,22 +203,16 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
         }
         return s;
     }
-    // 5 and 16 rhs at 8^4: FP32 11.0 -> 4.6 and 18.4 -> 5.8 us, FP64 13.0 -> 5.8
-    // and 13.2 -> 6.7; 3 rhs at 20x12x14x10: FP32 9.0 -> 7.7, FP16N 11.2 ->
-    // 5.2.  From 49152 sites (FP64: 32768) the shapes below are as fast.  The
-    // smallest lattices that the LDS staging fits (16x8x8x8) keep it: the
-    // solver's test of the staged kernels runs there.
-    const bool staged = fp == HISQ_FP32 && nrhs >= 4 && g.vh <= 4096 &&
-                        dslash_shape_fits(DslashShape{VAR_LDS, 4, LDS_BAND * g.hx, 2}, g, fp);
-    // three FP32 columns: two a thread from 40960 sites (one / two: FP32 links
-    // 16x8x32x22 16.8 / 14.1 us, FP32R12 10x18x20x26 14.0 / 12.2, 16^3x22 13.8 /
-    // 12.4, at 14^2x18x20 11.0 / 11.5)
-    if (fp == HISQ_FP32 && nrhs == 3 && g.vh >= 40960 && g.vh < 49152)
-        return DslashShape{VAR_SITE, 2, 128, g.nz % 8 == 0 ? 2 : 1};
-    if (!staged && g.vh < (fp == HISQ_FP64 ? 32768 : 49152))
-        return small_multi_shape(g, fp, nrhs);
-    if (staged)
-        return DslashShape{VAR_LDS, 4, LDS_BAND * g.hx, 2};
+    // The smallest lattices that the LDS staging fits keep it by contract, not for
+    // its speed: 16x8x8x8, 6 FP32 columns 10.0 us and 31.7 ms in a CG solve against
+    // 5.0 and 21.7 by the cost table (16 columns 8.9 and 30.5 against 8.8 and 31.4).
+    const DslashShape staged{VAR_LDS, 4, LDS_BAND * g.hx, 2};
+    if (fp == HISQ_FP32 && nrhs >= 4 && g.vh <= 4096 && dslash_shape_fits(staged, g, fp))
+        return staged;
+    if (fp == HISQ_FP32 && nrhs == 3 && g.vh >= 43008 && g.vh < 53248)  // see large_multi_fp32
+        return DslashShape{VAR_SITE, 2, 64, 1};
+    if (g.vh < 49152)
+        return small_multi_shape(g, lp, fp, nrhs);
     return fp == HISQ_FP64   ? large_multi_fp64(g, lp, nrhs)
            : fp == HISQ_FP32 ? large_multi_fp32(g, lp, nrhs)
                              : large_multi_fp16(g, nrhs);

@@ -650,7 +650,11 @@ def _device_links(dims, seed, naik_phase):
 # a thread of the built-in shape)
 LARGE_SHAPES = [
     ((32, 16, 16, 16), "fp32", 10, (2, 4)), ((32, 16, 16, 16), "fp32", 16, (2, 4)),    # ten columns: staged
-    ((32, 16, 16, 16), "fp32", 8, (0, 4)), ((32, 16, 16, 16), "fp32", 6, (0, 8)),
+    ((32, 16, 16, 16), "fp32", 8, (0, 4)), ((32, 16, 16, 16), "fp32", 6, (0, 2)), ((24, 24, 24, 12), "fp32", 6, (0, 8)),
+    ((16, 16, 16, 16), "fp32", 14, (2, 4)), ((20, 16, 14, 18), "fp32", 10, (0, 4)), ((10, 18, 20, 26), "fp32r12", 3, (0, 2)),
+    ((24, 24, 24, 12), "fp64", 14, (0, 2)), ((30, 28, 26, 10), "fp64", 9, (0, 4)), ((30, 28, 26, 10), "fp64", 6, (0, 8)),
+    ((48, 16, 16, 24), "fp32w14", 8, (2, 4)), ((24, 24, 24, 12), "fp32r12", 6, (0, 2)), ((32, 32, 32, 16), "fp32r12", 6, (2, 2)),
+    ((24, 24, 24, 12), "fp64r12", 9, (0, 2)), ((28, 26, 24, 18), "fp64r12", 9, (0, 4)), ((32, 32, 32, 12), "fp64r12", 10, (2, 4)),
     ((32, 32, 32, 8), "fp64", 3, (0, 4)), ((32, 32, 32, 8), "fp64", 4, (2, 4)),        # links above 256 MB
     ((32, 32, 32, 8), "fp64", 5, (0, 8)), ((32, 32, 32, 8), "fp64", 8, (2, 4)),
     ((32, 32, 32, 8), "fp64", 14, (0, 4)), ((32, 32, 32, 8), "fp64w14", 8, (2, 4)),
@@ -670,10 +674,10 @@ def test_built_in_shapes_of_large_lattices_are_those_tested(gpu_lib):
 
 @pytest.mark.parametrize("dims,prec,nrhs,shape", LARGE_SHAPES)
 def test_built_in_shapes_of_large_lattices(gpu_lib, dims, prec, nrhs, shape):
-    """The built-in shapes beyond the last-level cache and the one staged by
-    default, with whole and partial groups and non-temporal link loads (one
-    group of FP64, FP32 or W14 links): plain and with the epilogue, bit for bit
-    the columns one by one, one thread per site."""
+    """The built-in shapes on both sides of the rule's lines, among them those beyond
+    the last-level cache and those staged by default, with whole and partial groups
+    and non-temporal link loads (one group of FP64, FP32 or W14 links): plain and
+    with the epilogue, bit for bit the columns one by one, one thread per site."""
     h = gpu_lib
     lat = h.lattice(dims, -1)
     f = "fp16n" if prec == "fp16n" else prec[:4]
