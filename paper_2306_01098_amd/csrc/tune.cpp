@@ -83,7 +83,9 @@ DslashShape small_multi_shape(const Geom &g, int lp, int fp, int nrhs) {
 // 41.6, site 8 50.1; 24^3x12 23.1 / 24.7), else eight, which saves a pass over
 // the links (24^3x12, site 2 / 4 / 8: 28.5 / 36.0 / 27.1), but two below 73728
 // sites (24x16^3 19.4 / 19.7 / 20.6, FP32W14 18.6 / 18.8 / 20.5).  FP32R12 beyond
-// the MALL two a thread, staged (32^3x16, 2 / 4 / 8: 70.7 / 84.1 / 72.8).
+// the MALL two a thread, staged (32^3x16, 2 / 4 / 8: 70.7 / 84.1 / 72.8), where that
+// does not fit two below 262144 sites, eight above (site 2 / 8, 28x26x24x18 43.9 /
+// 49.7, 44x36x28x14 107.0 / 101.6, 36^3x16 130.8 / 119.7).
 // Three columns: two a thread, blocks of 64, between 43008 and 53248 sites (24x16^3,
 // one / two / four a thread: 17.0 / 13.8 / 15.2; 10x18x20x26 16.8 / 12.8 / 13.6,
 // FP32R12 13.9 / 12.2 / 13.7).
@@ -101,8 +103,11 @@ DslashShape large_multi_fp32(const Geom &g, int lp, int nrhs) {
         const DslashShape l = staged(g.vh >= (1 << 18) && nrhs >= 7 ? 4 : 2);
         return dslash_shape_fits(l, g, HISQ_FP32) ? l : DslashShape{VAR_SITE, 2, 128, remap};
     }
-    if (five_six && (r12 || g.vh < 73728))
-        return large && dslash_shape_fits(staged(2), g, HISQ_FP32) ? staged(2) : DslashShape{VAR_SITE, 2, 128, remap};
+    if (five_six && (r12 || g.vh < 73728)) {
+        if (large && dslash_shape_fits(staged(2), g, HISQ_FP32))
+            return staged(2);
+        return DslashShape{VAR_SITE, g.vh >= (1 << 18) ? 8 : 2, 128, remap};
+    }
     const bool eights = large && (nrhs + 7) / 8 * 8 - nrhs <= 3;  // 5 .. 8, 13 .. 16
     if (large || nrhs > 9 || (lp == HISQ_FP32W14 && nrhs >= 7)) {
         const DslashShape l = staged(nrhs == 2 ? 2 : eights ? 8 : 4);
@@ -174,7 +179,7 @@ DslashShape default_shape(const Geom &g, int lp, int fp, int nrhs) {
     if (nrhs == 1) {
         s.nin = 1;
         // Small lattices cannot fill 256 CUs with one thread per site in
-        // blocks of 256: up to 16384 sites per parity (49152 for FP32 and
+        // blocks of 256: up to 24576 sites per parity (49152 for FP32 and
         // FP16N links) four lanes per site (8^4 .. 16^3x8: 9.6-16.1 -> 9.2-9.3
         // us FP64; 16^4 FP32 12.2 -> 9.4 us), below 131072 blocks of 64
         // (24^3x6 FP64 19.4 -> 16.6 us).  FP64 at 20x12x14x10 (16800): 12.5 ->

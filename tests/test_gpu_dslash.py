@@ -654,6 +654,7 @@ LARGE_SHAPES = [
     ((16, 16, 16, 16), "fp32", 14, (2, 4)), ((20, 16, 14, 18), "fp32", 10, (0, 4)), ((10, 18, 20, 26), "fp32r12", 3, (0, 2)),
     ((24, 24, 24, 12), "fp64", 14, (0, 2)), ((30, 28, 26, 10), "fp64", 9, (0, 4)), ((30, 28, 26, 10), "fp64", 6, (0, 8)),
     ((48, 16, 16, 24), "fp32w14", 8, (2, 4)), ((24, 24, 24, 12), "fp32r12", 6, (0, 2)), ((32, 32, 32, 16), "fp32r12", 6, (2, 2)),
+    ((44, 36, 28, 14), "fp32r12", 6, (0, 8)), ((28, 26, 24, 18), "fp32r12", 5, (0, 2)),
     ((24, 24, 24, 12), "fp64r12", 9, (0, 2)), ((28, 26, 24, 18), "fp64r12", 9, (0, 4)), ((32, 32, 32, 12), "fp64r12", 10, (2, 4)),
     ((32, 32, 32, 8), "fp64", 3, (0, 4)), ((32, 32, 32, 8), "fp64", 4, (2, 4)),        # links above 256 MB
     ((32, 32, 32, 8), "fp64", 5, (0, 8)), ((32, 32, 32, 8), "fp64", 8, (2, 4)),
