@@ -199,7 +199,8 @@ hisq_status hisq_dslash(hisq_context *ctx, const hisq_lattice *lat, hisq_prec pr
  * c_Naik = -1/24 + naik_eps/8 the Naik links; links periodic.  All three
  * fields are device complex128 arrays in the canonical layout
  * (4, Nt, Nz, Ny, Nx, 3, 3) (pass fat and naik to hisq_pack_links).  FP64.
- *   ws  workspace of hisq_smear_workspace_bytes(lat) bytes (44 matrices per site).
+ *   ws  workspace of hisq_smear_workspace_bytes(lat) bytes (44 matrices per site,
+ *       of which the call uses 32).
  * thin, fat and naik must be distinct.  Asynchronous. */
 size_t hisq_smear_workspace_bytes(const hisq_lattice *lat);
 hisq_status hisq_smear_links(hisq_context *ctx, const hisq_lattice *lat, const void *thin_c128, double naik_eps,

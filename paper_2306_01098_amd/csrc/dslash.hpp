@@ -191,9 +191,9 @@ template <int FP, int NIN, bool ALL> __device__ __forceinline__ int col_at(int r
 }
 
 // Hops that the loads of links run ahead with several columns: two where four
-// columns a thread leave the registers for it (16 rhs FP32 at 32^3x8: 92 -> 82
-// us; NIN 8 72 -> 73; FP32R12, whose third row is rebuilt in registers, 24^3x12
-// 48.2 -> 49.9).
+// columns a thread leave the registers for it (16 rhs FP32 at 32^3x8, one thread
+// per site: 93 -> 80 us; NIN 8 73 -> 76; FP32R12, whose third row is rebuilt in
+// registers, 68.6 -> 74.5).
 template <int LP, int FP, int NIN, bool ALL> __device__ __forceinline__ constexpr int links_ahead() {
     return ALL && NIN == 4 && FP != HISQ_FP64 && !LinkIO<LP>::rebuild ? 2 : 1;
 }
@@ -201,9 +201,9 @@ template <int LP, int FP, int NIN, bool ALL> __device__ __forceinline__ constexp
 // Between the loads of the next hops and the arithmetic of this one, for
 // groups of several columns without branches: left alone, the compiler moves
 // each load down to its use to hold fewer registers, and nothing is in flight
-// while it computes (16 rhs FP32 at 48^3x12, one thread per site with NIN 8:
-// 459 us with a branch per column, 567 without, 427 with this; LDS-staged with
-// NIN 8: 399, 390, 384; 32^3x8, NIN 8: 90, 105, 74).
+// while it computes (16 rhs FP32 with NIN 8, with a branch per column / without /
+// without and with this: 48^3x12 one thread per site 461 / 656 / 425 us, LDS-staged
+// 391 / 388 / 383; 32^3x8 one thread per site 98 / 118 / 73).
 template <bool ALL, int NIN> __device__ __forceinline__ void keep_loads_ahead() {
     if constexpr (ALL && NIN > 1)
         __builtin_amdgcn_sched_barrier(0);
@@ -828,7 +828,7 @@ __global__ void __launch_bounds__(256) dslash_lds_kernel(const DslashParams prm)
         const int par = (mu >= 1 ? s.x : 0) + (mu >= 2 ? s.y : 0) + (mu >= 3 ? s.z : 0);
         return (par & 1) ? (A)-1 : (A)1;
     };
-    // loads run one hop ahead, two with four columns (16 rhs FP32 at 48^3x12: 424 -> 414 us; NIN 8 381 -> 434)
+    // loads run one hop ahead, two with four columns (16 rhs FP32 at 48^3x12: 423 -> 414 us; NIN 8 383 -> 434)
     constexpr int D = links_ahead<LP, FP, NIN, ALL>();
     HopBuf<NIN, A> buf[D + 1];
     A sgn[D + 1];

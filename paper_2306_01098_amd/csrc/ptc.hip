@@ -20,11 +20,11 @@
 // and the gradients of the 720 weights follow from it by the chain rule.
 //
 // Bound: memory.  At 32^4 the forward pass reads the links once (302 MB),
-// writes and reads the eight half-lattice vectors (101 MB each) and takes 117
-// us (spread 91, 4.6 TB/s, gather 26, 5.3 TB/s); layer by layer it took 753 us,
-// 460 of them FP32 arithmetic of the 8 -> 8 layer.  The backward pass with
-// input gradient took 2.2 ms; training on four pairs at 16^4 1656 -> 135 us,
-// small lattices bound by the launches.
+// writes and reads the eight half-lattice vectors (101 MB in all, each way) and
+// takes 118 to 127 us (fold 5, spread 86, 4.8 TB/s, gather 24, 4.8 TB/s); layer by
+// layer it took 753 us, 460 of them FP32 arithmetic of the 8 -> 8 layer.  The
+// backward pass with input gradient 2.2 ms -> 208 us (correlation 81); training
+// on four pairs at 16^4 1656 -> 132 us, small lattices bound by the launches.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(576) fold_kernel(const float2 *weights, double
 // Two wavefronts spread 64 odd sites, one with the hops in x and y and one with
 // those in z and t: four links a thread.  With all eight hops in a thread the
 // links and vectors take over 256 VGPRs and one wavefront per SIMD is left (118
-// us at 32^4 instead of 91).
+// us at 32^4 instead of 86).
 constexpr int CS = PB / 2;  // sites of a block
 
 // First half of the folded network on the odd sites y: the transported vectors

@@ -20,7 +20,7 @@
 // with matrices stored whole took 21.1 ms; element planes (whole-line loads),
 // 12 instead of 24 fields from pass 1 and the projection and Naik links fused
 // into pass 3 9.3 ms, with the block order of work_item 8.3 ms, with products
-// accumulated by FMA 7.8 ms, with pass 2's three fields in a thread 7.6 ms.
+// accumulated by FMA and pass 2's three fields in a thread 7.8 ms.
 // The staples run in loops that are not unrolled, so that one staple's three
 // matrices are in registers at a time; forced below 256 VGPRs (three
 // wavefronts per SIMD) the kernels spill and take 22 ms.
@@ -462,7 +462,7 @@ SmearLayout smear_layout(int64_t V) {
     L.y = L.u + 4 * V * mat;
     L.z = L.y + 4 * V * mat;
     L.r = L.z + 12 * V * mat;
-    L.total = 44 * V * mat;
+    L.total = 44 * V * mat;  // the size callers were told before the fields were 32 matrices a site
     return L;
 }
 
